@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -118,56 +119,56 @@ int end_launch(const char* what)
     return e == hipSuccess ? AVION_OK : hip_fail(e, what);
 }
 
-template <int D, int NW, typename E, bool CAUSAL>
+template <int D, int NW, int KG, typename E, bool CAUSAL>
 int launch_fwd(const raw16* q, const raw16* k, const raw16* v, raw16* o, float* lse, int B, int H, int N, Strides rs,
                float scale, hipStream_t st)
 {
-    using Cfg = FwdCfg<D, NW>;
+    using Cfg = FwdCfg<D, NW, KG>;
     static std::atomic<bool> lds_allowed{false};
-    const hipError_t attr = allow_lds(avion_fwd_kernel<D, NW, E, CAUSAL>, Cfg::LDS_BYTES, lds_allowed);
+    const hipError_t attr = allow_lds(avion_fwd_kernel<D, NW, KG, E, CAUSAL>, Cfg::LDS_BYTES, lds_allowed);
     if (attr != hipSuccess) return hip_fail(attr, "hipFuncSetAttribute(fwd)");
     const int nqb = (N + Cfg::BM - 1) / Cfg::BM;
     const long long nblocks = (long long)nqb * B * H;
     unsigned grid;
     if (!grid_for(nblocks, &grid)) return AVION_EUNSUPPORTED;
     begin_launch();
-    hipLaunchKernelGGL((avion_fwd_kernel<D, NW, E, CAUSAL>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, o, lse, H, N, rs.qkv,
+    hipLaunchKernelGGL((avion_fwd_kernel<D, NW, KG, E, CAUSAL>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, o, lse, H, N, rs.qkv,
                        rs.o, nqb, (int)nblocks, scale * kLog2e);
     return end_launch("launch avion_fwd_kernel");
 }
 
-template <int D, int NW, typename E, bool CAUSAL>
+template <int D, int NW, int KG, typename E, bool CAUSAL>
 int launch_dq(const raw16* q, const raw16* k, const raw16* v, const raw16* o, const raw16* dO, const float* lse, raw16* dq,
               float* rowsc, int B, int H, int N, Strides rs, float scale, hipStream_t st)
 {
-    using Cfg = DqCfg<D, NW>;
+    using Cfg = DqCfg<D, NW, KG>;
     static std::atomic<bool> lds_allowed{false};
-    const hipError_t attr = allow_lds(avion_dq_kernel<D, NW, E, CAUSAL>, Cfg::LDS_BYTES, lds_allowed);
+    const hipError_t attr = allow_lds(avion_dq_kernel<D, NW, KG, E, CAUSAL>, Cfg::LDS_BYTES, lds_allowed);
     if (attr != hipSuccess) return hip_fail(attr, "hipFuncSetAttribute(dq)");
     const int nqb = (N + Cfg::BM - 1) / Cfg::BM;
     const long long nblocks = (long long)nqb * B * H;
     unsigned grid;
     if (!grid_for(nblocks, &grid)) return AVION_EUNSUPPORTED;
     begin_launch();
-    hipLaunchKernelGGL((avion_dq_kernel<D, NW, E, CAUSAL>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, o, dO, lse, dq,
+    hipLaunchKernelGGL((avion_dq_kernel<D, NW, KG, E, CAUSAL>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, o, dO, lse, dq,
                        rowsc, H, N, rs.qkv, rs.o, nqb, (int)nblocks, scale * kLog2e, scale);
     return end_launch("launch avion_dq_kernel");
 }
 
-template <int D, int NW, typename E, bool CAUSAL>
+template <int D, int NW, int KG, typename E, bool CAUSAL>
 int launch_dkdv(const raw16* q, const raw16* k, const raw16* v, const raw16* dO, const float* rowsc, raw16* dk, raw16* dv,
                 int B, int H, int N, Strides rs, float scale, hipStream_t st)
 {
-    using Cfg = DkvCfg<D, NW>;
+    using Cfg = DkvCfg<D, NW, KG>;
     static std::atomic<bool> lds_allowed{false};
-    const hipError_t attr = allow_lds(avion_dkdv_kernel<D, NW, E, CAUSAL>, Cfg::LDS_BYTES, lds_allowed);
+    const hipError_t attr = allow_lds(avion_dkdv_kernel<D, NW, KG, E, CAUSAL>, Cfg::LDS_BYTES, lds_allowed);
     if (attr != hipSuccess) return hip_fail(attr, "hipFuncSetAttribute(dkdv)");
     const int nkb = (N + Cfg::BNK - 1) / Cfg::BNK;
     const long long nblocks = (long long)nkb * B * H;
     unsigned grid;
     if (!grid_for(nblocks, &grid)) return AVION_EUNSUPPORTED;
     begin_launch();
-    hipLaunchKernelGGL((avion_dkdv_kernel<D, NW, E, CAUSAL>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, dO, rowsc, dk,
+    hipLaunchKernelGGL((avion_dkdv_kernel<D, NW, KG, E, CAUSAL>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, dO, rowsc, dk,
                        dv, H, N, rs.qkv, rs.o, nkb, (int)nblocks, scale * kLog2e, scale);
     return end_launch("launch avion_dkdv_kernel");
 }
@@ -261,6 +262,33 @@ int by_variant(Variant var, int d, F f)
     return by_fmt(std::false_type{});
 }
 
+// How one launch of the big kernels is cut.  A workgroup owns 32 * NW rows of the stationary side; with
+// KG > 1 it has KG groups of NW wavefronts, each of which walks its own share of the streamed tiles.
+//   128 rows, 1 group       the full chip: three to four workgroups per compute unit fill each other's waits
+//   128 rows, 2 or 4 groups when 128-row blocks give every compute unit at most one workgroup: a lone
+//                           workgroup is one wavefront per SIMD, and a 32 x 32 unit then takes 560 ns of it
+//                           instead of 333.  From six tiles on (below, the exchange costs what the shorter
+//                           walk gains); four groups from 16 tiles on, in the forward at d = 64 (registers
+//                           of the backward and LDS at d = 80 allow two)
+//   64 rows, 2 groups       when even 64-row blocks do
+// Measured, us, one group -> this rule (forward; whole backward): 12 heads x 1568 30.2 -> 22.4; 65 -> 53,
+// 32 x 785 17.4 -> 15.1; 39.4 -> 34.9, 16 x 785 backward 37 -> 27, 16 x 500 11.9 -> 9.2, 8 x 200 7.9 -> 6.9;
+// 16.9 -> 14.5, 12 x 785 (d = 80) 19.9 -> 15.6; 47 -> 36.  On the other side of the lines two groups lose:
+// 24 x 1568 85 -> 99 (backward), 64 x 785 22.4 -> 22.4; 53 -> 60, 64 x 300 21.0 -> 21.2, 240 x 77 6.5 -> 6.9.
+constexpr long long kComputeUnits = 256;
+// `min_tiles`: the backward's two phases keep one group up to 128 tokens, where the whole backward is one
+// launch whose bits they give.
+template <typename F>
+int by_split(long long heads, int N, int min_tiles, F f)
+{
+    constexpr std::integral_constant<int, 1> one{};
+    constexpr std::integral_constant<int, 2> two{};
+    constexpr std::integral_constant<int, 4> four{};
+    const int tiles = (N + 63) / 64;
+    if (tiles >= min_tiles && heads * tiles <= kComputeUnits) return f(two, two);
+    if (tiles >= 6 && heads * ((N + 127) / 128) <= kComputeUnits) return tiles >= 16 ? f(four, four) : f(four, two);
+    return f(four, one);
+}
 
 int fwd_impl(const void* q, const void* k, const void* v, void* o, float* lse, int B, int H, int N, int d, int packed,
              Variant var, float scale, void* stream)
@@ -278,9 +306,12 @@ int fwd_impl(const void* q, const void* k, const void* v, void* o, float* lse, i
             return launch_win_fwd<decltype(dim)::value, typename decltype(fmt)::type, decltype(causal)::value>(
                 qq, kk, vv, oo, lse, B, H, N, rs, scale, st);
         });
-    return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
-        return launch_fwd<decltype(dim)::value, 4, typename decltype(fmt)::type, decltype(causal)::value>(
-            qq, kk, vv, oo, lse, B, H, N, rs, scale, st);
+    return by_split((long long)B * H, N, 2, [&](auto nw, auto kg) {
+        return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
+            constexpr int KG = decltype(dim)::value == 64 ? decltype(kg)::value : std::min(decltype(kg)::value, 2);
+            return launch_fwd<decltype(dim)::value, decltype(nw)::value, KG, typename decltype(fmt)::type,
+                      decltype(causal)::value>(qq, kk, vv, oo, lse, B, H, N, rs, scale, st);
+        });
     });
 }
 
@@ -306,9 +337,12 @@ int dq_impl(const void* q, const void* k, const void* v, const void* o, const fl
     const raw16 *qq = static_cast<const raw16*>(q), *kk = static_cast<const raw16*>(k), *vv = static_cast<const raw16*>(v),
                *oo = static_cast<const raw16*>(o), *gg = static_cast<const raw16*>(dO);
     raw16* dqq = static_cast<raw16*>(dq);
-    return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
-        return launch_dq<decltype(dim)::value, 4, typename decltype(fmt)::type, decltype(causal)::value>(
-            qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
+    return by_split((long long)B * H, N, 3, [&](auto nw, auto kg) {
+        return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
+            constexpr int KG = std::min(decltype(kg)::value, 2);
+            return launch_dq<decltype(dim)::value, decltype(nw)::value, KG, typename decltype(fmt)::type,
+                      decltype(causal)::value>(qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
+        });
     });
 }
 
@@ -329,9 +363,12 @@ int dkdv_impl(const void* q, const void* k, const void* v, const float* lse, con
     const raw16 *qq = static_cast<const raw16*>(q), *kk = static_cast<const raw16*>(k), *vv = static_cast<const raw16*>(v),
                *gg = static_cast<const raw16*>(dO);
     raw16 *dkk = static_cast<raw16*>(dk), *dvv = static_cast<raw16*>(dv);
-    return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
-        return launch_dkdv<decltype(dim)::value, 4, typename decltype(fmt)::type, decltype(causal)::value>(
-            qq, kk, vv, gg, rowsc, dkk, dvv, B, H, N, rs, scale, st);
+    return by_split((long long)B * H, N, 3, [&](auto nw, auto kg) {
+        return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
+            constexpr int KG = std::min(decltype(kg)::value, 2);
+            return launch_dkdv<decltype(dim)::value, decltype(nw)::value, KG, typename decltype(fmt)::type,
+                      decltype(causal)::value>(qq, kk, vv, gg, rowsc, dkk, dvv, B, H, N, rs, scale, st);
+        });
     });
 }
 

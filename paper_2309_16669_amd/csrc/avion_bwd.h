@@ -24,41 +24,73 @@
 // buffers filled by LDS-direct loads; one workgroup barrier per 64-row tile certifies that the next
 // tile has landed and that the previous one is no longer read, so that its buffer can be refilled.
 //
-// Template parameters of both kernels: head dim D, wavefronts per workgroup NW, element format E
+// Small launches.  With KG > 1 a workgroup holds KG groups of NW wavefronts for the same 32*NW rows, each
+// of which walks its own share of the streamed tiles through its own two buffers; group 0 adds the
+// accumulators in a fixed order at the end (the rule and both sides' times stand at by_split in
+// avion_attn.hip).
+//
+// Template parameters of both kernels: head dim D, wavefronts per group NW, groups KG, element format E
 // (Bf16 or F16: contraction instruction and roundings), CAUSAL (query i sees keys 0..i: units that
 // no (query, key) pair of a wavefront needs are skipped, units on the diagonal start their score
 // accumulator from a mask of 0 / -1e30, whose weights come out as exactly 0).
 #pragma once
 #include "avion_common.h"
 
+// Groups of wavefronts that walked different tiles for the same rows: the accumulators of groups 1..KG-1
+// are added to group 0's through LDS ([value][lane] floats in `area`, (KG-1)*NW*CT*4 KB) in group order.
+// Every wavefront of the workgroup calls it after its last tile read.
+template <int NW, int KG, int CT>
+DEVINL void add_groups(char* area, f32x16 (&acc)[CT], int grp, int wave, int lane, bool wave_active)
+{
+    if (grp > 0 && wave_active) {
+        float* mine = reinterpret_cast<float*>(area + ((grp - 1) * NW + wave) * CT * 4096) + lane;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) mine[(ct * 16 + i) * 64] = acc[ct][i];
+    }
+    __syncthreads();
+    if (grp == 0 && wave_active) {
+#pragma unroll
+        for (int og = 0; og < KG - 1; ++og) {
+            const float* other = reinterpret_cast<const float*>(area + (og * NW + wave) * CT * 4096) + lane;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[ct][i] += other[(ct * 16 + i) * 64];
+        }
+    }
+}
+
 // --------------------------------------------------------------------------------------------- dQ
 // One wavefront owns 32 queries (Q, dO as B-operand fragments, LSE and delta as per-lane scalars);
 // the workgroup's NW wavefronts share (K | V) tiles of 64 keys.
-template <int D, int NW>
+template <int D, int NW, int KG = 1>
 struct DqCfg {
     static constexpr int BN = 64;
-    static constexpr int NT = NW * 64;
+    static constexpr int NT = NW * KG * 64;
     static constexpr int BM = 32 * NW;
     using Ring = TileRing<D, NW, 2, false>;
-    static constexpr int LDS_BYTES = Ring::LDS_BYTES;
-    static constexpr int WAVES_PER_SIMD = D == 64 ? 3 : 2;  // LDS would allow more; registers do not
+    static constexpr int LDS_BYTES = KG * Ring::LDS_BYTES;
+    static constexpr int WAVES_PER_SIMD = D == 64 && KG == 1 ? 3 : 2;  // LDS would allow more; registers do not
 };
 
 // The work of one workgroup: query block qb of (batch, head) bh.
-template <int D, int NW, typename E, bool CAUSAL>
+template <int D, int NW, int KG, typename E, bool CAUSAL>
 DEVINL void avion_dq_body(char* smem, const raw16* __restrict__ q, const raw16* __restrict__ k,
                           const raw16* __restrict__ v, const raw16* __restrict__ o, const raw16* __restrict__ dO,
                           const float* __restrict__ lse, raw16* __restrict__ dq, float* __restrict__ rowsc, int H, int N,
                           int rs_qkv, int rs_o, int bh, int qb, float cs, float scale)
 {
-    using Cfg = DqCfg<D, NW>;
+    using Cfg = DqCfg<D, NW, KG>;
     using Ring = typename Cfg::Ring;
     constexpr int BN = Cfg::BN, BM = Cfg::BM, STRIDE = Ring::STRIDE;
     constexpr int KS = D / 16, CT = (D + 31) / 32;
 
     const int b = bh / H, h = bh % H;
     const int tid = threadIdx.x, lane = tid % 64, l32 = lane % 32, g = lane / 32;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int wave_id = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int wave = KG == 1 ? wave_id : wave_id % NW, grp = KG == 1 ? 0 : wave_id / NW;
     // token rows of Q, K, V, dQ are rs_qkv elements apart, those of O, dO rs_o
     const long rs = rs_qkv;
     const long head_off = (long)b * N * rs + (long)h * D;
@@ -72,8 +104,11 @@ DEVINL void avion_dq_body(char* smem, const raw16* __restrict__ q, const raw16* 
     const int mask_from = CAUSAL ? min(N, q0 + 1) : N;
     const int ntiles = ((CAUSAL ? min(N, qb * BM + BM) : N) + BN - 1) / BN;
 
-    const Ring ring(k + head_off, rs, v + head_off, rs, N, nullptr, 0, ntiles, smem, wave, lane);
-    ring.fetch(0);
+    // tiles of this group of wavefronts; every group passes the same barriers
+    const int per = (ntiles + KG - 1) / KG, t0 = grp * per, t1 = min(ntiles, t0 + per);
+
+    const Ring ring(k + head_off, rs, v + head_off, rs, N, nullptr, 0, ntiles, smem + grp * Ring::LDS_BYTES, wave, lane);
+    if (KG == 1 || t0 < t1) ring.fetch(t0);
 
     // Q and dO fragments (B operands), delta and LSE per lane
     frag8 qf[KS], gf[KS];
@@ -96,7 +131,7 @@ DEVINL void avion_dq_body(char* smem, const raw16* __restrict__ q, const raw16* 
         // per-query scalars for the dK/dV pass, in the form it consumes them: LSE*log2e and -delta,
         // each array padded to a multiple of 64 rows with +inf (weight 0) and 0
         const int qrow = q0 + l32, npad = (N + 63) & ~63;
-        if (g == 0 && qrow < npad) {
+        if (g == 0 && qrow < npad && grp == 0) {
             float* ws = rowsc + (long)bh * 2 * npad;
             ws[qrow] = qrow < N ? lc : INFINITY;
             ws[npad + qrow] = qrow < N ? -dl : 0.f;
@@ -141,9 +176,9 @@ DEVINL void avion_dq_body(char* smem, const raw16* __restrict__ q, const raw16* 
             for (int ct = 0; ct < CT; ++ct) acc[ct] = E::mfma(kt_f[half][ct], as_frag8(df[half]), acc[ct]);
     };
 
-    for (int t = 0; t < ntiles; ++t) {
-        ring.fetch(t + 1);  // into the buffer of tile t-1, which nobody reads any more
-        if (wave_active) {
+    for (int t = t0; t < t0 + per; ++t) {
+        if (KG == 1 || t + 1 < t1) ring.fetch(t + 1);  // into the buffer of tile t-1, which nobody reads any more
+        if (wave_active && (KG == 1 || t < t1)) {
 #pragma unroll
             for (int hk = 0; hk < 2; ++hk) {
                 const int key_base = t * BN + 32 * hk;
@@ -154,12 +189,17 @@ DEVINL void avion_dq_body(char* smem, const raw16* __restrict__ q, const raw16* 
         }
         Ring::landed_barrier();  // tile t+1 has landed; tile t is no longer read
     }
+    if constexpr (KG > 1) {
+        add_groups<NW, KG>(smem + NW * RowStore<D, E>::BYTES, acc, grp, wave, lane, wave_active);
+        static_assert(NW * RowStore<D, E>::BYTES + (KG - 1) * NW * CT * 4096 <= Cfg::LDS_BYTES, "exchange area");
+        if (grp > 0) return;
+    }
     if (!wave_active) return;
     RowStore<D, E>::run(smem + wave * RowStore<D, E>::BYTES, acc, scale, dq + head_off + (long)q0 * rs, rs, N - q0, lane);
 }
 
-template <int D, int NW, typename E, bool CAUSAL>
-__global__ void __launch_bounds__(NW * 64, (DqCfg<D, NW>::WAVES_PER_SIMD))
+template <int D, int NW, int KG, typename E, bool CAUSAL>
+__global__ void __launch_bounds__(NW * KG * 64, (DqCfg<D, NW, KG>::WAVES_PER_SIMD))
 avion_dq_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const raw16* __restrict__ v,
                     const raw16* __restrict__ o, const raw16* __restrict__ dO, const float* __restrict__ lse,
                     raw16* __restrict__ dq, float* __restrict__ rowsc, int H, int N, int rs_qkv, int rs_o, int nqb,
@@ -168,7 +208,7 @@ avion_dq_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const 
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int logical = xcd_local_id(blockIdx.x, nblocks);
     if (logical < 0) return;
-    avion_dq_body<D, NW, E, CAUSAL>(smem, q, k, v, o, dO, lse, dq, rowsc, H, N, rs_qkv, rs_o, logical / nqb, logical % nqb,
+    avion_dq_body<D, NW, KG, E, CAUSAL>(smem, q, k, v, o, dO, lse, dq, rowsc, H, N, rs_qkv, rs_o, logical / nqb, logical % nqb,
                                     cs, scale);
 }
 
@@ -176,26 +216,26 @@ avion_dq_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const 
 // One wavefront owns 32 keys (K, V as B-operand fragments); the workgroup's NW wavefronts share
 // (Q | dO | per-query scalars) tiles of 64 queries.  The dP accumulator starts from -delta, so the
 // subtraction in dS costs no vector-ALU instruction.
-template <int D, int NW>
+template <int D, int NW, int KG = 1>
 struct DkvCfg {
     static constexpr int BQ = 64;
-    static constexpr int NT = NW * 64;
+    static constexpr int NT = NW * KG * 64;
     static constexpr int BNK = 32 * NW;
     using Ring = TileRing<D, NW, 2, true>;
-    static constexpr int LDS_BYTES = Ring::LDS_BYTES;
+    static constexpr int LDS_BYTES = KG * Ring::LDS_BYTES;
     // resident wavefronts per SIMD the register budget is held to: three for D = 64 (at most 168
     // registers; the schedule relies on three wavefronts filling each other's waits), two for D = 80
-    static constexpr int WAVES_PER_SIMD = D == 64 ? 3 : 2;
+    static constexpr int WAVES_PER_SIMD = D == 64 && KG == 1 ? 3 : 2;
 };
 
 // The work of one workgroup: key block kb of (batch, head) bh.
-template <int D, int NW, typename E, bool CAUSAL>
+template <int D, int NW, int KG, typename E, bool CAUSAL>
 DEVINL void avion_dkdv_body(char* smem, const raw16* __restrict__ q, const raw16* __restrict__ k,
                             const raw16* __restrict__ v, const raw16* __restrict__ dO, const float* __restrict__ rowsc,
                             raw16* __restrict__ dk, raw16* __restrict__ dv, int H, int N, int rs_qkv, int rs_o, int bh,
                             int kb, float cs, float scale)
 {
-    using Cfg = DkvCfg<D, NW>;
+    using Cfg = DkvCfg<D, NW, KG>;
     using Ring = typename Cfg::Ring;
     constexpr int BQ = Cfg::BQ, BNK = Cfg::BNK, STRIDE = Ring::STRIDE;
     constexpr int KS = D / 16, CT = (D + 31) / 32;
@@ -203,7 +243,8 @@ DEVINL void avion_dkdv_body(char* smem, const raw16* __restrict__ q, const raw16
 
     const int b = bh / H, h = bh % H;
     const int tid = threadIdx.x, lane = tid % 64, l32 = lane % 32, g = lane / 32;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int wave_id = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int wave = KG == 1 ? wave_id : wave_id % NW, grp = KG == 1 ? 0 : wave_id / NW;
     // token rows of Q, K, V, dK, dV are rs_qkv elements apart, those of dO rs_o
     const long rs = rs_qkv;
     const long head_off = (long)b * N * rs + (long)h * D;
@@ -216,11 +257,13 @@ DEVINL void avion_dkdv_body(char* smem, const raw16* __restrict__ q, const raw16
 
     // causal attention: the keys of this workgroup are seen by the queries from its first key on only,
     // so the stream of query tiles starts there
-    const int t0 = CAUSAL ? kb * BNK / BQ : 0;
+    const int first = CAUSAL ? kb * BNK / BQ : 0;
+    // tiles of this group of wavefronts; every group passes the same barriers
+    const int per = (ntiles - first + KG - 1) / KG, t0 = first + grp * per, t1 = min(ntiles, t0 + per);
 
-    const Ring ring(q + head_off, rs, dO + head_off_o, rs_o, N, rowsc + (long)bh * 2 * npad, npad, ntiles, smem, wave,
-                    lane);
-    ring.fetch(t0);
+    const Ring ring(q + head_off, rs, dO + head_off_o, rs_o, N, rowsc + (long)bh * 2 * npad, npad, ntiles,
+                    smem + grp * Ring::LDS_BYTES, wave, lane);
+    if (KG == 1 || t0 < t1) ring.fetch(t0);
 
     // K and V fragments (B operands: lane = key) stay in registers
     frag8 kf[KS], vf[KS];
@@ -241,9 +284,9 @@ DEVINL void avion_dkdv_body(char* smem, const raw16* __restrict__ q, const raw16
     }
     Ring::landed_barrier();  // the first tile is in LDS (and the fragments above have arrived)
 
-    for (int t = t0; t < ntiles; ++t) {
-        ring.fetch(t + 1);  // into the buffer of tile t-1, which nobody reads any more
-        if (wave_active) {
+    for (int t = t0; t < t0 + per; ++t) {
+        if (KG == 1 || t + 1 < t1) ring.fetch(t + 1);  // into the buffer of tile t-1, which nobody reads any more
+        if (wave_active && (KG == 1 || t < t1)) {
             const char* buf = ring.buf(t);
 #pragma unroll
             for (int hq = 0; hq < 2; ++hq) {
@@ -305,6 +348,14 @@ DEVINL void avion_dkdv_body(char* smem, const raw16* __restrict__ q, const raw16
         }
         Ring::landed_barrier();  // tile t+1 has landed; tile t is no longer read
     }
+    if constexpr (KG > 1) {
+        // one accumulator after the other through the same area
+        add_groups<NW, KG>(smem + NW * RowStore<D, E>::BYTES, dka, grp, wave, lane, wave_active);
+        __syncthreads();
+        add_groups<NW, KG>(smem + NW * RowStore<D, E>::BYTES, dva, grp, wave, lane, wave_active);
+        static_assert(NW * RowStore<D, E>::BYTES + (KG - 1) * NW * CT * 4096 <= Cfg::LDS_BYTES, "exchange area");
+        if (grp > 0) return;
+    }
     if (!wave_active) return;
     char* region = smem + wave * RowStore<D, E>::BYTES;
     const int lane_now = lane_from_exec();
@@ -312,8 +363,8 @@ DEVINL void avion_dkdv_body(char* smem, const raw16* __restrict__ q, const raw16
     RowStore<D, E>::run(region, dva, 1.0f, dv + head_off + (long)k0 * rs, rs, N - k0, lane_now);
 }
 
-template <int D, int NW, typename E, bool CAUSAL>
-__global__ void __launch_bounds__(NW * 64, (DkvCfg<D, NW>::WAVES_PER_SIMD))
+template <int D, int NW, int KG, typename E, bool CAUSAL>
+__global__ void __launch_bounds__(NW * KG * 64, (DkvCfg<D, NW, KG>::WAVES_PER_SIMD))
 avion_dkdv_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const raw16* __restrict__ v,
                       const raw16* __restrict__ dO, const float* __restrict__ rowsc, raw16* __restrict__ dk,
                       raw16* __restrict__ dv, int H, int N, int rs_qkv, int rs_o, int nkb, int nblocks, float cs,
@@ -322,7 +373,7 @@ avion_dkdv_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, cons
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int logical = xcd_local_id(blockIdx.x, nblocks);
     if (logical < 0) return;
-    avion_dkdv_body<D, NW, E, CAUSAL>(smem, q, k, v, dO, rowsc, dk, dv, H, N, rs_qkv, rs_o, logical / nkb, logical % nkb, cs,
+    avion_dkdv_body<D, NW, KG, E, CAUSAL>(smem, q, k, v, dO, rowsc, dk, dv, H, N, rs_qkv, rs_o, logical / nkb, logical % nkb, cs,
                                       scale);
 }
 
@@ -352,11 +403,11 @@ avion_bwd_small_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k,
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int bh = xcd_local_id(blockIdx.x, nblocks);
     if (bh < 0) return;
-    avion_dq_body<D, NW, E, CAUSAL>(smem, q, k, v, o, dO, lse, dq, rowsc, H, N, rs_qkv, rs_o, bh, 0, cs, scale);
+    avion_dq_body<D, NW, 1, E, CAUSAL>(smem, q, k, v, o, dO, lse, dq, rowsc, H, N, rs_qkv, rs_o, bh, 0, cs, scale);
     // Workgroup scope is enough (writer and reader wavefronts sit on one compute unit and share its
     // vector cache) and is only a wait for the stores; a device-scope fence would write back and
     // invalidate the L2 once per workgroup.
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __syncthreads();
-    avion_dkdv_body<D, NW, E, CAUSAL>(smem, q, k, v, dO, rowsc, dk, dv, H, N, rs_qkv, rs_o, bh, 0, cs, scale);
+    avion_dkdv_body<D, NW, 1, E, CAUSAL>(smem, q, k, v, dO, rowsc, dk, dv, H, N, rs_qkv, rs_o, bh, 0, cs, scale);
 }

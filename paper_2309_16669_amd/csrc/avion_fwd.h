@@ -29,36 +29,44 @@
 // (workgroup-wide), and the whole workgroup then recomputes its rows with the classic running
 // maximum (avion_fwd_safe_pass).  Random or trained activations never get there.
 //
-// Template parameters: head dim D, wavefronts per workgroup NW, element format E (Bf16 or F16),
+// Small launches.  With KG > 1 a workgroup holds KG groups of NW wavefronts for the same 32*NW queries;
+// each group walks its own share of the key tiles through its own two buffers, with its own reference,
+// and group 0 adds the others' accumulators and sums, rescaled to the larger reference, in a fixed
+// order at the end.  What bounds a launch that leaves compute units with one workgroup is the serial
+// chain of one wavefront per SIMD, which this shortens (the rule and both sides' times stand at
+// by_split in avion_attn.hip).
+//
+// Template parameters: head dim D, wavefronts per group NW, groups KG, element format E (Bf16 or F16),
 // CAUSAL (query i sees keys 0..i; the reference m is then the maximum over the visible ones of the
 // first 32 keys -- key 0 is visible to every query).
 #pragma once
 #include "avion_common.h"
 
-template <int D, int NW>
+template <int D, int NW, int KG>
 struct FwdCfg {
     static constexpr int BN = 64;
-    static constexpr int NT = NW * 64;
+    static constexpr int NT = NW * KG * 64;
     static constexpr int BM = 32 * NW;
     using Ring = TileRing<D, NW, 2, false>;
     using Stage = TileStage<D, BN, NT>;  // the fallback pass stages its tiles through registers
     static_assert(Ring::TILE_BYTES == Stage::BYTES, "both movers use the same tile layout");
-    static constexpr int LDS_BYTES = Ring::LDS_BYTES;
-    // wavefronts per SIMD the register budget is sized for: what LDS lets a compute unit hold, at most 4
+    static constexpr int LDS_BYTES = KG * Ring::LDS_BYTES;
+    // wavefronts per SIMD the register budget is sized for: what LDS lets a compute unit hold, at most 4;
+    // with several groups one workgroup per compute unit
     static constexpr int WG_PER_CU = 160 * 1024 / LDS_BYTES;
-    static constexpr int WAVES_PER_SIMD = WG_PER_CU * NW / 4 > 4 ? 4 : WG_PER_CU * NW / 4;
+    static constexpr int WAVES_PER_SIMD = KG > 1 ? (NW * KG + 3) / 4 : WG_PER_CU * NW / 4 > 4 ? 4 : WG_PER_CU * NW / 4;
 };
 
 // Classic online softmax with a running maximum, one 64-key tile at a time, staged through
 // registers into the ring's two buffers.  Used only as the fallback described above; same register
 // layouts as the main loop.
 // key_limit: this lane's query sees keys below it (N, or query + 1 for causal attention).
-template <int D, int NW, typename E>
+template <int D, int NW, int KG, typename E>
 DEVINL void avion_fwd_safe_pass(char* smem, const SliceView& kh, const SliceView& vh, const frag8 (&qf)[D / 16],
                                 f32x16 (&oacc)[(D + 31) / 32], float& m_used, float& lsum, float& rsum, int N,
                                 int key_limit, float cs, bool wave_active, int tid, int l32, int g, int tr_off)
 {
-    using Cfg = FwdCfg<D, NW>;
+    using Cfg = FwdCfg<D, NW, KG>;
     using Stage = typename Cfg::Stage;
     using Ring = typename Cfg::Ring;
     constexpr int BN = 64, STRIDE = Stage::STRIDE, KS = D / 16, CT = (D + 31) / 32;
@@ -139,13 +147,13 @@ DEVINL void avion_fwd_safe_pass(char* smem, const SliceView& kh, const SliceView
 
 // (The causal instance carries a per-lane key bound and a few more scalars: it is sized for one
 // wavefront per SIMD less than the register file would otherwise hold, which keeps it free of spills.)
-template <int D, int NW, typename E, bool CAUSAL>
-__global__ void __launch_bounds__(NW * 64, (FwdCfg<D, NW>::WAVES_PER_SIMD - (CAUSAL && FwdCfg<D, NW>::WAVES_PER_SIMD > 3 ? 1 : 0)))
+template <int D, int NW, int KG, typename E, bool CAUSAL>
+__global__ void __launch_bounds__((FwdCfg<D, NW, KG>::NT), (FwdCfg<D, NW, KG>::WAVES_PER_SIMD - (KG == 1 && CAUSAL && FwdCfg<D, NW, KG>::WAVES_PER_SIMD > 3 ? 1 : 0)))
 avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const raw16* __restrict__ v,
                  raw16* __restrict__ o, float* __restrict__ lse, int H, int N, int rs_qkv, int rs_o, int nqb, int nblocks,
                  float cs)
 {
-    using Cfg = FwdCfg<D, NW>;
+    using Cfg = FwdCfg<D, NW, KG>;
     using Ring = typename Cfg::Ring;
     constexpr int BN = Cfg::BN, BM = Cfg::BM, STRIDE = Ring::STRIDE;
     constexpr int KS = D / 16;         // 16-deep steps over the channels
@@ -157,7 +165,9 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
     const int bh = logical / nqb, qb = logical % nqb;
     const int b = bh / H, h = bh % H;
     const int tid = threadIdx.x, lane = tid % 64, l32 = lane % 32, g = lane / 32;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int wave_id = __builtin_amdgcn_readfirstlane(tid / 64);
+    // wavefront of its group, and the group
+    const int wave = KG == 1 ? wave_id : wave_id % NW, grp = KG == 1 ? 0 : wave_id / NW;
     // token rows of Q, K, V are rs_qkv elements apart, those of O rs_o; a batch entry is N such rows
     const long rs = rs_qkv;
     const long head_off = (long)b * N * rs + (long)h * D;
@@ -175,8 +185,11 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
     const int mask_from = CAUSAL ? min(N, q0 + 1) : N;
     const int ntiles = ((CAUSAL ? min(N, qb * BM + BM) : N) + BN - 1) / BN;
 
-    const Ring ring(k + head_off, rs, v + head_off, rs, N, nullptr, 0, ntiles, smem, wave, lane);
-    ring.fetch(0);
+    // tiles of this key group; every group passes the same barriers
+    const int per = (ntiles + KG - 1) / KG, t0 = grp * per, t1 = min(ntiles, t0 + per);
+
+    const Ring ring(k + head_off, rs, v + head_off, rs, N, nullptr, 0, ntiles, smem + grp * Ring::LDS_BYTES, wave, lane);
+    if (KG == 1 || t0 < t1) ring.fetch(t0);
 
     // Q fragments stay in registers for the whole kernel
     frag8 qf[KS];
@@ -204,12 +217,17 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
             s = E::mfma(nat_frag(kt, STRIDE, 32 * hk + l32, ks, g), qf[ks], ks == 0 && !RAGGED ? f32x16_zero() : s);
         return s;
     };
-    // reference maximum: over the first 32 keys
-    if (wave_active) m_used = both_halves_max(max16(scores(std::true_type{}, ring.buf(0), 0, 0))) * cs;
+    // reference maximum: over the first 32 keys (of this group's)
+    if (wave_active && (KG == 1 || t0 < t1)) {
+        m_used = both_halves_max(max16(scores(std::true_type{}, ring.buf(t0), 0, t0 * BN))) * cs;
+        // a query that sees none of them (causal, a later group): any finite reference will do, its weights
+        // must come out as 0
+        if (KG > 1 && CAUSAL) m_used = t0 * BN < key_limit ? m_used : 0.f;
+    }
 
-    for (int t = 0; t < ntiles; ++t) {
-        ring.fetch(t + 1);  // into the buffer of tile t-1, which nobody reads any more
-        if (wave_active) {
+    for (int t = t0; t < t0 + per; ++t) {
+        if (KG == 1 || t + 1 < t1) ring.fetch(t + 1);  // into the buffer of tile t-1, which nobody reads any more
+        if (wave_active && (KG == 1 || t < t1)) {
             const char* kt = ring.buf(t);
             const char* vt = kt + Ring::OFF_B;
 #pragma unroll
@@ -251,9 +269,46 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
     // overflow of the fixed reference: redo this workgroup's rows with the running maximum
     bool bad = false;
     if (wave_active) bad = !(both_halves_sum(lsum) <= E::kRowSumLimit);
-    if (__syncthreads_or(bad ? 1 : 0))
-        avion_fwd_safe_pass<D, NW, E>(smem, kh, vh, qf, oacc, m_used, lsum, rsum, N, key_limit, cs, wave_active, tid, l32, g,
-                                      tr_off);
+    const bool redo = __syncthreads_or(bad ? 1 : 0);
+    if (redo)
+        avion_fwd_safe_pass<D, NW, KG, E>(smem, kh, vh, qf, oacc, m_used, lsum, rsum, N, key_limit, cs,
+                                          wave_active && grp == 0, tid, l32, g, tr_off);
+    if constexpr (KG > 1) {
+        // The groups' results meet in LDS (behind the row-store areas of the epilogue) as [value][lane]
+        // floats and are added in group order, each scaled to the larger of the two references.  After a
+        // redone pass group 0 holds everything.
+        constexpr int VALS = CT * 16 + 3, WAVE_BYTES = VALS * 256;
+        static_assert(NW * RowStore<D, E>::BYTES + (KG - 1) * NW * WAVE_BYTES <= Cfg::LDS_BYTES, "exchange area");
+        char* area = smem + NW * RowStore<D, E>::BYTES;
+        if (grp > 0 && wave_active && !redo) {
+            float* mine = reinterpret_cast<float*>(area + ((grp - 1) * NW + wave) * WAVE_BYTES) + lane;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) mine[(ct * 16 + i) * 64] = oacc[ct][i];
+            mine[(VALS - 3) * 64] = lsum;
+            mine[(VALS - 2) * 64] = rsum;
+            // a query that sees no key of this group: reference -inf, so that nothing of it counts
+            mine[(VALS - 1) * 64] = t0 < t1 && t0 * BN < key_limit ? m_used : -INFINITY;
+        }
+        __syncthreads();
+        if (grp > 0) return;
+        if (wave_active && !redo) {
+#pragma unroll
+            for (int og = 0; og < KG - 1; ++og) {
+                const float* other = reinterpret_cast<const float*>(area + (og * NW + wave) * WAVE_BYTES) + lane;
+                const float m2 = other[(VALS - 1) * 64];
+                const float mn = fmaxf(m_used, m2), a1 = fast_exp2(m_used - mn), a2 = fast_exp2(m2 - mn);
+                lsum = lsum * a1 + other[(VALS - 3) * 64] * a2;
+                rsum = rsum * a1 + other[(VALS - 2) * 64] * a2;
+                m_used = mn;
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) oacc[ct][i] = oacc[ct][i] * a1 + other[(ct * 16 + i) * 64] * a2;
+            }
+        }
+    }
 
     // every wavefront is past its last tile read (barrier above): the tile buffers are free and
     // serve as the per-wavefront staging area of the output rows

@@ -143,3 +143,35 @@ def _lse_of(w, x, f16, causal):
     av.attn_fwd_ex(q, k, v, o, lse, w.scale, causal)
     torch.cuda.synchronize()
     return lse
+
+
+# Launches small enough that several groups of wavefronts share a workgroup's rows (forward and backward): two to
+# four groups over 64- and 128-row blocks, key tiles that do not divide among the groups, groups without a tile, and
+# the first size beyond each line of the rule.  Bounds as everywhere in this file.
+@pytest.mark.parametrize("B,H,N,d,f16,causal", [
+    (1, 2, 65, 64, False, False), (1, 2, 65, 80, True, True), (1, 3, 129, 64, False, True), (1, 2, 161, 80, False, False),
+    (2, 64, 128, 64, False, False), (2, 64, 129, 64, True, True), (1, 86, 321, 64, False, False), (1, 64, 385, 64, False, True),
+    (1, 52, 321, 80, True, False), (1, 17, 961, 64, False, False), (1, 17, 1025, 64, False, True), (1, 16, 1025, 80, False, False),
+    (1, 43, 321, 64, False, True), (1, 32, 1025, 64, True, False)])
+def test_launches_split_into_groups_match_the_oracle(B, H, N, d, f16, causal):
+    w = si.small_workload(B, H, N, d, seed=9300 + N + d)
+    x = si.make_inputs(w, fmt="f16" if f16 else "bf16")
+    check(w, x, run_ex(w, x, f16, causal, False), f16, causal)
+
+
+@pytest.mark.parametrize("H,N,sink", [(2, 300, 250), (2, 300, 40), (17, 1025, 1000)])
+def test_a_group_whose_reference_overflows_redoes_the_block(H, N, sink):
+    # keys from `sink` on carry scores far above the first 32 keys of their group: 2^15 in fp16 is passed
+    w = si.small_workload(1, H, N, 64, seed=9400 + N, scale=1.0)
+    x = si.make_inputs(w, fmt="f16")
+    k = x["k"].copy()
+    k[:, sink:sink + 4] = (si.f16_bits_to_f64(k[:, sink:sink + 4]) * 6).astype(np.float16).view(np.uint16)
+    x["k"] = k
+    out = run_ex(w, x, True, False, False)
+    import oracle
+    ro, rl = oracle.fwd_f64(*(si.f16_bits_to_f64(x[n]) for n in ("q", "k", "v")), w.scale)
+    o, lse = out["o"].double().cpu().numpy(), out["lse"].double().cpu().numpy()
+    # forward only: rows are near one-hot, and the rounding of O inside delta alone moves dQ beyond the general bound
+    # (tests/test_tolerance_model.py).  O within one unit in the last place of its largest value, LSE in fp32.
+    assert np.all(np.isfinite(o)) and np.abs(o - ro).max() <= 2.0 ** -10 * np.abs(ro).max()
+    assert np.abs(lse - rl).max() <= 2e-6 * np.abs(rl).max() + 1e-3
