@@ -142,7 +142,8 @@ def main():
 
     if not torch.cuda.is_available():
         sys.exit("bench.py: no GPU visible")
-    if not os.path.exists(av.LIB_PATH):
+    from paper_2309_16669_amd import build as hip_build
+    if not (os.path.exists(av.LIB_PATH) and os.path.exists(hip_build.TORCH_MODULE)):
         import __graft_entry__
         __graft_entry__.build()
     av.load_library()

@@ -6,11 +6,17 @@ combination of bf16 / fp16, causal or not, packed or not is available) through t
 package.  Nothing is computed here: every step of the forward and of the backward runs in the HIP
 kernels, and there is no fallback if the library is missing.
 
+Plain calls go through the native functions of `csrc/avion_torch.cpp` (same checks, allocations, entry points
+and saved tensors; the interpreter costs several times a small call's kernels).  They decline whatever is not
+plain -- tensor subclasses, function transforms, modes, tracing, forward-mode tangents, arguments that do not
+fit -- and those calls take the classes below, which treat or refuse them.
+
 What is saved for the backward is O(N) per (batch, head): q, k, v, o and the fp32 log-sum-exp -- no
 N x N matrix (the memory saving of Sec. 4.1 of the paper).
 
-The backward's workspace is kept per (device, stream) and grown on demand, so a layer's backward does
-not go through the allocator every step; backward calls on one stream are ordered and may share it.
+The classes keep the backward's workspace per (device, stream), grown on demand; backward calls on one
+stream are ordered and may share it.  The native calls take theirs from torch's allocator for the length of
+the call.
 
 `layer_norm(x, gamma, beta)` and `bias_gelu(x, bias)` wrap the layer-normalisation and bias + GELU
 entry points the same way (what they keep for the backward is stated in their docstrings).
@@ -22,7 +28,24 @@ import math
 import torch
 
 from . import (attn_bwd_ex, attn_bwd_workspace_bytes, attn_fwd_ex, bias_gelu_bwd, bias_gelu_bwd_workspace_bytes, bias_gelu_fwd,
-               layernorm_bwd, layernorm_bwd_workspace_bytes, layernorm_fwd)
+               layernorm_bwd, layernorm_bwd_workspace_bytes, layernorm_fwd, load_library)
+
+_native = None
+
+
+def native_calls():
+    """The module of native calls; raises if it has not been built."""
+    global _native
+    if _native is None:
+        load_library()
+        try:
+            from . import _avion_torch
+        except ImportError as e:
+            raise ImportError("paper_2309_16669_amd/_avion_torch.so is missing or does not load: build it first "
+                              "(python -c 'import __graft_entry__ as g; g.build()')") from e
+        _native = _avion_torch
+    return _native
+
 
 _workspaces: dict = {}
 
@@ -164,29 +187,36 @@ def bias_gelu_linear(x, bias, weight, out_bias=None):
     """linear(GELU(x + bias), weight, out_bias): the second half of the encoder's MLP, keeping only x (the
     first matrix product's output) for the backward; x bf16 or fp16 [..., F], bias fp32 [F], weight
     [out, F] and out_bias [out] in the format of x."""
-    return _BiasGeluLinear.apply(x, bias, weight, out_bias)
+    out = (_native or native_calls()).bias_gelu_linear(x, bias, weight, out_bias)
+    return _BiasGeluLinear.apply(x, bias, weight, out_bias) if out is None else out
 
 
 def layer_norm(x, gamma, beta, eps: float = 1e-5):
     """Layer normalisation over the last axis of x (bf16 or fp16, any leading shape, width <= 2048 and a
     multiple of 8) with fp32 gain and bias.  Differentiable in x, gamma and beta; keeps x and two floats
     per token for the backward."""
-    return _LayerNorm.apply(x, gamma, beta, float(eps))
+    y = (_native or native_calls()).layer_norm(x, gamma, beta, float(eps))
+    return _LayerNorm.apply(x, gamma, beta, float(eps)) if y is None else y
 
 
 def bias_gelu(x, bias):
     """GELU(x + bias) (exact erf form) over the last axis of x (bf16 or fp16, width a multiple of 8) with
     an fp32 bias.  Differentiable in x and bias; keeps only x for the backward."""
-    return _BiasGelu.apply(x, bias)
+    y = (_native or native_calls()).bias_gelu(x, bias)
+    return _BiasGelu.apply(x, bias) if y is None else y
 
 
 def attention(q, k, v, scale: float | None = None, causal: bool = False):
     """softmax(scale * q k^T) v per (batch, head) for q, k, v of shape [B, N, H, d], bf16 or fp16,
     d in {64, 80}; `causal`: query i attends to keys 0..i.  Differentiable.  scale defaults to 1/sqrt(d)."""
-    return _Attention.apply(q, k, v, 1.0 / math.sqrt(q.shape[-1]) if scale is None else float(scale), bool(causal))
+    scale, causal = 1.0 / math.sqrt(q.shape[-1]) if scale is None else float(scale), bool(causal)
+    o = (_native or native_calls()).attention(q, k, v, scale, causal)
+    return _Attention.apply(q, k, v, scale, causal) if o is None else o
 
 
 def attention_qkvpacked(qkv, scale: float | None = None, causal: bool = False):
     """The same for the [B, N, 3, H, d] output of a joint QKV projection (bf16 or fp16); the gradient
     comes back in the same packing."""
-    return _AttentionPacked.apply(qkv, 1.0 / math.sqrt(qkv.shape[-1]) if scale is None else float(scale), bool(causal))
+    scale, causal = 1.0 / math.sqrt(qkv.shape[-1]) if scale is None else float(scale), bool(causal)
+    o = (_native or native_calls()).attention_qkvpacked(qkv, scale, causal)
+    return _AttentionPacked.apply(qkv, scale, causal) if o is None else o

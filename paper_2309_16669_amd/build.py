@@ -1,4 +1,4 @@
-"""Builds libavion_attn.so (gfx950 only) in-tree with hipcc.  Cross-compiles without a GPU."""
+"""Builds libavion_attn.so (gfx950 only, hipcc) and _avion_torch.so (host C++) in-tree.  Cross-compiles without a GPU."""
 from __future__ import annotations
 
 import os
@@ -8,6 +8,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libavion_attn.so")
+TORCH_MODULE = os.path.join(PKG, "_avion_torch.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -47,5 +48,24 @@ def build_library(verbose: bool = False, extra_flags=()) -> str:
     return LIB
 
 
+def build_torch_module(verbose: bool = False) -> str:
+    """The autograd front end's native calls (host C++, csrc/avion_torch.cpp), linked against the library."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    includes = [*cpp_extension.include_paths("cuda"), sysconfig.get_paths()["include"]]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
+           "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1",   # what torch's and HIP's headers ask of a host compiler
+           "-I", os.path.join(ROOT, "include"), *(a for p in includes for a in ("-isystem", p)),
+           os.path.join(CSRC, "avion_torch.cpp"), "-o", TORCH_MODULE, "-L", torch_lib, "-lc10", "-lc10_hip", "-ltorch_cpu",
+           "-ltorch_hip", "-ltorch", "-ltorch_python", "-L", PKG, "-lavion_attn", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return TORCH_MODULE
+
+
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_torch_module(verbose=True))

@@ -1,0 +1,120 @@
+"""The native calls of the autograd front end against its Python classes: same bits, same saved tensors, same
+refusals.  The classes call the same entry points, so equality is exact."""
+import numpy as np
+import pytest
+
+
+def _calls():
+    import torch
+    from paper_2309_16669_amd import autograd as ag
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    bf = torch.bfloat16
+    rn = lambda *s, dt=bf: torch.randn(*s, generator=g, device="cuda").to(dt)
+    f32 = lambda n: rn(n, dt=torch.float32)
+    return {
+        "attention": (ag.attention, ag._Attention, [rn(2, 70, 3, 64) for _ in range(3)], (0.125, False)),
+        "attention_f16_causal": (ag.attention, ag._Attention, [rn(1, 200, 2, 80, dt=torch.float16) for _ in range(3)], (0.1, True)),
+        "attention_strided": (ag.attention, ag._Attention, [rn(2, 3, 70, 64).transpose(1, 2) for _ in range(3)], (0.125, False)),
+        "qkvpacked": (ag.attention_qkvpacked, ag._AttentionPacked, [rn(2, 70, 3, 2, 64)], (0.125, True)),
+        "layer_norm": (ag.layer_norm, ag._LayerNorm, [rn(2, 5, 768), f32(768), f32(768)], (1e-6,)),
+        "layer_norm_strided": (ag.layer_norm, ag._LayerNorm, [rn(40, 64).t(), f32(80)[::2], f32(40)], (1e-5,)),
+        "bias_gelu": (ag.bias_gelu, ag._BiasGelu, [rn(3, 7, 1024), f32(1024)], ()),
+        "bias_gelu_linear": (ag.bias_gelu_linear, ag._BiasGeluLinear, [rn(9, 256), f32(256), rn(64, 256), rn(64)], ()),
+        "bias_gelu_linear_no_bias": (ag.bias_gelu_linear, ag._BiasGeluLinear, [rn(9, 256), f32(256), rn(64, 256)], ()),
+    }
+
+
+NAMES = ["attention", "attention_f16_causal", "attention_strided", "qkvpacked", "layer_norm", "layer_norm_strided", "bias_gelu",
+         "bias_gelu_linear", "bias_gelu_linear_no_bias"]
+
+
+def _pass(f, args, rest, grad=None, saved=None):
+    import torch
+    leaves = [a.detach().requires_grad_() for a in args]
+    pack = lambda t: ((saved.append((tuple(t.shape), t.dtype)) if saved is not None else None), t)[1]
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda t: t):
+        y = f(*leaves, *rest)
+    grad = torch.ones_like(y) if grad is None else grad(y)
+    return [y.detach(), *torch.autograd.grad(y, leaves, grad)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", NAMES)
+def test_same_bits_and_saved_tensors_as_the_classes(name):
+    import torch
+    front, cls, args, rest = _calls()[name]
+    apply = lambda *a: cls.apply(*(a if name != "bias_gelu_linear_no_bias" else (*a, None)))
+    wide = lambda y: torch.linspace(-1, 1, y.shape[-1], device="cuda").to(y.dtype).expand(y.shape)   # a gradient that is a view
+    for grad in (None, wide):
+        s1, s2 = [], []
+        a, b = _pass(front, args, rest, grad, s1), _pass(apply, args, rest, grad, s2)
+        assert s1 == s2 and len(a) == len(b)
+        for t, u in zip(a, b):
+            assert t.shape == u.shape and t.dtype == u.dtype and torch.equal(t, u)
+    with torch.no_grad():
+        assert torch.equal(front(*args, *rest), a[0]) and not front(*args, *rest).requires_grad
+
+
+@pytest.mark.gpu
+def test_plain_calls_are_taken_and_others_are_declined():
+    import torch
+    from paper_2309_16669_amd import autograd as ag
+    native = ag.native_calls()
+    front, cls, args, rest = _calls()["layer_norm"]
+    assert native.layer_norm(*args, 1e-5) is not None
+
+    class Sub(torch.Tensor):
+        pass
+    x, gamma, beta = args
+    declined = [(x.as_subclass(Sub), gamma, beta), (x.float(), gamma, beta), (x, gamma.double(), beta), (x, gamma[:-8], beta),
+                (x.cpu(), gamma, beta), (x[:0], gamma, beta)]
+    for bad in declined:
+        assert native.layer_norm(*bad, 1e-5) is None
+    q, k, v = _calls()["attention"][2]
+    assert native.attention(q, k, v, 0.125, False) is not None
+    for bad in ((q.float(), k, v), (q, k[:, :-1], v), (q, k.half(), v), (q[0], k[0], v[0])):
+        assert native.attention(*bad, 0.125, False) is None
+    # refused before, refused now: function transforms and forward-mode tangents
+    for f in (lambda: torch.func.vmap(ag.layer_norm, in_dims=(0, None, None))(x, gamma, beta),
+              lambda: torch.func.jvp(lambda t: ag.layer_norm(t, gamma, beta), (x,), (x,))):
+        with pytest.raises(Exception):
+            f()
+
+
+@pytest.mark.gpu
+def test_errors_of_the_library_keep_their_type_in_both_directions():
+    import torch
+    import paper_2309_16669_amd as av
+    from paper_2309_16669_amd import autograd as ag
+    bad = [torch.randn(1, 40, 2, 48, device="cuda").to(torch.bfloat16) for _ in range(3)]      # d = 48 is not built
+    with pytest.raises(av.AvionError) as e:
+        ag.attention(*bad)
+    assert e.value.code == av.EUNSUPPORTED
+    q, k, v = (t.requires_grad_() for t in _calls()["attention"][2])
+    o = ag.attention(q, k, v)
+    odd = torch.zeros(o.numel() + 1, dtype=o.dtype, device="cuda")[1:].view_as(o)              # contiguous, off by two bytes
+    with pytest.raises(av.AvionError) as e:
+        torch.autograd.grad(o, [q], odd)
+    assert e.value.code == av.EUNSUPPORTED
+
+
+@pytest.mark.gpu
+def test_checkpointing_rebuilds_the_same_gradients():
+    import torch
+    from torch.utils.checkpoint import checkpoint
+    for name in ("attention", "bias_gelu_linear"):
+        front, cls, args, rest = _calls()[name]
+        a = _pass(front, args, rest)
+        b = _pass(lambda *t: checkpoint(front, *t, use_reentrant=False), args, rest)
+        assert all(torch.equal(t, u) for t, u in zip(a, b))
+
+
+def test_host_tensors_are_refused_as_before():
+    import torch
+    from paper_2309_16669_amd import autograd as ag
+    q = torch.from_numpy(np.zeros((1, 40, 2, 64), np.float32)).to(torch.bfloat16)
+    with pytest.raises(ValueError):
+        ag.attention(q, q, q)
+    with pytest.raises(ValueError):
+        ag.layer_norm(q, torch.ones(64), torch.zeros(64))
