@@ -15,6 +15,7 @@
 
 #include "avion_bwd.h"
 #include "avion_fwd.h"
+#include "avion_head.h"
 #include "avion_ln.h"
 #include "avion_small.h"
 #include "avion_gelu.h"
@@ -71,6 +72,8 @@ struct Variant {
     bool f16;
     bool causal;
 };
+
+constexpr long long kComputeUnits = 256;
 
 constexpr float kMinScale = 8.673617379884035e-19f;  // 2^-60
 
@@ -137,20 +140,20 @@ int launch_fwd(const raw16* q, const raw16* k, const raw16* v, raw16* o, float* 
     return end_launch("launch avion_fwd_kernel");
 }
 
-template <int D, int NW, int KG, typename E, bool CAUSAL>
+template <int D, int NW, int KG, typename E, bool CAUSAL, bool TILE16>
 int launch_dq(const raw16* q, const raw16* k, const raw16* v, const raw16* o, const raw16* dO, const float* lse, raw16* dq,
               float* rowsc, int B, int H, int N, Strides rs, float scale, hipStream_t st)
 {
     using Cfg = DqCfg<D, NW, KG>;
     static std::atomic<bool> lds_allowed{false};
-    const hipError_t attr = allow_lds(avion_dq_kernel<D, NW, KG, E, CAUSAL>, Cfg::LDS_BYTES, lds_allowed);
+    const hipError_t attr = allow_lds(avion_dq_kernel<D, NW, KG, E, CAUSAL, TILE16>, Cfg::LDS_BYTES, lds_allowed);
     if (attr != hipSuccess) return hip_fail(attr, "hipFuncSetAttribute(dq)");
     const int nqb = (N + Cfg::BM - 1) / Cfg::BM;
     const long long nblocks = (long long)nqb * B * H;
     unsigned grid;
     if (!grid_for(nblocks, &grid)) return AVION_EUNSUPPORTED;
     begin_launch();
-    hipLaunchKernelGGL((avion_dq_kernel<D, NW, KG, E, CAUSAL>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, o, dO, lse, dq,
+    hipLaunchKernelGGL((avion_dq_kernel<D, NW, KG, E, CAUSAL, TILE16>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, o, dO, lse, dq,
                        rowsc, H, N, rs.qkv, rs.o, nqb, (int)nblocks, scale * kLog2e, scale);
     return end_launch("launch avion_dq_kernel");
 }
@@ -189,6 +192,25 @@ int launch_bwd_small(const raw16* q, const raw16* k, const raw16* v, const raw16
     hipLaunchKernelGGL((avion_bwd_small_kernel<D, NW, E, CAUSAL>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, o,
                        dO, lse, dq, dk, dv, rowsc, H, N, rs.qkv, rs.o, (int)nblocks, scale * kLog2e, scale);
     return end_launch("launch avion_bwd_small_kernel");
+}
+
+// Whole backward, one workgroup per head at a time (avion_head.h).
+template <int NW, typename E, bool CAUSAL>
+int launch_bwd_head(const raw16* q, const raw16* k, const raw16* v, const raw16* o, const raw16* dO, const float* lse,
+                    raw16* dq, raw16* dk, raw16* dv, int B, int H, int N, Strides rs, float scale, hipStream_t st)
+{
+    using Cfg = HeadCfg<NW>;
+    static std::atomic<bool> lds_allowed{false};
+    const hipError_t attr = allow_lds(avion_bwd_head_kernel<NW, E, CAUSAL>, Cfg::LDS_BYTES, lds_allowed);
+    if (attr != hipSuccess) return hip_fail(attr, "hipFuncSetAttribute(bwd_head)");
+    const int heads = B * H;
+    unsigned grid;
+    if (!grid_for(heads, &grid)) return AVION_EUNSUPPORTED;
+    if (Cfg::WALK) grid = (unsigned)std::min<long long>(heads, kComputeUnits);  // workgroups walk the heads
+    begin_launch();
+    hipLaunchKernelGGL((avion_bwd_head_kernel<NW, E, CAUSAL>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, o,
+                       dO, lse, dq, dk, dv, H, N, rs.qkv, rs.o, heads, scale * kLog2e, scale);
+    return end_launch("launch avion_bwd_head_kernel");
 }
 
 // Sequences of at most 32 tokens: one wavefront per window of floor(32 / N) problems (avion_small.h).
@@ -242,24 +264,29 @@ int launch_win_bwd(const raw16* q, const raw16* k, const raw16* v, const raw16* 
 }
 
 // Kernel instances: four wavefronts per workgroup for every kernel, head size, format and masking.
-// Calls f(head dim, element format, causal) with the three as compile-time tags.
+// by_variant calls f(head dim, element format, causal) with the three as compile-time tags, by_format
+// f(element format, causal).
 template <typename T>
 struct TypeTag {
     using type = T;
 };
 template <typename F>
+int by_format(Variant var, F f)
+{
+    auto by_mask = [&](auto fmt) {
+        if (var.causal) return f(fmt, std::true_type{});
+        return f(fmt, std::false_type{});
+    };
+    if (var.f16) return by_mask(TypeTag<F16>{});
+    return by_mask(TypeTag<Bf16>{});
+}
+template <typename F>
 int by_variant(Variant var, int d, F f)
 {
-    auto by_dim = [&](auto fmt, auto causal) {
+    return by_format(var, [&](auto fmt, auto causal) {
         if (d == 64) return f(std::integral_constant<int, 64>{}, fmt, causal);
         return f(std::integral_constant<int, 80>{}, fmt, causal);
-    };
-    auto by_fmt = [&](auto causal) {
-        if (var.f16) return by_dim(TypeTag<F16>{}, causal);
-        return by_dim(TypeTag<Bf16>{}, causal);
-    };
-    if (var.causal) return by_fmt(std::true_type{});
-    return by_fmt(std::false_type{});
+    });
 }
 
 // How one launch of the big kernels is cut.  A workgroup owns 32 * NW rows of the stationary side; with
@@ -275,9 +302,8 @@ int by_variant(Variant var, int d, F f)
 // 32 x 785 17.4 -> 15.1; 39.4 -> 34.9, 16 x 785 backward 37 -> 27, 16 x 500 11.9 -> 9.2, 8 x 200 7.9 -> 6.9;
 // 16.9 -> 14.5, 12 x 785 (d = 80) 19.9 -> 15.6; 47 -> 36.  On the other side of the lines two groups lose:
 // 24 x 1568 85 -> 99 (backward), 64 x 785 22.4 -> 22.4; 53 -> 60, 64 x 300 21.0 -> 21.2, 240 x 77 6.5 -> 6.9.
-constexpr long long kComputeUnits = 256;
-// `min_tiles`: the backward's two phases keep one group up to 128 tokens, where the whole backward is one
-// launch whose bits they give.
+// `min_tiles`: the backward's two phases keep one group where the whole backward is one launch, whose bits
+// they give: up to 256 tokens at 64 channels, 128 at 80.
 template <typename F>
 int by_split(long long heads, int N, int min_tiles, F f)
 {
@@ -321,6 +347,30 @@ bool workspace_ok(const void* workspace, size_t workspace_bytes, int B, int H, i
            workspace_bytes >= avion_attn_bwd_workspace_bytes(B, H, N, d);
 }
 
+// Whole heads per workgroup (avion_head.h): what its LDS holds at 64 channels (at 80 three tiles of 256 rows
+// take 160 KB), above the window kernels' lengths.  Both sides' times stand there.
+constexpr int kHeadMaxN = 256;
+bool by_head(int N, int d) { return d == 64 && N > kWindowMaxN && N <= kHeadMaxN; }
+
+int head_impl(const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dO, void* dq,
+              void* dk, void* dv, int B, int H, int N, int packed, Variant var, float scale, void* stream)
+{
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const Strides rs{packed * H * 64, H * 64};
+    const raw16 *qq = static_cast<const raw16*>(q), *kk = static_cast<const raw16*>(k), *vv = static_cast<const raw16*>(v),
+                *oo = static_cast<const raw16*>(o), *gg = static_cast<const raw16*>(dO);
+    raw16 *dqq = static_cast<raw16*>(dq), *dkk = static_cast<raw16*>(dk), *dvv = static_cast<raw16*>(dv);
+    return by_format(var, [&](auto fmt, auto causal) {
+        using E = typename decltype(fmt)::type;
+        constexpr bool C = decltype(causal)::value;
+        if (N <= HeadCfg<4>::MAX_N)
+            return launch_bwd_head<4, E, C>(qq, kk, vv, oo, gg, lse, dqq, dkk, dvv, B, H, N, rs, scale, st);
+        return launch_bwd_head<8, E, C>(qq, kk, vv, oo, gg, lse, dqq, dkk, dvv, B, H, N, rs, scale, st);
+    });
+}
+
+int split_tiles(int d) { return d == 64 ? kHeadMaxN / 64 + 1 : BwdSmallCfg<80, 4>::MAX_N / 64 + 1; }
+
 int dq_impl(const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dO, void* dq, int B,
             int H, int N, int d, int packed, Variant var, float scale, void* workspace, size_t workspace_bytes, void* stream)
 {
@@ -337,11 +387,13 @@ int dq_impl(const void* q, const void* k, const void* v, const void* o, const fl
     const raw16 *qq = static_cast<const raw16*>(q), *kk = static_cast<const raw16*>(k), *vv = static_cast<const raw16*>(v),
                *oo = static_cast<const raw16*>(o), *gg = static_cast<const raw16*>(dO);
     raw16* dqq = static_cast<raw16*>(dq);
-    return by_split((long long)B * H, N, 3, [&](auto nw, auto kg) {
+    // the lengths of the head kernel: only avion_attn_bwd_dq comes here with them (bf16, no mask, not packed)
+    if (by_head(N, d)) return launch_dq<64, 4, 1, Bf16, false, true>(qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
+    return by_split((long long)B * H, N, split_tiles(d), [&](auto nw, auto kg) {
         return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
             constexpr int KG = std::min(decltype(kg)::value, 2);
             return launch_dq<decltype(dim)::value, decltype(nw)::value, KG, typename decltype(fmt)::type,
-                      decltype(causal)::value>(qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
+                      decltype(causal)::value, decltype(dim)::value == 80>(qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
         });
     });
 }
@@ -363,7 +415,7 @@ int dkdv_impl(const void* q, const void* k, const void* v, const float* lse, con
     const raw16 *qq = static_cast<const raw16*>(q), *kk = static_cast<const raw16*>(k), *vv = static_cast<const raw16*>(v),
                *gg = static_cast<const raw16*>(dO);
     raw16 *dkk = static_cast<raw16*>(dk), *dvv = static_cast<raw16*>(dv);
-    return by_split((long long)B * H, N, 3, [&](auto nw, auto kg) {
+    return by_split((long long)B * H, N, split_tiles(d), [&](auto nw, auto kg) {
         return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
             constexpr int KG = std::min(decltype(kg)::value, 2);
             return launch_dkdv<decltype(dim)::value, decltype(nw)::value, KG, typename decltype(fmt)::type,
@@ -372,19 +424,19 @@ int dkdv_impl(const void* q, const void* k, const void* v, const float* lse, con
     });
 }
 
-// Whole backward in one launch (N <= 128); arguments already checked by the caller.
+// Whole backward in one launch of both passes (d = 80, N <= 128); arguments already checked by the caller.
 int bwd_small_impl(const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dO, void* dq,
-                   void* dk, void* dv, int B, int H, int N, int d, int packed, Variant var, float scale, void* workspace,
+                   void* dk, void* dv, int B, int H, int N, int packed, Variant var, float scale, void* workspace,
                    void* stream)
 {
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const Strides rs{packed * H * d, H * d};
+    const Strides rs{packed * H * 80, H * 80};
     float* rowsc = static_cast<float*>(workspace);
     const raw16 *qq = static_cast<const raw16*>(q), *kk = static_cast<const raw16*>(k), *vv = static_cast<const raw16*>(v),
                 *oo = static_cast<const raw16*>(o), *gg = static_cast<const raw16*>(dO);
     raw16 *dqq = static_cast<raw16*>(dq), *dkk = static_cast<raw16*>(dk), *dvv = static_cast<raw16*>(dv);
-    return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
-        return launch_bwd_small<decltype(dim)::value, 4, typename decltype(fmt)::type, decltype(causal)::value>(
+    return by_format(var, [&](auto fmt, auto causal) {
+        return launch_bwd_small<80, 4, typename decltype(fmt)::type, decltype(causal)::value>(
             qq, kk, vv, oo, gg, lse, dqq, dkk, dvv, rowsc, B, H, N, rs, scale, st);
     });
 }
@@ -413,8 +465,10 @@ int bwd_impl(const void* q, const void* k, const void* v, const void* o, const f
                 qq, kk, vv, oo, gg, lse, dqq, dkk, dvv, B, H, N, rs, scale, st);
         });
     }
-    if (N <= BwdSmallCfg<64, 4>::MAX_N)
-        return bwd_small_impl(q, k, v, o, lse, dO, dq, dk, dv, B, H, N, d, packed, var, scale, workspace, stream);
+    if (by_head(N, d))
+        return head_impl(q, k, v, o, lse, dO, dq, dk, dv, B, H, N, packed, var, scale, stream);
+    if (N <= BwdSmallCfg<80, 4>::MAX_N)
+        return bwd_small_impl(q, k, v, o, lse, dO, dq, dk, dv, B, H, N, packed, var, scale, workspace, stream);
     const int rq = dq_impl(q, k, v, o, lse, dO, dq, B, H, N, d, packed, var, scale, workspace, workspace_bytes, stream);
     if (rq != AVION_OK) return rq;
     return dkdv_impl(q, k, v, lse, dO, dk, dv, B, H, N, d, packed, var, scale, workspace, workspace_bytes, stream);

@@ -37,27 +37,24 @@
 #include "avion_common.h"
 
 // Groups of wavefronts that walked different tiles for the same rows: the accumulators of groups 1..KG-1
-// are added to group 0's through LDS ([value][lane] floats in `area`, (KG-1)*NW*CT*4 KB) in group order.
+// are added to group 0's through LDS ([value][lane] floats in `area`) in group order.
 // Every wavefront of the workgroup calls it after its last tile read.
-template <int NW, int KG, int CT>
-DEVINL void add_groups(char* area, f32x16 (&acc)[CT], int grp, int wave, int lane, bool wave_active)
+template <int NW, int KG, typename Acc>
+DEVINL void add_groups(char* area, Acc& acc, int grp, int wave, int lane, bool wave_active)
 {
+    constexpr int VALS = sizeof(Acc) / 4, WAVE_BYTES = VALS * 256;
     if (grp > 0 && wave_active) {
-        float* mine = reinterpret_cast<float*>(area + ((grp - 1) * NW + wave) * CT * 4096) + lane;
+        float* mine = reinterpret_cast<float*>(area + ((grp - 1) * NW + wave) * WAVE_BYTES) + lane;
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) mine[(ct * 16 + i) * 64] = acc[ct][i];
+        for (int i = 0; i < VALS; ++i) mine[i * 64] = acc_get(acc, i);
     }
     __syncthreads();
     if (grp == 0 && wave_active) {
 #pragma unroll
         for (int og = 0; og < KG - 1; ++og) {
-            const float* other = reinterpret_cast<const float*>(area + (og * NW + wave) * CT * 4096) + lane;
+            const float* other = reinterpret_cast<const float*>(area + (og * NW + wave) * WAVE_BYTES) + lane;
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[ct][i] += other[(ct * 16 + i) * 64];
+            for (int i = 0; i < VALS; ++i) acc_add(acc, i, other[i * 64]);
         }
     }
 }
@@ -72,11 +69,17 @@ struct DqCfg {
     static constexpr int BM = 32 * NW;
     using Ring = TileRing<D, NW, 2, false>;
     static constexpr int LDS_BYTES = KG * Ring::LDS_BYTES;
-    static constexpr int WAVES_PER_SIMD = D == 64 && KG == 1 ? 3 : 2;  // LDS would allow more; registers do not
+    static constexpr int WAVES_PER_SIMD = KG > 1 ? 2 : 3;  // LDS would allow four at d = 64; registers do not
 };
 
 // The work of one workgroup: query block qb of (batch, head) bh.
-template <int D, int NW, int KG, typename E, bool CAUSAL>
+// TILE16: dQ^T is formed in 16 x 16 tiles (16x16x32 products) over 32 keys at a time; dS^T changes from the
+// score accumulators' layout to their B operand with two lane swaps per word.  At d = 80 the channels are
+// then five tiles instead of three of 32 with a half of padding, and 162 registers instead of 204 hold three
+// wavefronts per SIMD instead of two: 128 heads x 1568 197 -> 174 us.  At d = 64 it serves the lengths of
+// avion_bwd_head_kernel (avion_head.h), whose operands, order and so bits these are (3072 x 196 121 -> 122 us
+// for this phase alone); beyond them the 32 x 32 tiles are 0 to 3 % faster and stay.
+template <int D, int NW, int KG, typename E, bool CAUSAL, bool TILE16>
 DEVINL void avion_dq_body(char* smem, const raw16* __restrict__ q, const raw16* __restrict__ k,
                           const raw16* __restrict__ v, const raw16* __restrict__ o, const raw16* __restrict__ dO,
                           const float* __restrict__ lse, raw16* __restrict__ dq, float* __restrict__ rowsc, int H, int N,
@@ -85,7 +88,7 @@ DEVINL void avion_dq_body(char* smem, const raw16* __restrict__ q, const raw16* 
     using Cfg = DqCfg<D, NW, KG>;
     using Ring = typename Cfg::Ring;
     constexpr int BN = Cfg::BN, BM = Cfg::BM, STRIDE = Ring::STRIDE;
-    constexpr int KS = D / 16, CT = (D + 31) / 32;
+    constexpr int KS = D / 16, CT = TILE16 ? D / 16 : (D + 31) / 32;  // 16-deep steps and channel tiles
 
     const int b = bh / H, h = bh % H;
     const int tid = threadIdx.x, lane = tid % 64, l32 = lane % 32, g = lane / 32;
@@ -138,9 +141,15 @@ DEVINL void avion_dq_body(char* smem, const raw16* __restrict__ q, const raw16* 
         }
     }
     const float nlc = -lc;
-    f32x16 acc[CT];
+    std::conditional_t<TILE16, f32x4[CT][2], f32x16[CT]> acc;  // [channel tile]([query tile])
+    acc_zero(acc);
+    // TILE16: dP starts from -delta of the lane's query, so the subtraction in dS costs no vector instruction
+    // (the 32 x 32 form has no registers for it)
+    f32x16 dp0 = f32x16_zero();
+    if constexpr (TILE16) {
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[ct] = f32x16_zero();
+        for (int i = 0; i < 16; ++i) dp0[i] = -dl;
+    }
 
     Ring::landed_barrier();  // tile 0 is in LDS (and the fragments above have arrived)
 
@@ -155,25 +164,39 @@ DEVINL void avion_dq_body(char* smem, const raw16* __restrict__ q, const raw16* 
             const frag8 ak = nat_frag(kt, STRIDE, 32 * hk + l32, ks, g);
             const frag8 av = nat_frag(vt, STRIDE, 32 * hk + l32, ks, g);
             s = E::mfma(ak, qf[ks], ks == 0 && !RAGGED ? f32x16_zero() : s);
-            dp = E::mfma(av, gf[ks], ks == 0 ? f32x16_zero() : dp);
+            dp = E::mfma(av, gf[ks], ks == 0 ? dp0 : dp);
         }
-        // the K^T operands are requested before the vector work so that they are there after it
-        frag8 kt_f[2][CT];
+        // the K^T operands of the 32 x 32 form are requested before the vector work so that they are there
+        // after it; the other form's registers are worth more as a third wavefront
+        frag8 kt_f[2][TILE16 ? 1 : CT];
+        if constexpr (!TILE16) {
 #pragma unroll
-        for (int half = 0; half < 2; ++half)
+            for (int half = 0; half < 2; ++half)
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) kt_f[half][ct] = tr_frag(kt, STRIDE, tr_off, ct, 2 * hk + half);
+                for (int ct = 0; ct < CT; ++ct) kt_f[half][ct] = tr_frag(kt, STRIDE, tr_off, ct, 2 * hk + half);
+        }
         u32x4 df[2];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const float pe = fast_exp2(fmaf(s[i], cs, nlc));
-            s[i] = pe * (dp[i] - dl);
+            s[i] = TILE16 ? pe * dp[i] : pe * (dp[i] - dl);
             if (i % 2 == 1) df[i / 8][(i / 2) % 4] = E::pack(s[i - 1], s[i]);
         }
+        if constexpr (TILE16) {
+            frag8 dsf[2];
+            acc_to_frag16(df[0], df[1], dsf[0], dsf[1]);
 #pragma unroll
-        for (int half = 0; half < 2; ++half)
+            for (int ct = 0; ct < CT; ++ct) {
+                const frag8 a = tr16_frag(kt, STRIDE, lane, 16 * ct, hk);
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) acc[ct] = E::mfma(kt_f[half][ct], as_frag8(df[half]), acc[ct]);
+                for (int x = 0; x < 2; ++x) acc[ct][x] = E::mfma16(a, dsf[x], acc[ct][x]);
+            }
+        } else {
+#pragma unroll
+            for (int half = 0; half < 2; ++half)
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) acc[ct] = E::mfma(kt_f[half][ct], as_frag8(df[half]), acc[ct]);
+        }
     };
 
     for (int t = t0; t < t0 + per; ++t) {
@@ -191,14 +214,15 @@ DEVINL void avion_dq_body(char* smem, const raw16* __restrict__ q, const raw16* 
     }
     if constexpr (KG > 1) {
         add_groups<NW, KG>(smem + NW * RowStore<D, E>::BYTES, acc, grp, wave, lane, wave_active);
-        static_assert(NW * RowStore<D, E>::BYTES + (KG - 1) * NW * CT * 4096 <= Cfg::LDS_BYTES, "exchange area");
+        static_assert(NW * RowStore<D, E>::BYTES + (KG - 1) * NW * (int)sizeof(acc) * 64 <= Cfg::LDS_BYTES, "exchange area");
         if (grp > 0) return;
     }
     if (!wave_active) return;
-    RowStore<D, E>::run(smem + wave * RowStore<D, E>::BYTES, acc, scale, dq + head_off + (long)q0 * rs, rs, N - q0, lane);
+    RowStore<D, E>::run(smem + wave * RowStore<D, E>::BYTES, acc, scale, dq + head_off + (long)q0 * rs, rs, N - q0,
+                        lane_from_exec());
 }
 
-template <int D, int NW, int KG, typename E, bool CAUSAL>
+template <int D, int NW, int KG, typename E, bool CAUSAL, bool TILE16>
 __global__ void __launch_bounds__(NW * KG * 64, (DqCfg<D, NW, KG>::WAVES_PER_SIMD))
 avion_dq_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const raw16* __restrict__ v,
                     const raw16* __restrict__ o, const raw16* __restrict__ dO, const float* __restrict__ lse,
@@ -208,7 +232,7 @@ avion_dq_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const 
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int logical = xcd_local_id(blockIdx.x, nblocks);
     if (logical < 0) return;
-    avion_dq_body<D, NW, KG, E, CAUSAL>(smem, q, k, v, o, dO, lse, dq, rowsc, H, N, rs_qkv, rs_o, logical / nqb, logical % nqb,
+    avion_dq_body<D, NW, KG, E, CAUSAL, TILE16>(smem, q, k, v, o, dO, lse, dq, rowsc, H, N, rs_qkv, rs_o, logical / nqb, logical % nqb,
                                     cs, scale);
 }
 
@@ -378,8 +402,8 @@ avion_dkdv_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, cons
 }
 
 // ------------------------------------------------------------------------- whole backward, short sequences
-// For N <= 32*NW one workgroup covers all queries and all keys of a (batch, head): the two passes
-// then run back to back inside one workgroup, so that the second pass finds Q, K, V and dO in the
+// (d = 80; at 64 channels avion_head.h takes these lengths.)  For N <= 32*NW one workgroup covers all
+// queries and all keys of a (batch, head): the two passes then run back to back inside one workgroup, so that the second pass finds Q, K, V and dO in the
 // L2 where the first one has just pulled them (launched separately it would fetch them from HBM
 // again), and one launch is saved.  Same arithmetic, same bits as the two kernels.  The per-query
 // scalars still travel through the workspace: a workgroup-scope fence makes the first pass's stores visible
@@ -403,7 +427,7 @@ avion_bwd_small_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k,
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int bh = xcd_local_id(blockIdx.x, nblocks);
     if (bh < 0) return;
-    avion_dq_body<D, NW, 1, E, CAUSAL>(smem, q, k, v, o, dO, lse, dq, rowsc, H, N, rs_qkv, rs_o, bh, 0, cs, scale);
+    avion_dq_body<D, NW, 1, E, CAUSAL, true>(smem, q, k, v, o, dO, lse, dq, rowsc, H, N, rs_qkv, rs_o, bh, 0, cs, scale);
     // Workgroup scope is enough (writer and reader wavefronts sit on one compute unit and share its
     // vector cache) and is only a wait for the stores; a device-scope fence would write back and
     // invalidate the L2 once per workgroup.

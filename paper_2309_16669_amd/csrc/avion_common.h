@@ -68,6 +68,10 @@ struct Bf16 {
     {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
     }
+    DEVINL static f32x4 mfma16(frag8 a, frag8 b, f32x4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
+    }
     // two fp32 -> packed pair, low half = a
     DEVINL static unsigned pack(float a, float b)
     {
@@ -91,6 +95,10 @@ struct F16 {
     DEVINL static f32x16 mfma(frag8 a, frag8 b, f32x16 c)
     {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
+    }
+    DEVINL static f32x4 mfma16(frag8 a, frag8 b, f32x4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
     }
     DEVINL static unsigned pack(float a, float b)
     {
@@ -296,6 +304,69 @@ DEVINL frag8 tr_frag(const char* tile, int stride, int lane_off, int ct, int ste
     return as_frag8(r);
 }
 
+// v_mfma_f32_16x16x32: A (16 x 32) and B (32 x 16) hold row / column l%16 and 8 contraction slots of lane
+// group G = l/16, the accumulator column l%16 and rows 4G..4G+3.  Slots 0..3 of group G stand for the
+// 32-step's tokens 4G..4G+3, slots 4..7 for 16+4G..16+4G+3.
+// Transposed fragment of that form: lane = column c0 + l%16, tokens of 32-token step `step`
+DEVINL frag8 tr16_frag(const char* tile, int stride, int lane, int c0, int step)
+{
+    const int G = lane >> 4, j = lane & 15;
+    const lds_char* p = (const lds_char*)tile + (32 * step + 4 * G + (j >> 2)) * stride + (c0 + 4 * (j & 3)) * 2;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 16 * stride));
+    const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+    const u32x4 r = {l2[0], l2[1], h2[0], h2[1]};
+    return as_frag8(r);
+}
+// 16 x 16 tile of transposed accumulators: lane = row l%16 of the result (`row` points at its 16 channels),
+// 4 channels of group G
+template <typename E>
+DEVINL void store_tile16(const f32x4& acc, float mul, raw16* row, int lane)
+{
+    const u32x2 w = {E::pack(acc[0] * mul, acc[1] * mul), E::pack(acc[2] * mul, acc[3] * mul)};
+    *reinterpret_cast<u32x2*>(row + 4 * (lane >> 4)) = w;
+}
+// 32 x 32 accumulator rounded to packed pairs (w0 = fragment of rows 0..15, w1 of rows 16..31 as acc_to_frag
+// packs them) -> B fragments of 16x16x32 for its columns 0..15 (b0) and 16..31 (b1).  Row quarters 4G..4G+3
+// sit with the columns in two 16-lane rows of each wavefront half; two swaps per word bring quarter G of
+// both 16-row blocks to lane group G.
+DEVINL void acc_to_frag16(u32x4 w0, u32x4 w1, frag8& b0, frag8& b1)
+{
+    const unsigned x[4] = {w0[0], w0[1], w1[0], w1[1]}, y[4] = {w0[2], w0[3], w1[2], w1[3]};
+    u32x4 r0, r1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const auto a = __builtin_amdgcn_permlane32_swap(x[i], y[i], false, false);
+        const auto c = __builtin_amdgcn_permlane16_swap(a[0], a[1], false, false);
+        r0[i] = c[0];
+        r1[i] = c[1];
+    }
+    b0 = as_frag8(r0);
+    b1 = as_frag8(r1);
+}
+
+// The two forms of a wavefront's 32-column result: transposed 32 x 32 tiles, or 16 x 16 tiles [channel tile][column tile]
+template <int CT>
+DEVINL void acc_zero(f32x16 (&acc)[CT])
+{
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[ct] = f32x16_zero();
+}
+template <int CT>
+DEVINL void acc_zero(f32x4 (&acc)[CT][2])
+{
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[ct][0] = acc[ct][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+// register i of either form
+template <int CT>
+DEVINL float acc_get(const f32x16 (&acc)[CT], int i) { return acc[i / 16][i % 16]; }
+template <int CT>
+DEVINL void acc_add(f32x16 (&acc)[CT], int i, float x) { acc[i / 16][i % 16] += x; }
+template <int CT>
+DEVINL float acc_get(const f32x4 (&acc)[CT][2], int i) { return acc[i / 8][i / 4 % 2][i % 4]; }
+template <int CT>
+DEVINL void acc_add(f32x4 (&acc)[CT][2], int i, float x) { acc[i / 8][i / 4 % 2][i % 4] += x; }
 // ---------------------------------------------------------------------------------------------
 // Staging of a tile of R token rows x D channels from global memory into LDS through registers,
 // so that the global loads of the next tile are in flight while the current one is computed on.
@@ -483,6 +554,21 @@ struct RowStore {
                     *reinterpret_cast<u32x2*>(region + l32 * STRIDE + c0 * 2) = w;
                 }
             }
+        flush(region, dst, rs, rows_valid, lane);
+    }
+    // the same for 16 x 16 tiles: acc[channel tile][row tile], lane = row l%16, register v = channel 4*(l/16) + v
+    DEVINL static void run(char* region, const f32x4 (&acc)[D / 16][2], float mul, raw16* dst, long rs, int rows_valid, int lane)
+    {
+#pragma unroll
+        for (int ct = 0; ct < D / 16; ++ct)
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+                store_tile16<E>(acc[ct][x], mul, reinterpret_cast<raw16*>(region + (16 * x + lane % 16) * STRIDE + ct * 32), lane);
+        flush(region, dst, rs, rows_valid, lane);
+    }
+    // the staged rows to memory
+    DEVINL static void flush(const char* region, raw16* dst, long rs, int rows_valid, int lane)
+    {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

@@ -175,3 +175,30 @@ def test_a_group_whose_reference_overflows_redoes_the_block(H, N, sink):
     # (tests/test_tolerance_model.py).  O within one unit in the last place of its largest value, LSE in fp32.
     assert np.all(np.isfinite(o)) and np.abs(o - ro).max() <= 2.0 ** -10 * np.abs(ro).max()
     assert np.abs(lse - rl).max() <= 2e-6 * np.abs(rl).max() + 1e-3
+
+
+# Whole heads per workgroup (64 channels, 33..256 tokens): both sides of every 32-token block, 64-row slot and instance
+# boundary, one block to eight, more heads than compute units (workgroups that walk several heads, with heads left over),
+# every format, mask and packing.  The two phases give the same bits (the workspace of the first feeds the second).
+@pytest.mark.parametrize("B,H,N,f16,causal,packed", [
+    (1, 3, 33, False, False, False), (2, 3, 64, True, True, True), (3, 2, 65, False, True, False), (1, 2, 95, True, False, True),
+    (1, 5, 96, False, False, True), (2, 2, 97, False, True, False), (1, 3, 128, True, False, False), (1, 3, 129, False, True, True),
+    (2, 2, 160, False, False, False), (1, 2, 161, True, True, False), (1, 3, 192, False, False, True), (1, 3, 193, False, True, False),
+    (1, 2, 224, True, False, False), (1, 2, 225, False, False, True), (2, 1, 256, False, True, True), (1, 2, 257, False, False, False),
+    (27, 10, 130, False, False, True), (3, 172, 196, False, True, False), (45, 6, 256, True, False, False), (33, 16, 49, False, False, False)])
+def test_whole_heads_match_the_oracle_and_the_two_phases(B, H, N, f16, causal, packed):
+    import torch
+    import paper_2309_16669_amd as av
+    w = si.small_workload(B, H, N, 64, seed=9500 + N)
+    x = si.make_inputs(w, fmt="f16" if f16 else "bf16")
+    out = run_ex(w, x, f16, causal, packed)
+    check(w, x, out, f16, causal)
+    if f16 or causal or packed:
+        return                                            # the phases are bf16, unmasked and unpacked entry points
+    q, k, v, dO = (_upload(x[n], False) for n in ("q", "k", "v", "dO"))
+    dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(3))
+    ws = torch.empty(av.attn_bwd_workspace_bytes(B, H, N, 64), dtype=torch.uint8, device="cuda").fill_(255)
+    av.attn_bwd_dq(q, k, v, out["o"], out["lse"], dO, dq, w.scale, ws)
+    av.attn_bwd_dkdv(q, k, v, out["lse"], dO, dk, dv, w.scale, ws)
+    for n, t in (("dq", dq), ("dk", dk), ("dv", dv)):
+        assert torch.equal(out[n].contiguous().view(torch.int16), t.view(torch.int16)), n
