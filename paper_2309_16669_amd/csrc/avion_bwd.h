@@ -151,6 +151,8 @@ DEVINL void avion_dq_body(char* smem, const raw16* __restrict__ q, const raw16* 
         for (int i = 0; i < 16; ++i) dp0[i] = -dl;
     }
 
+    hold(qf);
+    hold(gf);
     Ring::landed_barrier();  // tile 0 is in LDS (and the fragments above have arrived)
 
     // one 32-key unit: rows 32*hk.. of the tile pair; RAGGED units reach past the last key and
@@ -306,6 +308,8 @@ DEVINL void avion_dkdv_body(char* smem, const raw16* __restrict__ q, const raw16
         dka[ct] = f32x16_zero();
         dva[ct] = f32x16_zero();
     }
+    hold(kf);
+    hold(vf);
     Ring::landed_barrier();  // the first tile is in LDS (and the fragments above have arrived)
 
     for (int t = t0; t < t0 + per; ++t) {

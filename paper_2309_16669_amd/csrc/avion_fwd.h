@@ -204,6 +204,7 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
     for (int ct = 0; ct < CT; ++ct) oacc[ct] = f32x16_zero();
     float m_used = 0.f, lsum = 0.f, rsum = 0.f;
 
+    hold(qf);
     Ring::landed_barrier();  // tile 0 is in LDS (and the Q fragments have arrived)
 
     // S^T of one unit (32 keys starting at row 32*hk of the K tile); RAGGED units reach past the

@@ -19,9 +19,9 @@
 // their two blocks are done, and the next head's rows are fetched into them right then, without registers
 // (LDS-direct loads); O, V and LSE follow in registers.  4 wavefronts (33..128 tokens): two workgroups per
 // compute unit overlap each other, one head each.
-// Measured, whole backward, us, two kernels -> this one: 3072 heads x 196 257 -> 203 (616 MB: 3.0 TB/s; one
+// Measured, whole backward, us, two kernels -> this one: 3072 heads x 196 252 -> 191 (616 MB: 3.2 TB/s; one
 // head per workgroup 259), x 160 203 -> 144, x 256 298 -> 248, 8000 x 200 causal 583 -> 460; one launch of
-// two passes -> this one: 16384 x 77 causal 367 -> 325 (4.0 TB/s), 4000 x 128 143 -> 126, 8 x 77 10.5 -> 8.6.
+// two passes -> this one: 16384 x 77 causal 367 -> 304 (4.3 TB/s), 4000 x 128 143 -> 119, 8 x 77 10.5 -> 8.6.
 // dQ in 32 x 32 tiles after every fourth block (fewer barriers, longer chains): 226 at 3072 x 196.
 #pragma once
 #include "avion_common.h"
@@ -115,6 +115,9 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
         const int next = bh + gridDim.x;
         const bool more = Cfg::WALK && next < nheads;
         const long off = head_off(bh);
+        hold(vf);
+        hold(of);
+        asm volatile("" : "+v"(lse_in));
         asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // this head has landed
 
         // per-query scalars of this wavefront's query block: LSE*log2e (+inf past the end: weight 0) and -delta
