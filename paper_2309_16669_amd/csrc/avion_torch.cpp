@@ -72,6 +72,18 @@ bool parameter(PyObject* obj, int64_t width, const Tensor& like, const Tensor** 
            (*out)->device() == like.device();
 }
 
+// The binding's checks (`_require`) before an address is taken.  A saved tensor is whatever the unpack hook of
+// torch.autograd.graph.saved_tensors_hooks returned: other strides, another format, on the host, shorter.  The
+// incoming gradient has the shape, format and device of the forward's output (autograd checks that).
+void require(const Tensor& t, const char* name, at::IntArrayRef shape, at::ScalarType dtype, const Tensor& grad)
+{
+    TORCH_CHECK_VALUE(t.defined() && t.layout() == at::kStrided && t.is_cuda() && t.device() == grad.device(), name,
+                      " must live on the GPU of the gradient");
+    TORCH_CHECK_VALUE(t.scalar_type() == dtype, name, " must be ", dtype, ", got ", t.scalar_type());
+    TORCH_CHECK_VALUE(t.is_contiguous(), name, " must be contiguous");
+    TORCH_CHECK_VALUE(t.sizes() == shape, name, " must have shape ", shape, ", got ", t.sizes());
+}
+
 Tensor workspace(size_t bytes, const Tensor& like) { return at::empty({(int64_t)bytes}, like.options().dtype(at::kByte)); }
 
 // ------------------------------------------------------------------------------------- attention
@@ -105,8 +117,18 @@ variable_list attention_bwd(const Tensor& q, const Tensor& k, const Tensor& v, c
                             const Tensor& grad, double scale, bool causal)
 {
     const bool packed = !k.defined();
-    const Shape s = shape_of(q, packed);
     const Tensor dO = grad.contiguous();
+    const Shape s = shape_of(dO, false);
+    const at::ScalarType dt = dO.scalar_type();
+    if (packed) {
+        require(q, "qkv", {s.B, s.N, 3, s.H, s.d}, dt, dO);
+    } else {
+        require(q, "q", dO.sizes(), dt, dO);
+        require(k, "k", dO.sizes(), dt, dO);
+        require(v, "v", dO.sizes(), dt, dO);
+    }
+    require(o, "o", dO.sizes(), dt, dO);
+    require(lse, "lse", {s.B, s.H, s.N}, at::kFloat, dO);
     variable_list g{at::empty_like(q)};
     if (!packed) {
         g.push_back(at::empty_like(k));
@@ -204,7 +226,11 @@ struct LayerNorm : torch::autograd::Function<LayerNorm> {
     {
         const variable_list s = ctx->get_saved_variables();
         const Tensor &x = s[0], gamma = s[1].contiguous(), dy = grad[0].contiguous();
-        const int64_t M = x.size(0), D = x.size(1);
+        const int64_t D = dy.size(-1), M = dy.numel() / D;
+        require(x, "x", {M, D}, dy.scalar_type(), dy);
+        require(gamma, "gamma", {D}, at::kFloat, dy);
+        require(s[2], "mean", {M}, at::kFloat, dy);
+        require(s[3], "rstd", {M}, at::kFloat, dy);
         const Tensor dx = at::empty_like(x), dgamma = at::empty_like(gamma), dbeta = at::empty_like(gamma);
         const size_t need = avion_layernorm_bwd_workspace_bytes(M, (int)D);
         const Tensor ws = workspace(need, x);
@@ -257,8 +283,12 @@ struct BiasGelu : torch::autograd::Function<BiasGelu> {
     static variable_list backward(AutogradContext* ctx, variable_list grad)
     {
         const variable_list s = ctx->get_saved_variables();
+        const Tensor dy = grad[0].contiguous();
+        const int64_t F = dy.size(-1);
+        require(s[0], "x", {dy.numel() / F, F}, dy.scalar_type(), dy);
+        require(s[1].contiguous(), "bias", {F}, at::kFloat, dy);
         Tensor dx, dbias;
-        gelu_bwd(s[0], s[1], grad[0].contiguous(), dx, dbias);
+        gelu_bwd(s[0], s[1], dy, dx, dbias);
         return {dx.view(ctx->saved_data["shape"].toIntVector()), dbias};
     }
 };
@@ -273,6 +303,7 @@ struct BiasGeluLinear : torch::autograd::Function<BiasGeluLinear> {
         const Tensor out = out_bias ? at::addmm(*out_bias, y, weight.t()) : at::matmul(y, weight.t());
         ctx->save_for_backward({x, bias, weight});
         ctx->saved_data["shape"] = x_.sizes().vec();
+        ctx->saved_data["format"] = x.scalar_type();
         ctx->saved_data["has_out_bias"] = out_bias.has_value();
         std::vector<int64_t> shape = x_.sizes().vec();
         shape.back() = weight.size(0);
@@ -282,14 +313,18 @@ struct BiasGeluLinear : torch::autograd::Function<BiasGeluLinear> {
     {
         const variable_list s = ctx->get_saved_variables();
         const Tensor &x = s[0], &bias = s[1], &weight = s[2];
-        const Tensor d2 = grad[0].contiguous().view({x.size(0), weight.size(0)});
+        const std::vector<int64_t> shape = ctx->saved_data["shape"].toIntVector();
+        const int64_t F = shape.back(), M = grad[0].numel() / grad[0].size(-1);
+        require(x, "x", {M, F}, ctx->saved_data["format"].toScalarType(), grad[0]);
+        require(bias.contiguous(), "bias", {F}, at::kFloat, grad[0]);
+        const Tensor d2 = grad[0].contiguous().view({M, weight.size(0)});
         Tensor y = gelu_fwd(x, bias, x.sizes());  // rebuilt, not kept
         const Tensor dweight = at::matmul(d2.t(), y);
         const Tensor dy = at::matmul(d2, weight);
         y.reset();
         Tensor dx, dbias;
         gelu_bwd(x, bias, dy.contiguous(), dx, dbias);
-        return {dx.view(ctx->saved_data["shape"].toIntVector()), dbias, dweight,
+        return {dx.view(shape), dbias, dweight,
                 ctx->saved_data["has_out_bias"].toBool() ? d2.sum(0) : Tensor()};
     }
 };
