@@ -322,8 +322,9 @@ struct BiasGeluLinear : torch::autograd::Function<BiasGeluLinear> {
         const Tensor dweight = at::matmul(d2.t(), y);
         const Tensor dy = at::matmul(d2, weight);
         y.reset();
+        require(dy, "dy", {M, F}, x.scalar_type(), grad[0]);  // under autocast a product comes in autocast's format
         Tensor dx, dbias;
-        gelu_bwd(x, bias, dy.contiguous(), dx, dbias);
+        gelu_bwd(x, bias, dy, dx, dbias);
         return {dx.view(shape), dbias, dweight,
                 ctx->saved_data["has_out_bias"].toBool() ? d2.sum(0) : Tensor()};
     }

@@ -159,6 +159,38 @@ def test_saved_tensors_that_a_hook_changed_are_refused_as_by_the_classes(name, k
     assert refused >= 1
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("inside", [False, True])
+@pytest.mark.parametrize("auto", ["float16", "bfloat16"])
+@pytest.mark.parametrize("own", ["float16", "bfloat16"])
+def test_products_under_autocast_behave_as_in_the_class(own, auto, inside):
+    # autocast may give the second product (or its gradient) another 16-bit format than the activation's
+    import torch
+    from paper_2309_16669_amd import autograd as ag
+    args = [a if a.dtype == torch.float32 else a.to(getattr(torch, own)) for a in _calls()["bias_gelu_linear"][2]]
+
+    def outcome(f):
+        leaves = [a.detach().requires_grad_() for a in args]
+        with torch.autocast("cuda", dtype=getattr(torch, auto)):
+            y = f(*leaves)
+            try:
+                if inside:
+                    return [y, *torch.autograd.grad(y, leaves, torch.ones_like(y))]
+            except (ValueError, RuntimeError) as e:
+                return type(e)
+        try:
+            return [y, *torch.autograd.grad(y, leaves, torch.ones_like(y))]
+        except (ValueError, RuntimeError) as e:
+            return type(e)
+
+    a, b = outcome(ag.bias_gelu_linear), outcome(ag._BiasGeluLinear.apply)
+    assert isinstance(a, list) == isinstance(b, list), (a, b)
+    if isinstance(a, list):
+        assert all(t.dtype == u.dtype and torch.equal(t, u) for t, u in zip(a, b))
+    else:
+        assert a is b
+
+
 def test_host_tensors_are_refused_as_before():
     import torch
     from paper_2309_16669_amd import autograd as ag
