@@ -84,6 +84,19 @@ void require(const Tensor& t, const char* name, at::IntArrayRef shape, at::Scala
     TORCH_CHECK_VALUE(t.sizes() == shape, name, " must have shape ", shape, ", got ", t.sizes());
 }
 
+// Runs a call without the interpreter lock, as torch's own functions and ctypes do: an allocation that goes to the
+// driver or a launch that waits for room in the queue stops this thread only.  The caller's frame holds the arguments.
+template <typename F>
+pybind11::object without_lock(F call)
+{
+    Tensor out;
+    {
+        pybind11::gil_scoped_release release;
+        out = call();
+    }
+    return pybind11::cast(out);
+}
+
 Tensor workspace(size_t bytes, const Tensor& like) { return at::empty({(int64_t)bytes}, like.options().dtype(at::kByte)); }
 
 // ------------------------------------------------------------------------------------- attention
@@ -193,7 +206,7 @@ pybind11::object attention(pybind11::handle q_, pybind11::handle k_, pybind11::h
     if (q->dim() != 4 || !element_format(*q) || !fits_int(*q)) return pybind11::none();
     for (const Tensor* t : {k, v})
         if (t->scalar_type() != q->scalar_type() || t->sizes() != q->sizes() || t->device() != q->device()) return pybind11::none();
-    return pybind11::cast(Attention::apply(*q, *k, *v, scale, causal));
+    return without_lock([&] { return Attention::apply(*q, *k, *v, scale, causal); });
     END_HANDLE_TH_ERRORS_PYBIND
 }
 pybind11::object attention_qkvpacked(pybind11::handle qkv_, double scale, bool causal)
@@ -202,7 +215,7 @@ pybind11::object attention_qkvpacked(pybind11::handle qkv_, double scale, bool c
     const Tensor* qkv;
     if (!plain(qkv_.ptr(), &qkv) || !plain_thread()) return pybind11::none();
     if (qkv->dim() != 5 || qkv->size(2) != 3 || !element_format(*qkv) || !fits_int(*qkv)) return pybind11::none();
-    return pybind11::cast(AttentionPacked::apply(*qkv, scale, causal));
+    return without_lock([&] { return AttentionPacked::apply(*qkv, scale, causal); });
     END_HANDLE_TH_ERRORS_PYBIND
 }
 
@@ -248,7 +261,7 @@ pybind11::object layer_norm(pybind11::handle x_, pybind11::handle gamma_, pybind
     if (x->dim() < 1 || !element_format(*x) || x->size(-1) > INT32_MAX) return pybind11::none();
     if (!parameter(gamma_.ptr(), x->size(-1), *x, &gamma) || !parameter(beta_.ptr(), x->size(-1), *x, &beta))
         return pybind11::none();
-    return pybind11::cast(LayerNorm::apply(*x, *gamma, *beta, eps));
+    return without_lock([&] { return LayerNorm::apply(*x, *gamma, *beta, eps); });
     END_HANDLE_TH_ERRORS_PYBIND
 }
 
@@ -339,7 +352,7 @@ pybind11::object bias_gelu(pybind11::handle x_, pybind11::handle bias_)
     HANDLE_TH_ERRORS
     const Tensor *x, *bias;
     if (!gelu_args(x_, bias_, &x, &bias)) return pybind11::none();
-    return pybind11::cast(BiasGelu::apply(*x, *bias));
+    return without_lock([&] { return BiasGelu::apply(*x, *bias); });
     END_HANDLE_TH_ERRORS_PYBIND
 }
 pybind11::object bias_gelu_linear(pybind11::handle x_, pybind11::handle bias_, pybind11::handle weight_, pybind11::handle out_)
@@ -355,7 +368,7 @@ pybind11::object bias_gelu_linear(pybind11::handle x_, pybind11::handle bias_, p
             out->scalar_type() != x->scalar_type() || out->device() != x->device())
             return pybind11::none();
     }
-    return pybind11::cast(BiasGeluLinear::apply(*x, *bias, *weight, out ? std::optional<Tensor>(*out) : std::nullopt));
+    return without_lock([&] { return BiasGeluLinear::apply(*x, *bias, *weight, out ? std::optional<Tensor>(*out) : std::nullopt); });
     END_HANDLE_TH_ERRORS_PYBIND
 }
 

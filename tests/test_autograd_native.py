@@ -191,6 +191,34 @@ def test_products_under_autocast_behave_as_in_the_class(own, auto, inside):
         assert a is b
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ["attention", "qkvpacked", "layer_norm", "bias_gelu", "bias_gelu_linear"])
+def test_other_threads_run_during_a_call(name):
+    # with a switch interval longer than the test another thread runs only when a call gives up the interpreter lock
+    # (the outputs are kept: freeing a tensor gives it up too)
+    import sys
+    import threading
+    import torch
+    front, _, args, rest = _calls()[name]
+    with torch.no_grad():
+        front(*args, *rest)
+        go, ran, kept, interval = threading.Event(), [], [], sys.getswitchinterval()
+        other = threading.Thread(target=lambda: (go.wait(), ran.append(True)))
+        other.start()
+        try:
+            sys.setswitchinterval(1000)
+            go.set()
+            for _ in range(2000):
+                kept.append(front(*args, *rest))
+                if ran:
+                    break
+            seen = bool(ran)
+        finally:
+            sys.setswitchinterval(interval)
+            other.join()
+    assert seen
+
+
 def test_host_tensors_are_refused_as_before():
     import torch
     from paper_2309_16669_amd import autograd as ag
