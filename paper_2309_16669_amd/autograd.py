@@ -24,6 +24,8 @@ entry points the same way (what they keep for the backward is stated in their do
 from __future__ import annotations
 
 import math
+import types
+import warnings
 
 import torch
 
@@ -34,15 +36,18 @@ _native = None
 
 
 def native_calls():
-    """The module of native calls; raises if it has not been built."""
+    """The module of native calls.  Where it is not built or does not load (another torch than it was built with) a
+    stand-in that declines every call, with a warning: the classes below then serve them all."""
     global _native
     if _native is None:
         load_library()
         try:
             from . import _avion_torch
         except ImportError as e:
-            raise ImportError("paper_2309_16669_amd/_avion_torch.so is missing or does not load: build it first "
-                              "(python -c 'import __graft_entry__ as g; g.build()')") from e
+            warnings.warn(f"paper_2309_16669_amd/_avion_torch.so does not load ({e}); the Python classes take its calls, at "
+                          "several times the host time.  Build it: python -c 'import __graft_entry__ as g; g.build()'")
+            names = ("attention", "attention_qkvpacked", "layer_norm", "bias_gelu", "bias_gelu_linear")
+            _avion_torch = types.SimpleNamespace(**{n: lambda *args: None for n in names})
         _native = _avion_torch
     return _native
 

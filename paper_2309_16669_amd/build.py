@@ -32,10 +32,10 @@ def headers():
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
-        return True
-    t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(p) > t for p in sources() + headers())
+    def older(built, made_from):
+        return not os.path.exists(built) or any(os.path.getmtime(p) > os.path.getmtime(built) for p in made_from)
+    return (older(LIB, sources() + headers()) or
+            older(TORCH_MODULE, [os.path.join(CSRC, "avion_torch.cpp"), os.path.join(ROOT, "include", "avion_attn.h")]))
 
 
 def build_library(verbose: bool = False, extra_flags=()) -> str:

@@ -227,3 +227,37 @@ def test_host_tensors_are_refused_as_before():
         ag.attention(q, q, q)
     with pytest.raises(ValueError):
         ag.layer_norm(q, torch.ones(64), torch.zeros(64))
+
+
+def test_a_tree_without_the_native_module_serves_every_call(monkeypatch):
+    # only the HIP library is needed; the classes answer (here: refuse host tensors), after a warning
+    import sys
+    import torch
+    import paper_2309_16669_amd as av
+    from paper_2309_16669_amd import autograd as ag
+    monkeypatch.setattr(ag, "_native", None)
+    monkeypatch.delattr(av, "_avion_torch", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2309_16669_amd._avion_torch", None)
+    q = torch.zeros(1, 40, 2, 64, dtype=torch.bfloat16)
+    w, b = torch.ones(64), torch.ones(64, 64, dtype=torch.bfloat16)
+    with pytest.warns(UserWarning, match="_avion_torch"):
+        with pytest.raises(ValueError):
+            ag.attention(q, q, q)
+    for call in (lambda: ag.attention_qkvpacked(torch.stack([q] * 3, 2)), lambda: ag.layer_norm(q, w, w),
+                 lambda: ag.bias_gelu(q, w), lambda: ag.bias_gelu_linear(q, w, b)):
+        with pytest.raises(ValueError):
+            call()
+
+
+def test_a_missing_or_old_module_is_stale(monkeypatch, tmp_path):
+    import os
+    from paper_2309_16669_amd import build
+    lib, module = tmp_path / "lib.so", tmp_path / "module.so"
+    lib.touch()
+    monkeypatch.setattr(build, "LIB", str(lib))
+    monkeypatch.setattr(build, "TORCH_MODULE", str(module))
+    assert build.is_stale()
+    module.touch()
+    assert not build.is_stale()
+    os.utime(module, (0, 0))
+    assert build.is_stale()
