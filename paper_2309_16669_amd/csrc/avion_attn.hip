@@ -387,7 +387,8 @@ int dq_impl(const void* q, const void* k, const void* v, const void* o, const fl
     const raw16 *qq = static_cast<const raw16*>(q), *kk = static_cast<const raw16*>(k), *vv = static_cast<const raw16*>(v),
                *oo = static_cast<const raw16*>(o), *gg = static_cast<const raw16*>(dO);
     raw16* dqq = static_cast<raw16*>(dq);
-    // the lengths of the head kernel: only avion_attn_bwd_dq comes here with them (bf16, no mask, not packed)
+    // the lengths of the head kernel: avion_attn_bwd_dq alone comes here with them, and only its form is built
+    if (by_head(N, d) && (var.f16 || var.causal)) return AVION_EUNSUPPORTED;
     if (by_head(N, d)) return launch_dq<64, 4, 1, Bf16, false, true>(qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
     return by_split((long long)B * H, N, split_tiles(d), [&](auto nw, auto kg) {
         return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
