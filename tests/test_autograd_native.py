@@ -219,6 +219,76 @@ def test_other_threads_run_during_a_call(name):
     assert seen
 
 
+PLAIN = ["attention_f16_causal", "qkvpacked", "layer_norm", "bias_gelu"]
+
+
+def _one_pass(front, leaves, rest, dy):
+    import torch
+    y = front(*leaves, *rest)
+    return [y.detach(), *torch.autograd.grad(y, leaves, dy)]
+
+
+@pytest.mark.gpu
+def test_threads_with_a_stream_each_do_not_disturb_each_other():
+    # workspaces and outputs come from the allocator on each thread's stream, the backward runs on it too
+    import threading
+    import torch
+    calls, jobs = _calls(), []
+    for name in PLAIN:
+        front, _, args, rest = calls[name]
+        leaves = [a.detach().requires_grad_() for a in args]
+        dy = torch.randn_like(front(*leaves, *rest))
+        jobs.append((front, leaves, rest, dy, _one_pass(front, leaves, rest, dy)))
+    torch.cuda.synchronize()
+    got = [[] for _ in jobs]
+
+    def work(i):
+        front, leaves, rest, dy, _ = jobs[i]
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(20):
+                got[i].append(_one_pass(front, leaves, rest, dy))
+            torch.cuda.current_stream().synchronize()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(jobs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for (*_, ref), outs in zip(jobs, got):
+        assert len(outs) == 20
+        for out in outs:
+            assert all(torch.equal(a, b) for a, b in zip(ref, out))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", PLAIN)
+def test_forward_and_backward_can_be_captured_and_replayed(name):
+    import torch
+    front, _, args, rest = _calls()[name]
+    leaves = [a.detach().clone().requires_grad_() for a in args]
+    inputs = [[torch.randn_like(a) for a in args] for _ in range(3)]
+    dy = torch.randn_like(front(*leaves, *rest))
+    refs = [_one_pass(front, [t.clone().requires_grad_() for t in x], rest, dy) for x in inputs]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        _one_pass(front, leaves, rest, dy)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = _one_pass(front, leaves, rest, dy)
+    for i in (0, 1, 2, 1):
+        with torch.no_grad():
+            for leaf, t in zip(leaves, inputs[i]):
+                leaf.copy_(t)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(refs[i], out)), i
+        _one_pass(front, [t.clone().requires_grad_() for t in inputs[(i + 1) % 3]], rest, dy)    # eager work in between
+
+
 def test_host_tensors_are_refused_as_before():
     import torch
     from paper_2309_16669_amd import autograd as ag

@@ -130,7 +130,8 @@ def test_full_size_configs_on_sampled_heads(name):
     assert np.sqrt(((dv_sum - do_sum) ** 2).sum() / (do_sum ** 2).sum()) <= 2e-3
 
 
-@pytest.mark.parametrize("shape", [(2, 3, 700, 64), (1, 4, 1568, 64), (2, 2, 300, 80)])
+# small launches, whose workgroups hold several groups of wavefronts, and launches beyond that (one group, as at full size)
+@pytest.mark.parametrize("shape", [(2, 3, 700, 64), (1, 4, 1568, 64), (2, 2, 300, 80), (2, 45, 321, 64), (2, 43, 321, 80)])
 def test_bitwise_reproducible(shape):
     # no atomics and no order-dependent reductions: repeated runs agree bit for bit (this is also
     # what exposes a tile that is read before it has completely arrived)
@@ -379,12 +380,13 @@ def test_largest_addressable_head_slice():
                                             B, H, N + 64, d, ctypes.c_float(0.125), None) == av.EUNSUPPORTED
 
 
-def test_two_streams_with_their_own_workspaces_do_not_disturb_each_other():
+@pytest.mark.parametrize("shapes", [((2, 4, 700, 64), (1, 6, 1100, 64)), ((3, 30, 321, 64), (2, 48, 400, 64))])
+def test_two_streams_with_their_own_workspaces_do_not_disturb_each_other(shapes):
     # calls only enqueue on the caller's stream: two problems in flight on two streams, each with its
     # own workspace, give the same bits as when run one after the other on the default stream
     import torch
     import paper_2309_16669_amd as av
-    ws_ = [si.small_workload(2, 4, 700, 64, seed=91), si.small_workload(1, 6, 1100, 64, seed=92)]
+    ws_ = [si.small_workload(*s, seed=91 + i) for i, s in enumerate(shapes)]
     xs = [si.make_inputs(w) for w in ws_]
     ref = [gh.run_hip(w, x) for w, x in zip(ws_, xs)]
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
@@ -451,8 +453,8 @@ def test_autograd_front_end_matches_oracle_gradients():
 
 @pytest.mark.parametrize("B,H,N,d", [(3, 5, 100, 64), (2, 2, 128, 64), (2, 3, 77, 80), (1, 2, 129, 64)])
 def test_whole_backward_equals_its_two_phases(B, H, N, d):
-    # avion_attn_bwd runs short sequences (N <= 128) as one launch and longer ones as two; either way
-    # it must give the bits of avion_attn_bwd_dq followed by avion_attn_bwd_dkdv
+    # avion_attn_bwd runs short sequences (N <= 256 at d = 64, <= 128 at 80) as one launch and longer ones as two;
+    # either way it must give the bits of avion_attn_bwd_dq followed by avion_attn_bwd_dkdv
     import torch
     import paper_2309_16669_amd as av
     w = si.small_workload(B, H, N, d, seed=5150 + N)

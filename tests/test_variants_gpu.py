@@ -126,11 +126,19 @@ def test_autograd_front_end_covers_the_combinations():
     (o.float() * _upload(x["dO"], False).float()).sum().backward()
     check(w, x, dict(o=o.detach(), lse=_lse_of(w, x, False, True), dq=qkv.grad[:, :, 0], dk=qkv.grad[:, :, 1],
                      dv=qkv.grad[:, :, 2]), False, True)
-    # the workspace of the backward is kept per (device, stream): a second backward allocates none
-    before = dict(ag._workspaces)
+    # the classes keep the workspace of the backward per (device, stream): a second backward of theirs allocates none
     q2, k2, v2 = (_upload(x[n], False).requires_grad_() for n in ("q", "k", "v"))
-    ag.attention(q2, k2, v2, w.scale).float().sum().backward()
-    assert {k_: v_.data_ptr() for k_, v_ in ag._workspaces.items()} == {k_: v_.data_ptr() for k_, v_ in before.items()}
+    ag._Attention.apply(q2, k2, v2, w.scale, False).float().sum().backward()
+    before = {k_: v_.data_ptr() for k_, v_ in ag._workspaces.items()}
+    assert (q2.device, torch.cuda.current_stream().cuda_stream) in before
+    ag._Attention.apply(q2, k2, v2, w.scale, False).float().sum().backward()
+    assert {k_: v_.data_ptr() for k_, v_ in ag._workspaces.items()} == before
+    # the native calls take theirs from torch's allocator and keep none
+    held = torch.cuda.memory_allocated()
+    for _ in range(2):
+        g = torch.autograd.grad(ag.attention(q2, k2, v2, w.scale).float().sum(), [q2, k2, v2])
+        del g
+    assert torch.cuda.memory_allocated() == held
 
 
 def _lse_of(w, x, f16, causal):
@@ -157,6 +165,40 @@ def test_launches_split_into_groups_match_the_oracle(B, H, N, d, f16, causal):
     w = si.small_workload(B, H, N, d, seed=9300 + N + d)
     x = si.make_inputs(w, fmt="f16" if f16 else "bf16")
     check(w, x, run_ex(w, x, f16, causal, False), f16, causal)
+
+
+# The same kernels with one group per workgroup, as every full-size launch runs them: at least 257 blocks of 128 rows.
+@pytest.mark.parametrize("B,H,N,d,f16,causal,packed", [
+    (2, 43, 321, 80, False, True, False), (2, 43, 321, 80, True, True, True), (1, 86, 321, 80, False, False, True),
+    (2, 43, 321, 64, True, True, False), (1, 86, 321, 64, False, False, True)])
+def test_launches_of_one_group_match_the_oracle(B, H, N, d, f16, causal, packed):
+    w = si.small_workload(B, H, N, d, seed=9350 + N + d)
+    x = si.make_inputs(w, fmt="f16" if f16 else "bf16")
+    check(w, x, run_ex(w, x, f16, causal, packed), f16, causal)
+
+
+# The running-maximum fallback of the forward in launches of one group (130 heads x 2 blocks).  Keys from 64 on are 16
+# (fp16: 4) times larger and scale = 1, so later scores overflow the fixed reference by far.  Bounds: one unit in the last
+# place of the largest reference value for O (near one-hot rows), fp32 rounding of LSE at its magnitude.
+@pytest.mark.parametrize("d", [64, 80])
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("causal", [False, True])
+def test_the_running_maximum_fallback_in_launches_of_one_group(d, f16, causal):
+    import oracle
+    import torch
+    import paper_2309_16669_amd as av
+    w = si.small_workload(10, 13, 200, d, seed=9370 + d, scale=1.0)
+    x = si.make_inputs(w, fmt="f16" if f16 else "bf16")
+    widen, narrow = (si.f16_bits_to_f64, si.f32_to_f16_bits) if f16 else (si.bf16_bits_to_f64, si.f32_to_bf16_bits)
+    x["k"][:, 64:] = narrow((widen(x["k"][:, 64:]) * (4 if f16 else 16)).astype(np.float32))     # exact: powers of two
+    q, k, v = (_upload(x[n], f16) for n in ("q", "k", "v"))
+    o = torch.full_like(q, float("nan"))
+    lse = torch.full((w.B, w.H, w.N), float("nan"), dtype=torch.float32, device="cuda")
+    av.attn_fwd_ex(q, k, v, o, lse, w.scale, causal)
+    ro, rl = oracle.fwd_f64(*(widen(x[n]) for n in ("q", "k", "v")), w.scale, causal=causal)
+    og, lg = o.double().cpu().numpy(), lse.double().cpu().numpy()
+    assert np.all(np.isfinite(og)) and np.abs(og - ro).max() <= 2.0 ** (-10 if f16 else -7) * np.abs(ro).max()
+    assert np.abs(lg - rl).max() <= 2e-6 * np.abs(rl).max() + 1e-3
 
 
 @pytest.mark.parametrize("H,N,sink", [(2, 300, 250), (2, 300, 40), (17, 1025, 1000)])
