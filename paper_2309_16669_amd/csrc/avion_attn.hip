@@ -263,7 +263,7 @@ int launch_win_bwd(const raw16* q, const raw16* k, const raw16* v, const raw16* 
     return end_launch("launch avion_win_bwd_kernel");
 }
 
-// Kernel instances: four wavefronts per workgroup for every kernel, head size, format and masking.
+// Kernel instances by head size, format and masking (wavefronts per workgroup: by_split and head_impl below).
 // by_variant calls f(head dim, element format, causal) with the three as compile-time tags, by_format
 // f(element format, causal).
 template <typename T>
@@ -298,9 +298,9 @@ int by_variant(Variant var, int d, F f)
 //                           walk gains); four groups from 16 tiles on, in the forward at d = 64 (registers
 //                           of the backward and LDS at d = 80 allow two)
 //   64 rows, 2 groups       when even 64-row blocks do
-// Measured, us, one group -> this rule (forward; whole backward): 12 heads x 1568 30.2 -> 22.4; 65 -> 53,
-// 32 x 785 17.4 -> 15.1; 39.4 -> 34.9, 16 x 785 backward 37 -> 27, 16 x 500 11.9 -> 9.2, 8 x 200 7.9 -> 6.9;
-// 16.9 -> 14.5, 12 x 785 (d = 80) 19.9 -> 15.6; 47 -> 36.  On the other side of the lines two groups lose:
+// Measured, us, one group -> this rule (forward; whole backward): 12 heads x 1568 30.4 -> 21.3; 65 -> 52,
+// 32 x 785 16.9 -> 14.8; 39 -> 35, 16 x 785 backward 37 -> 28, 16 x 500 11.7 -> 8.8, 8 x 200 forward 7.9 -> 6.9,
+// 12 x 785 (d = 80) 20.1 -> 14.3; 48 -> 35.  On the other side of the lines two groups lose:
 // 24 x 1568 85 -> 99 (backward), 64 x 785 22.4 -> 22.4; 53 -> 60, 64 x 300 21.0 -> 21.2, 240 x 77 6.5 -> 6.9.
 // `min_tiles`: the backward's two phases keep one group where the whole backward is one launch, whose bits
 // they give: up to 256 tokens at 64 channels, 128 at 80.
@@ -348,7 +348,7 @@ bool workspace_ok(const void* workspace, size_t workspace_bytes, int B, int H, i
 }
 
 // Whole heads per workgroup (avion_head.h): what its LDS holds at 64 channels (at 80 three tiles of 256 rows
-// take 160 KB), above the window kernels' lengths.  Both sides' times stand there.
+// take 160 KB), above the window kernels' lengths, whatever the number of heads.  Both sides' times stand there.
 constexpr int kHeadMaxN = 256;
 bool by_head(int N, int d) { return d == 64 && N > kWindowMaxN && N <= kHeadMaxN; }
 

@@ -407,8 +407,8 @@ avion_dkdv_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, cons
 
 // ------------------------------------------------------------------------- whole backward, short sequences
 // (d = 80; at 64 channels avion_head.h takes these lengths.)  For N <= 32*NW one workgroup covers all
-// queries and all keys of a (batch, head): the two passes then run back to back inside one workgroup, so that the second pass finds Q, K, V and dO in the
-// L2 where the first one has just pulled them (launched separately it would fetch them from HBM
+// queries and all keys of a (batch, head): the two passes then run back to back inside one workgroup, so
+// that the second pass finds Q, K, V and dO in the L2 where the first one has just pulled them (launched separately it would fetch them from HBM
 // again), and one launch is saved.  Same arithmetic, same bits as the two kernels.  The per-query
 // scalars still travel through the workspace: a workgroup-scope fence makes the first pass's stores visible
 // before the second pass's tile mover reads them, the barrier also frees the LDS the first pass

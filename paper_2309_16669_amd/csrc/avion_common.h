@@ -2,7 +2,8 @@
 //
 // Register and LDS layouts used throughout
 // ----------------------------------------
-// All contractions use v_mfma_f32_32x32x16_bf16 or _f16 (one wavefront, 32x32 output tile, 16 deep):
+// Contractions use v_mfma_f32_32x32x16_bf16 or _f16 (one wavefront, 32x32 output tile, 16 deep; dQ also in 16 x 16
+// tiles, whose layout stands at tr16_frag):
 //   A operand (32 x 16): lane l holds row  l%32, contraction slots 8*(l/32) .. 8*(l/32)+7
 //   B operand (16 x 32): lane l holds col  l%32, contraction slots 8*(l/32) .. 8*(l/32)+7
 //   accumulator (32x32): lane l holds col  l%32; register v (0..15) holds row
@@ -161,6 +162,8 @@ DEVINL void wait_all_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 // front of the first contraction, and where that is inside the main loop so does a wait that also holds the
 // next tile's fetch.  Placed where the loads are waited for anyway.  Forward on 384 heads x 1568 305 -> 289 us,
 // 128 x 1568 (d = 80) 145 -> 133, 3072 x 196 88 -> 82; whole-head backward on 16384 x 77 325 -> 304.
+// In the two-kernel backward it gives 0.5 to 2 % on a full chip and costs up to 0.7 us where a launch is one short
+// wave of workgroups (64 x 257 causal 20.2 -> 20.9 us).
 template <int n>
 DEVINL void hold(frag8 (&f)[n])
 {
@@ -231,8 +234,9 @@ constexpr unsigned kOutOfRangeBase = 0x80000000u;
 // Global -> LDS without passing through registers (buffer_load_dwordx4 ... lds): the 16 bytes that
 // lane i fetches from byte offset `voff` of the buffer land at LDS address lds_addr + 16*i, so one
 // instruction fills 1 KB of LDS; lds_addr (it travels in M0) must be the same in all lanes.
-// Offsets beyond the buffer deposit zeros.  Completion is tracked by the vector-memory counter
-// (s_waitcnt vmcnt) for the fetch and by lgkmcnt for the write into LDS.
+// Offsets beyond the buffer deposit zeros.  A request counts in the vector-memory counter (s_waitcnt vmcnt) until
+// its bytes are in LDS, and in no other (measured: with one outstanding to cold memory, an LDS read and its wait for
+// lgkmcnt take 104 cycles, the wait for vmcnt 840 to 1150).
 // Written as inline assembly on purpose: told that an instruction writes LDS asynchronously, the
 // compiler makes every later LDS read wait for ALL outstanding loads, which would serialise the
 // prefetch; here the ordering is established by hand (vmcnt waits + workgroup barriers).
@@ -515,12 +519,10 @@ struct TileRing {
             load_to_lds16(RawBuffer(desc[j]), dst, past_end ? kOutOfRangeBase : voff[j] + (unsigned)ti * vstep[j]);
         }
     }
-    // Wait for all of this wavefront's requests, then meet the other wavefronts: after it every
-    // requested tile is in LDS, and every wavefront is past the code before the barrier.  An
-    // LDS-direct load counts in both counters -- vmcnt for the fetch, then lgkmcnt for the deposit
-    // into LDS, hence two waits in this order -- and only when both have drained is the data visible
-    // to other wavefronts.  (Plain
-    // instructions: to the compiler the loads above are opaque, so no fence would wait for them.)
+    // Wait for all of this wavefront's requests (vmcnt) and LDS accesses (lgkmcnt), then meet the other
+    // wavefronts: after it every requested tile is in LDS, and every wavefront is past the code, and the
+    // LDS reads, before the barrier.  (Plain instructions: to the compiler the loads above are opaque, so
+    // no fence would wait for them.)
     DEVINL static void landed_barrier()
     {
         asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");

@@ -22,6 +22,12 @@
 // Measured, whole backward, us, two kernels -> this one: 3072 heads x 196 252 -> 191 (616 MB: 3.2 TB/s; one
 // head per workgroup 259), x 160 203 -> 144, x 256 298 -> 248, 8000 x 200 causal 583 -> 460; one launch of
 // two passes -> this one: 16384 x 77 causal 367 -> 304 (4.3 TB/s), 4000 x 128 143 -> 119, 8 x 77 10.5 -> 8.6.
+// Few heads (nothing is walked up to 256; 257..511 leave half the chip idle in the second round), two kernels
+// of one group each -> this one: 8 x 200 16.9 -> 15.3, 256 x 200 27.9 -> 19.5, 257 x 200 31.4 -> 30.1,
+// 384 x 200 36.7 -> 32.7, 8 x 256 17.7 -> 17.0, 257 x 256 36.1 -> 35.5; 0.60 to 0.99 of the two at 1 to 768
+// heads x 129..256, causal and not.  Two kernels of two groups each (by_split's form for at most 256 64-row
+// blocks) are slower than this one up to 192 tokens and from 96 heads on, and faster below that: by 0 to 4 %
+// at 196..224 tokens, 8 to 14 % at 240..256.
 // dQ in 32 x 32 tiles after every fourth block (fewer barriers, longer chains): 226 at 3072 x 196.
 #pragma once
 #include "avion_common.h"
