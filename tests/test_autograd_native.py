@@ -208,7 +208,7 @@ def test_other_threads_run_during_a_call(name):
         try:
             sys.setswitchinterval(1000)
             go.set()
-            for _ in range(2000):
+            for _ in range(10000):
                 kept.append(front(*args, *rest))
                 if ran:
                     break
