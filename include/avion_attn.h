@@ -268,6 +268,25 @@ int avion_bias_gelu_bwd(const void *x, const float *bias, const void *dy, void *
                         void *workspace, size_t workspace_bytes, void *stream);
 
 /*
+ * The same backward that also writes y = GELU(x + bias), the input of the MLP's second matrix product, whose
+ * weight gradient needs it again: one pass over x instead of this and one more avion_bias_gelu_fwd.  Same bits as
+ * the two.  dx may be dy (then overwritten); y [M, F] may not alias anything.
+ */
+int avion_bias_gelu_bwd_y(const void *x, const float *bias, const void *dy, void *dx, void *y, float *dbias,
+                          long long M, int F, unsigned flags,
+                          void *workspace, size_t workspace_bytes, void *stream);
+
+/*
+ * Column sums of x [M, F] (bf16, fp16 with AVION_FLAG_F16) into sum [F] of the same format: the gradient of a bias
+ * added to every row.  fp32 arithmetic, one rounding, fixed order of additions.  F % 8 == 0, F <= 65536; pointers
+ * 16-byte aligned; workspace 256-byte aligned, avion_column_sum_workspace_bytes(M, F) bytes.
+ */
+size_t avion_column_sum_workspace_bytes(long long M, int F);
+
+int avion_column_sum(const void *x, void *sum, long long M, int F, unsigned flags,
+                     void *workspace, size_t workspace_bytes, void *stream);
+
+/*
  * Allocation-free backward, for callers that cannot provide device scratch of their own: code
  * under HIP graph capture, tight serving or training loops, harnesses that forbid hipMalloc.
  * Same operation, arguments, rules and bits as avion_attn_bwd (bf16, not causal), without the

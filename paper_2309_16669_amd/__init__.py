@@ -82,6 +82,12 @@ def load_library() -> ctypes.CDLL:
         lib.avion_bias_gelu_bwd_workspace_bytes.argtypes = [ll, i]
         lib.avion_bias_gelu_bwd.restype = i
         lib.avion_bias_gelu_bwd.argtypes = [p, p, p, p, p, ll, i, u, p, sz, p]
+        lib.avion_bias_gelu_bwd_y.restype = i
+        lib.avion_bias_gelu_bwd_y.argtypes = [p, p, p, p, p, p, ll, i, u, p, sz, p]
+        lib.avion_column_sum_workspace_bytes.restype = sz
+        lib.avion_column_sum_workspace_bytes.argtypes = [ll, i]
+        lib.avion_column_sum.restype = i
+        lib.avion_column_sum.argtypes = [p, p, ll, i, u, p, sz, p]
         lib.avion_attn_bwd_noalloc.restype = i
         lib.avion_attn_bwd_noalloc.argtypes = [p, p, p, p, p, p, p, p, p, i, i, i, i, f, p]
         _lib = lib
@@ -369,3 +375,32 @@ def bias_gelu_bwd(x, bias, dy, dx, dbias, workspace, stream=None) -> None:
     _check(load_library().avion_bias_gelu_bwd(_ptr(x), _ptr(bias), _ptr(dy), _ptr(dx), _ptr(dbias), M, F,
                                               _flags(x.dtype, False, False), _ptr(workspace), workspace.numel(),
                                               _stream_handle(stream)))
+
+
+def bias_gelu_bwd_y(x, bias, dy, dx, y, dbias, workspace, stream=None) -> None:
+    """avion_bias_gelu_bwd_y: bias_gelu_bwd that also writes y = GELU(x + bias); dx may be dy."""
+    import torch
+    M, F = x.shape
+    for t, n in ((x, "x"), (dy, "dy"), (dx, "dx"), (y, "y")):
+        _require(t, n, x.dtype, (M, F))
+    for t, n in ((bias, "bias"), (dbias, "dbias")):
+        _require(t, n, torch.float32, (F,))
+    _require(workspace, "workspace", torch.uint8)
+    _check(load_library().avion_bias_gelu_bwd_y(_ptr(x), _ptr(bias), _ptr(dy), _ptr(dx), _ptr(y), _ptr(dbias), M, F,
+                                                _flags(x.dtype, False, False), _ptr(workspace), workspace.numel(),
+                                                _stream_handle(stream)))
+
+
+def column_sum_workspace_bytes(M: int, F: int) -> int:
+    return int(load_library().avion_column_sum_workspace_bytes(M, F))
+
+
+def column_sum(x, out, workspace, stream=None) -> None:
+    """avion_column_sum: out [F] = sum over the rows of x [M, F], both bf16 or fp16."""
+    import torch
+    M, F = x.shape
+    _require(x, "x", x.dtype, (M, F))
+    _require(out, "out", x.dtype, (F,))
+    _require(workspace, "workspace", torch.uint8)
+    _check(load_library().avion_column_sum(_ptr(x), _ptr(out), M, F, _flags(x.dtype, False, False), _ptr(workspace),
+                                           workspace.numel(), _stream_handle(stream)))

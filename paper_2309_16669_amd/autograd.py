@@ -29,8 +29,8 @@ import warnings
 
 import torch
 
-from . import (attn_bwd_ex, attn_bwd_workspace_bytes, attn_fwd_ex, bias_gelu_bwd, bias_gelu_bwd_workspace_bytes, bias_gelu_fwd,
-               layernorm_bwd, layernorm_bwd_workspace_bytes, layernorm_fwd, load_library)
+from . import (attn_bwd_ex, attn_bwd_workspace_bytes, attn_fwd_ex, bias_gelu_bwd, bias_gelu_bwd_workspace_bytes, bias_gelu_bwd_y,
+               bias_gelu_fwd, column_sum, column_sum_workspace_bytes, layernorm_bwd, layernorm_bwd_workspace_bytes, layernorm_fwd, load_library)
 
 _native = None
 
@@ -157,9 +157,19 @@ class _BiasGelu(torch.autograd.Function):
         return dx.view(ctx.shape), dbias
 
 
+def _column_sum(d):
+    """d.sum(0); torch's where the rows are no multiple of 16 bytes."""
+    need = column_sum_workspace_bytes(*d.shape)
+    if need == 0 or d.data_ptr() % 16 != 0:
+        return d.sum(0)
+    out = torch.empty((d.shape[1],), dtype=d.dtype, device=d.device)
+    column_sum(d, out, _workspace_of(need, d.device))
+    return out
+
+
 class _BiasGeluLinear(torch.autograd.Function):
-    """linear(GELU(x + bias), weight, out_bias) that keeps x only: the activation's output is rebuilt in the
-    backward pass (one more avion_bias_gelu_fwd) for the weight gradient.  The two matrix products per
+    """linear(GELU(x + bias), weight, out_bias) that keeps x only: the activation's output is rebuilt by the
+    backward pass (avion_bias_gelu_bwd_y) for the weight gradient.  The two matrix products per
     direction are torch's (library GEMMs)."""
 
     @staticmethod
@@ -178,14 +188,10 @@ class _BiasGeluLinear(torch.autograd.Function):
         x2, bias, weight = ctx.saved_tensors
         M, F = x2.shape
         d2 = dout.contiguous().view(M, weight.shape[0])
-        y = torch.empty_like(x2)
-        bias_gelu_fwd(x2, bias.contiguous(), y)          # rebuilt, not kept
-        dweight = d2.t() @ y
-        dy = d2 @ weight
-        del y
-        dx, dbias = torch.empty_like(x2), torch.empty_like(bias)
-        bias_gelu_bwd(x2, bias.contiguous(), dy, dx, dbias, _workspace_of(bias_gelu_bwd_workspace_bytes(M, F), x2.device))
-        return dx.view(ctx.shape), dbias, dweight, (d2.sum(0) if ctx.has_out_bias else None)
+        dx = d2 @ weight                                 # with respect to the activation's output; then, in its place, to x
+        y, dbias = torch.empty_like(x2), torch.empty_like(bias)
+        bias_gelu_bwd_y(x2, bias.contiguous(), dx, dx, y, dbias, _workspace_of(bias_gelu_bwd_workspace_bytes(M, F), x2.device))
+        return dx.view(ctx.shape), dbias, d2.t() @ y, (_column_sum(d2) if ctx.has_out_bias else None)
 
 
 def bias_gelu_linear(x, bias, weight, out_bias=None):

@@ -528,6 +528,52 @@ GeluGrid gelu_grid(long long M, int F)
     return g;
 }
 
+template <bool WITH_Y>
+int gelu_bwd_impl(const void* x, const float* bias, const void* dy, void* dx, void* y, float* dbias, long long M, int F,
+                  unsigned flags, void* workspace, size_t workspace_bytes, void* stream)
+{
+    if (!x || !bias || !dy || !dx || !dbias) return AVION_EINVAL;
+    const int rc = gelu_check(M, F, flags);
+    if (rc != AVION_OK) return rc;
+    const void* ptrs[] = {x, bias, dy, dx, y, dbias};
+    for (const void* p : ptrs)
+        if (!aligned16(p)) return AVION_EUNSUPPORTED;
+    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 ||
+        workspace_bytes < avion_bias_gelu_bwd_workspace_bytes(M, F))
+        return AVION_EWORKSPACE;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    float* part = static_cast<float*>(workspace);
+    const GeluGrid g = gelu_grid(M, F);
+    const bool f16 = (flags & AVION_FLAG_F16) != 0, stream_past_cache = gelu_streams(M, F);
+    auto launch = [&](auto fmt, auto streaming) {
+        hipLaunchKernelGGL((avion_bias_gelu_bwd_kernel<typename decltype(fmt)::type, decltype(streaming)::value, WITH_Y>),
+                           dim3((unsigned)(g.ncb * g.nrg)), dim3(kGeluThreads), 0, st, static_cast<const raw16*>(x), bias,
+                           static_cast<const raw16*>(dy), static_cast<raw16*>(dx), static_cast<raw16*>(y), part, (long)M, F,
+                           g.ncb);
+    };
+    begin_launch();
+    if (f16 && stream_past_cache) launch(TypeTag<F16>{}, std::true_type{});
+    else if (f16) launch(TypeTag<F16>{}, std::false_type{});
+    else if (stream_past_cache) launch(TypeTag<Bf16>{}, std::true_type{});
+    else launch(TypeTag<Bf16>{}, std::false_type{});
+    const int r1 = end_launch("launch avion_bias_gelu_bwd_kernel");
+    if (r1 != AVION_OK) return r1;
+    // column sums of the row groups' partials: the reduction kernel splits its 2 * (F / 2) columns into two outputs
+    begin_launch();
+    hipLaunchKernelGGL((avion_ln_param_reduce_kernel<void>), dim3((F + kLnReduceCols - 1) / kLnReduceCols),
+                       dim3(kLnReduceCols * kLnReduceGroups), 0, st, part, dbias, dbias + F / 2, g.nrg, F / 2);
+    return end_launch("launch avion_ln_param_reduce_kernel");
+}
+// column sums: 256 columns a workgroup; row groups so that a thread has about kSumFly rows, at most 1024 workgroups
+GeluGrid sum_grid(long long M, int F)
+{
+    GeluGrid g;
+    g.ncb = (F + kSumCols - 1) / kSumCols;
+    const long long want = (M + kSumRows * kSumFly - 1) / (kSumRows * kSumFly), most = std::max(1, 1024 / g.ncb);
+    g.nrg = (int)std::min(want, most);
+    return g;
+}
+
 constexpr unsigned kAllFlags = AVION_FLAG_F16 | AVION_FLAG_CAUSAL | AVION_FLAG_QKVPACKED;
 
 // q, k, v planes of a packed [B, N, 3, H, d] tensor
@@ -741,7 +787,7 @@ int avion_layernorm_bwd(const void* x, const float* gamma, const float* mean, co
     });
     if (r1 != AVION_OK) return r1;
     begin_launch();
-    hipLaunchKernelGGL(avion_ln_param_reduce_kernel, dim3((2 * D + kLnReduceCols - 1) / kLnReduceCols),
+    hipLaunchKernelGGL((avion_ln_param_reduce_kernel<void>), dim3((2 * D + kLnReduceCols - 1) / kLnReduceCols),
                        dim3(kLnReduceCols * kLnReduceGroups), 0, st, part, dgamma, dbeta, (int)grid, D);
     return end_launch("launch avion_ln_param_reduce_kernel");
 }
@@ -778,36 +824,54 @@ int avion_bias_gelu_fwd(const void* x, const float* bias, void* y, long long M, 
 int avion_bias_gelu_bwd(const void* x, const float* bias, const void* dy, void* dx, float* dbias, long long M, int F,
                         unsigned flags, void* workspace, size_t workspace_bytes, void* stream)
 {
-    if (!x || !bias || !dy || !dx || !dbias) return AVION_EINVAL;
+    return gelu_bwd_impl<false>(x, bias, dy, dx, nullptr, dbias, M, F, flags, workspace, workspace_bytes, stream);
+}
+
+int avion_bias_gelu_bwd_y(const void* x, const float* bias, const void* dy, void* dx, void* y, float* dbias, long long M,
+                          int F, unsigned flags, void* workspace, size_t workspace_bytes, void* stream)
+{
+    if (!y) return AVION_EINVAL;
+    return gelu_bwd_impl<true>(x, bias, dy, dx, y, dbias, M, F, flags, workspace, workspace_bytes, stream);
+}
+
+size_t avion_column_sum_workspace_bytes(long long M, int F)
+{
+    if (gelu_check(M, F, 0) != AVION_OK) return 0;
+    const size_t bytes = (size_t)sum_grid(M, F).nrg * F * sizeof(float);
+    return (bytes + 255) & ~(size_t)255;
+}
+
+int avion_column_sum(const void* x, void* sum, long long M, int F, unsigned flags, void* workspace, size_t workspace_bytes,
+                     void* stream)
+{
+    if (!x || !sum) return AVION_EINVAL;
     const int rc = gelu_check(M, F, flags);
     if (rc != AVION_OK) return rc;
-    const void* ptrs[] = {x, bias, dy, dx, dbias};
-    for (const void* p : ptrs)
-        if (!aligned16(p)) return AVION_EUNSUPPORTED;
+    if (!aligned16(x) || !aligned16(sum)) return AVION_EUNSUPPORTED;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 ||
-        workspace_bytes < avion_bias_gelu_bwd_workspace_bytes(M, F))
+        workspace_bytes < avion_column_sum_workspace_bytes(M, F))
         return AVION_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     float* part = static_cast<float*>(workspace);
-    const GeluGrid g = gelu_grid(M, F);
-    const bool f16 = (flags & AVION_FLAG_F16) != 0, stream_past_cache = gelu_streams(M, F);
-    auto launch = [&](auto fmt, auto streaming) {
-        hipLaunchKernelGGL((avion_bias_gelu_bwd_kernel<typename decltype(fmt)::type, decltype(streaming)::value>),
-                           dim3((unsigned)(g.ncb * g.nrg)), dim3(kGeluThreads), 0, st, static_cast<const raw16*>(x), bias,
-                           static_cast<const raw16*>(dy), static_cast<raw16*>(dx), part, (long)M, F, g.ncb);
+    const GeluGrid g = sum_grid(M, F);
+    auto run = [&](auto fmt) {
+        using E = typename decltype(fmt)::type;
+        const dim3 grid((unsigned)(g.ncb * g.nrg)), block(kSumCols / 8 * kSumRows);
+        const raw16* in = static_cast<const raw16*>(x);
+        raw16* out = static_cast<raw16*>(sum);
+        begin_launch();
+        if (g.nrg == 1)
+            hipLaunchKernelGGL((avion_column_sum_kernel<E, true>), grid, block, 0, st, in, out, part, (long)M, F, g.ncb);
+        else
+            hipLaunchKernelGGL((avion_column_sum_kernel<E, false>), grid, block, 0, st, in, out, part, (long)M, F, g.ncb);
+        const int r1 = end_launch("launch avion_column_sum_kernel");
+        if (r1 != AVION_OK || g.nrg == 1) return r1;
+        begin_launch();
+        hipLaunchKernelGGL((avion_ln_param_reduce_kernel<E>), dim3((F + kLnReduceCols - 1) / kLnReduceCols),
+                           dim3(kLnReduceCols * kLnReduceGroups), 0, st, part, out, out + F / 2, g.nrg, F / 2);
+        return end_launch("launch avion_ln_param_reduce_kernel");
     };
-    begin_launch();
-    if (f16 && stream_past_cache) launch(TypeTag<F16>{}, std::true_type{});
-    else if (f16) launch(TypeTag<F16>{}, std::false_type{});
-    else if (stream_past_cache) launch(TypeTag<Bf16>{}, std::true_type{});
-    else launch(TypeTag<Bf16>{}, std::false_type{});
-    const int r1 = end_launch("launch avion_bias_gelu_bwd_kernel");
-    if (r1 != AVION_OK) return r1;
-    // column sums of the row groups' partials: the reduction kernel splits its 2 * (F / 2) columns into two outputs
-    begin_launch();
-    hipLaunchKernelGGL(avion_ln_param_reduce_kernel, dim3((F + kLnReduceCols - 1) / kLnReduceCols),
-                       dim3(kLnReduceCols * kLnReduceGroups), 0, st, part, dbias, dbias + F / 2, g.nrg, F / 2);
-    return end_launch("launch avion_ln_param_reduce_kernel");
+    return (flags & AVION_FLAG_F16) != 0 ? run(TypeTag<F16>{}) : run(TypeTag<Bf16>{});
 }
 
 }  // extern "C"

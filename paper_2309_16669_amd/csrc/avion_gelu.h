@@ -24,6 +24,7 @@
 // exponential and one reciprocal.
 #pragma once
 #include "avion_common.h"
+#include "avion_ln.h"
 
 constexpr int kGeluThreads = 128;     // threads per workgroup = 16-byte column chunks per workgroup
 constexpr int kGeluRows = 4;          // rows in flight per thread
@@ -99,11 +100,14 @@ avion_bias_gelu_fwd_kernel(const raw16* __restrict__ x, const float* __restrict_
     }
 }
 
-// dx, and this row group's partial sums of dbias into part[row group][F]
-template <typename E, bool STREAM>
+// dx, and this row group's partial sums of dbias into part[row group][F].  With WITH_Y also the activation's output,
+// which the second product's weight gradient needs: 8 bytes an element in one pass instead of 10 in two (a forward
+// and this): [12544, 3072] 31 + 55 -> 62 us with dx in dy's place, [50176, 3072] 124 + 190 -> 251.  dx may be dy: an
+// element is read and written by one thread.
+template <typename E, bool STREAM, bool WITH_Y>
 __global__ void __launch_bounds__(kGeluThreads)
-avion_bias_gelu_bwd_kernel(const raw16* __restrict__ x, const float* __restrict__ bias, const raw16* __restrict__ dy,
-                           raw16* __restrict__ dx, float* __restrict__ part, long M, int F, int ncb)
+avion_bias_gelu_bwd_kernel(const raw16* __restrict__ x, const float* __restrict__ bias, const raw16* dy, raw16* dx,
+                           raw16* __restrict__ y, float* __restrict__ part, long M, int F, int ncb)
 {
     const int cb = blockIdx.x % ncb;
     const long rg = blockIdx.x / ncb, nrg = gridDim.x / ncb;
@@ -129,7 +133,7 @@ avion_bias_gelu_bwd_kernel(const raw16* __restrict__ x, const float* __restrict_
         for (int k = 0; k < kGeluRows; ++k) {
             const long row = r + k * nrg;
             if (row < M) {
-                float o[8];
+                float o[8], act[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float h = E::widen(as_frag8(in[k]), e) + b[e];
@@ -137,14 +141,70 @@ avion_bias_gelu_bwd_kernel(const raw16* __restrict__ x, const float* __restrict_
                     gelu_terms(h, cdf, hpdf);
                     o[e] = E::widen(as_frag8(gin[k]), e) * (cdf + hpdf);
                     acc[e] += o[e];
+                    act[e] = h * cdf;
                 }
                 u32x4 w;
 #pragma unroll
                 for (int p = 0; p < 4; ++p) w[p] = E::pack(o[2 * p], o[2 * p + 1]);
                 gelu_store<STREAM>(dx + row * F + col, w);
+                if constexpr (WITH_Y) {
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) w[p] = E::pack(act[2 * p], act[2 * p + 1]);
+                    gelu_store<STREAM>(y + row * F + col, w);
+                }
             }
         }
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) part[rg * F + col + e] = acc[e];
+}
+
+// Column sums of a [M, F] tensor of 16-bit elements, in fp32, rounded once: the gradient of a bias that is added to
+// every row (the second product's).  A workgroup takes 256 columns (32 threads of 16 bytes) and every nrg-th group of
+// 8 rows; its 8 row lanes meet in LDS.  With one row group the sums leave as they are, otherwise as fp32 partials that
+// avion_ln_param_reduce_kernel adds in a fixed order.
+// Bound by memory where M is large, by two launches where it is small: calls of 12544 x 768 20.6 (torch's sum) -> 12.8 us,
+// 50176 x 768 34.8 -> 16.4, 12544 x 3072 29.5 -> 15.3; 77 x 512 5.4 -> 12 (both sides through Python).
+constexpr int kSumCols = 256, kSumRows = 8, kSumFly = 4;
+template <typename E, bool ONLY>
+__global__ void __launch_bounds__(kSumCols / 8 * kSumRows)
+avion_column_sum_kernel(const raw16* __restrict__ x, raw16* __restrict__ sum, float* __restrict__ part, long M, int F, int ncb)
+{
+    __shared__ __attribute__((aligned(16))) float sh[kSumRows - 1][kSumCols];
+    const int cb = blockIdx.x % ncb, c = threadIdx.x % (kSumCols / 8), lane_row = threadIdx.x / (kSumCols / 8);
+    const long rg = blockIdx.x / ncb, stride = gridDim.x / ncb * kSumRows;
+    const int col = cb * kSumCols + c * 8;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (col < F) {
+        for (long r = rg * kSumRows + lane_row; r < M; r += stride * kSumFly) {
+            u32x4 in[kSumFly];
+#pragma unroll
+            for (int k = 0; k < kSumFly; ++k) {
+                const long row = r + k * stride;
+                in[k] = row < M ? *reinterpret_cast<const u32x4*>(x + row * F + col) : u32x4{0u, 0u, 0u, 0u};
+            }
+#pragma unroll
+            for (int k = 0; k < kSumFly; ++k)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e] += E::widen(as_frag8(in[k]), e);
+        }
+    }
+    if (lane_row > 0) store8(&sh[lane_row - 1][c * 8], acc);
+    __syncthreads();
+    if (lane_row > 0 || col >= F) return;
+#pragma unroll
+    for (int i = 0; i < kSumRows - 1; ++i) {
+        float a[8];
+        load8(&sh[i][c * 8], a);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] += a[e];
+    }
+    if constexpr (ONLY) {
+        u32x4 w;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) w[p] = E::pack(acc[2 * p], acc[2 * p + 1]);
+        *reinterpret_cast<u32x4*>(sum + col) = w;
+    } else {
+        store8(part + rg * F + col, acc);
+    }
 }

@@ -265,8 +265,10 @@ avion_ln_bwd_kernel(const raw16* __restrict__ x, const float* __restrict__ gamma
 // wavefront by lane exchange, the wavefronts' through LDS.  64 columns per workgroup (a quarter of the
 // workgroups), four loads in flight -> this: 7.2 -> 4.8 us for 1024 x 1536, 9.6 -> 8.0 for 1365 x 3072.
 constexpr int kLnReduceCols = 16, kLnReduceGroups = 64;
+// E: element format of the result, void for fp32.
+template <typename E>
 __global__ void __launch_bounds__(kLnReduceCols * kLnReduceGroups)
-avion_ln_param_reduce_kernel(const float* __restrict__ part, float* __restrict__ dgamma, float* __restrict__ dbeta,
+avion_ln_param_reduce_kernel(const float* __restrict__ part, void* __restrict__ dgamma, void* __restrict__ dbeta,
                              int nparts, int D)
 {
     constexpr int WAVES = kLnReduceCols * kLnReduceGroups / 64, FLY = 8;
@@ -293,7 +295,9 @@ avion_ln_param_reduce_kernel(const float* __restrict__ part, float* __restrict__
         float t = sh[0][col];
 #pragma unroll
         for (int w = 1; w < WAVES; ++w) t += sh[w][col];
-        if (c < D) dgamma[c] = t;
-        else dbeta[c - D] = t;
+        void* out = c < D ? dgamma : dbeta;
+        const int at = c < D ? c : c - D;
+        if constexpr (std::is_void_v<E>) static_cast<float*>(out)[at] = t;
+        else static_cast<raw16*>(out)[at] = (raw16)E::pack(t, 0.f);
     }
 }

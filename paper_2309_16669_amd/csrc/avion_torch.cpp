@@ -284,6 +284,17 @@ void gelu_bwd(const Tensor& x, const Tensor& bias_, const Tensor& dy, Tensor& dx
                               x.size(0), (int)x.size(1), format_flag(x), ws.data_ptr(), need, stream()));
 }
 
+// d.sum(0); torch's where the rows are no multiple of 16 bytes
+Tensor column_sum(const Tensor& d)
+{
+    const int64_t M = d.size(0), F = d.size(1);
+    const size_t need = F <= INT32_MAX ? avion_column_sum_workspace_bytes(M, (int)F) : 0;
+    if (need == 0 || !element_format(d) || reinterpret_cast<uintptr_t>(d.data_ptr()) % 16 != 0) return d.sum(0);
+    const Tensor sum = at::empty({F}, d.options());
+    check(avion_column_sum(d.data_ptr(), sum.data_ptr(), M, (int)F, format_flag(d), workspace(need, d).data_ptr(), need, stream()));
+    return sum;
+}
+
 struct BiasGelu : torch::autograd::Function<BiasGelu> {
     static Tensor forward(AutogradContext* ctx, const Tensor& x_, const Tensor& bias)
     {
@@ -305,8 +316,8 @@ struct BiasGelu : torch::autograd::Function<BiasGelu> {
         return {dx.view(ctx->saved_data["shape"].toIntVector()), dbias};
     }
 };
-// linear(GELU(x + bias), weight, out_bias) that keeps x only: the activation's output is rebuilt in the
-// backward pass for the weight gradient.  The matrix products are torch's.
+// linear(GELU(x + bias), weight, out_bias) that keeps x only: the activation's output is rebuilt by the
+// backward pass, beside dx, for the weight gradient.  The matrix products are torch's.
 struct BiasGeluLinear : torch::autograd::Function<BiasGeluLinear> {
     static Tensor forward(AutogradContext* ctx, const Tensor& x_, const Tensor& bias, const Tensor& weight,
                           const std::optional<Tensor>& out_bias)
@@ -331,15 +342,15 @@ struct BiasGeluLinear : torch::autograd::Function<BiasGeluLinear> {
         require(x, "x", {M, F}, ctx->saved_data["format"].toScalarType(), grad[0]);
         require(bias.contiguous(), "bias", {F}, at::kFloat, grad[0]);
         const Tensor d2 = grad[0].contiguous().view({M, weight.size(0)});
-        Tensor y = gelu_fwd(x, bias, x.sizes());  // rebuilt, not kept
-        const Tensor dweight = at::matmul(d2.t(), y);
         const Tensor dy = at::matmul(d2, weight);
-        y.reset();
         require(dy, "dy", {M, F}, x.scalar_type(), grad[0]);  // under autocast a product comes in autocast's format
-        Tensor dx, dbias;
-        gelu_bwd(x, bias, dy, dx, dbias);
-        return {dx.view(shape), dbias, dweight,
-                ctx->saved_data["has_out_bias"].toBool() ? d2.sum(0) : Tensor()};
+        // the gradient of x takes dy's place; y is rebuilt beside it, not kept
+        const Tensor b = bias.contiguous(), y = at::empty_like(x), dbias = at::empty_like(b);
+        const size_t need = avion_bias_gelu_bwd_workspace_bytes(M, (int)F);
+        check(avion_bias_gelu_bwd_y(x.data_ptr(), b.data_ptr<float>(), dy.data_ptr(), dy.data_ptr(), y.data_ptr(),
+                                    dbias.data_ptr<float>(), M, (int)F, format_flag(x), workspace(need, x).data_ptr(), need, stream()));
+        return {dy.view(shape), dbias, at::matmul(d2.t(), y),
+                ctx->saved_data["has_out_bias"].toBool() ? column_sum(d2) : Tensor()};
     }
 };
 bool gelu_args(pybind11::handle x_, pybind11::handle bias_, const Tensor** x, const Tensor** bias)

@@ -296,3 +296,43 @@ def test_layer_norm_and_bias_gelu_can_be_captured_in_a_graph_and_replayed():
             a, b = (v.view(torch.int16), refs[i][k].view(torch.int16)) if v.dtype == torch.bfloat16 else (v, refs[i][k])
             assert torch.equal(a, b), (i, k)
         run(ins[(i + 1) % 3], outputs())                      # unrelated eager work between replays
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("fmt", ["bf16", "f16"])
+@pytest.mark.parametrize("M,F", [(1, 8), (5, 1032), (77, 3072), (4099, 1024), (22016, 3072)])   # the last is streamed past the cache
+def test_backward_with_the_activation_gives_the_bits_of_the_two_calls(M, F, fmt, in_place):
+    import torch
+    import paper_2309_16669_amd as av
+    inp, ref = _run(M, F, 31, fmt)
+    dt = torch.float16 if fmt == "f16" else torch.bfloat16
+    up = lambda bits: torch.from_numpy(np.ascontiguousarray(bits).view(np.int16)).cuda().view(dt)
+    x, dy, bias = up(inp["x"]), up(inp["dy"]), torch.from_numpy(inp["bias"]).cuda()
+    y, dbias = torch.full_like(x, float("nan")), torch.full((F,), float("nan"), dtype=torch.float32, device="cuda")
+    dx = dy if in_place else torch.full_like(x, float("nan"))
+    ws = torch.empty(av.bias_gelu_bwd_workspace_bytes(M, F), dtype=torch.uint8, device="cuda")
+    av.bias_gelu_bwd_y(x, bias, dy, dx, y, dbias, ws)
+    torch.cuda.synchronize()
+    for a, b in ((y, ref["y"]), (dx, ref["dx"])):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    assert torch.equal(dbias, ref["dbias"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt", ["bf16", "f16"])
+# one row group up to 32 rows; ragged last column block, row group and 16-column piece of the reduction
+@pytest.mark.parametrize("M,F", [(1, 8), (8, 256), (32, 264), (33, 8), (65, 1000), (12545, 768), (40000, 2568)])
+def test_column_sums(M, F, fmt):
+    import torch
+    import paper_2309_16669_amd as av
+    dt, u = (torch.float16, 2.0 ** -11) if fmt == "f16" else (torch.bfloat16, 2.0 ** -8)
+    gen = torch.Generator(device="cuda").manual_seed(M + F)
+    x = torch.randn(M, F, device="cuda", generator=gen).to(dt)
+    out = torch.full((F,), float("nan"), dtype=dt, device="cuda")
+    ws = torch.full((av.column_sum_workspace_bytes(M, F),), 255, dtype=torch.uint8, device="cuda")
+    av.column_sum(x, out, ws)
+    ref, mag = x.double().sum(0), x.double().abs().sum(0)
+    # the rounding of the result, and of the fp32 additions: a sum passes at most M / 8 + 64 of them one after the other
+    bound = u * ref.abs() + (M / 8 + 64) * 2.0 ** -24 * mag + 1e-7
+    assert bool(((out.double() - ref).abs() <= bound).all())
