@@ -564,11 +564,14 @@ int gelu_bwd_impl(const void* x, const float* bias, const void* dy, void* dx, vo
                        dim3(kLnReduceCols * kLnReduceGroups), 0, st, part, dbias, dbias + F / 2, g.nrg, F / 2);
     return end_launch("launch avion_ln_param_reduce_kernel");
 }
-// column sums: 256 columns a workgroup; row groups so that a thread has about kSumFly rows, at most 1024 workgroups
+// column sums: 256 columns a workgroup; row groups so that a thread has about kSumFly rows, at most 1024 workgroups.
+// Up to kSumOneLaunch rows one row group, whose few more loads in a row cost less than the second launch.
 GeluGrid sum_grid(long long M, int F)
 {
     GeluGrid g;
     g.ncb = (F + kSumCols - 1) / kSumCols;
+    g.nrg = 1;
+    if (M <= kSumOneLaunch) return g;
     const long long want = (M + kSumRows * kSumFly - 1) / (kSumRows * kSumFly), most = std::max(1, 1024 / g.ncb);
     g.nrg = (int)std::min(want, most);
     return g;

@@ -165,7 +165,7 @@ avion_bias_gelu_bwd_kernel(const raw16* __restrict__ x, const float* __restrict_
 // avion_ln_param_reduce_kernel adds in a fixed order.
 // Bound by memory where M is large, by two launches where it is small: calls of 12544 x 768 20.6 (torch's sum) -> 12.8 us,
 // 50176 x 768 34.8 -> 16.4, 12544 x 3072 29.5 -> 15.3; 77 x 512 5.4 -> 12 (both sides through Python).
-constexpr int kSumCols = 256, kSumRows = 8, kSumFly = 4;
+constexpr int kSumCols = 256, kSumRows = 8, kSumFly = 4, kSumOneLaunch = 256;
 template <typename E, bool ONLY>
 __global__ void __launch_bounds__(kSumCols / 8 * kSumRows)
 avion_column_sum_kernel(const raw16* __restrict__ x, raw16* __restrict__ sum, float* __restrict__ part, long M, int F, int ncb)

@@ -321,8 +321,8 @@ def test_backward_with_the_activation_gives_the_bits_of_the_two_calls(M, F, fmt,
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("fmt", ["bf16", "f16"])
-# one row group up to 32 rows; ragged last column block, row group and 16-column piece of the reduction
-@pytest.mark.parametrize("M,F", [(1, 8), (8, 256), (32, 264), (33, 8), (65, 1000), (12545, 768), (40000, 2568)])
+# one row group up to 256 rows; ragged last column block, row group and 16-column piece of the reduction
+@pytest.mark.parametrize("M,F", [(1, 8), (8, 256), (32, 264), (256, 8), (257, 1000), (12545, 768), (40000, 2568)])
 def test_column_sums(M, F, fmt):
     import torch
     import paper_2309_16669_amd as av
