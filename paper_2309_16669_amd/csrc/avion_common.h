@@ -87,6 +87,12 @@ struct Bf16 {
         const v2 ones = {(__bf16)1.0f, (__bf16)1.0f};
         return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(v2, pair), ones, acc, false);
     }
+    // acc[0..3] + the four elements of two packed pairs, per lane: a 4 x 4 x 4 product with ones
+    DEVINL static f32x4 add_four(u32x2 x, f32x4 acc)
+    {
+        const s16x4 ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+        return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(s16x4, x), acc, 0, 0, 0);
+    }
     DEVINL static float widen(frag8 f, int e) { return (float)__builtin_bit_cast(v8, f)[e]; }
 };
 struct F16 {
@@ -112,6 +118,12 @@ struct F16 {
     {
         const v2 ones = {(_Float16)1.0f, (_Float16)1.0f};
         return __builtin_amdgcn_fdot2(__builtin_bit_cast(v2, pair), ones, acc, false);
+    }
+    DEVINL static f32x4 add_four(u32x2 x, f32x4 acc)
+    {
+        typedef __attribute__((ext_vector_type(4))) _Float16 v4;
+        const v4 ones = {(_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f};
+        return __builtin_amdgcn_mfma_f32_4x4x4f16(ones, __builtin_bit_cast(v4, x), acc, 0, 0, 0);
     }
     DEVINL static float widen(frag8 f, int e) { return (float)__builtin_bit_cast(v8, f)[e]; }
 };
