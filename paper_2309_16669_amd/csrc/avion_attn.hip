@@ -195,20 +195,20 @@ int launch_bwd_small(const raw16* q, const raw16* k, const raw16* v, const raw16
 }
 
 // Whole backward, one workgroup per head at a time (avion_head.h).
-template <int NW, typename E, bool CAUSAL>
+template <int NW, int NB, typename E, bool CAUSAL>
 int launch_bwd_head(const raw16* q, const raw16* k, const raw16* v, const raw16* o, const raw16* dO, const float* lse,
                     raw16* dq, raw16* dk, raw16* dv, int B, int H, int N, Strides rs, float scale, hipStream_t st)
 {
-    using Cfg = HeadCfg<NW>;
+    using Cfg = HeadCfg<NW, NB>;
     static std::atomic<bool> lds_allowed{false};
-    const hipError_t attr = allow_lds(avion_bwd_head_kernel<NW, E, CAUSAL>, Cfg::LDS_BYTES, lds_allowed);
+    const hipError_t attr = allow_lds(avion_bwd_head_kernel<NW, NB, E, CAUSAL>, Cfg::LDS_BYTES, lds_allowed);
     if (attr != hipSuccess) return hip_fail(attr, "hipFuncSetAttribute(bwd_head)");
     const int heads = B * H;
     unsigned grid;
     if (!grid_for(heads, &grid)) return AVION_EUNSUPPORTED;
     if (Cfg::WALK) grid = (unsigned)std::min<long long>(heads, kComputeUnits);  // workgroups walk the heads
     begin_launch();
-    hipLaunchKernelGGL((avion_bwd_head_kernel<NW, E, CAUSAL>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, o,
+    hipLaunchKernelGGL((avion_bwd_head_kernel<NW, NB, E, CAUSAL>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, o,
                        dO, lse, dq, dk, dv, H, N, rs.qkv, rs.o, heads, scale * kLog2e, scale);
     return end_launch("launch avion_bwd_head_kernel");
 }
@@ -363,9 +363,20 @@ int head_impl(const void* q, const void* k, const void* v, const void* o, const 
     return by_format(var, [&](auto fmt, auto causal) {
         using E = typename decltype(fmt)::type;
         constexpr bool C = decltype(causal)::value;
-        if (N <= HeadCfg<4>::MAX_N)
-            return launch_bwd_head<4, E, C>(qq, kk, vv, oo, gg, lse, dqq, dkk, dvv, B, H, N, rs, scale, st);
-        return launch_bwd_head<8, E, C>(qq, kk, vv, oo, gg, lse, dqq, dkk, dvv, B, H, N, rs, scale, st);
+        auto run = [&](auto nw, auto nb) {
+            return launch_bwd_head<decltype(nw)::value, decltype(nb)::value, E, C>(qq, kk, vv, oo, gg, lse, dqq, dkk, dvv, B, H, N, rs, scale, st);
+        };
+        constexpr std::integral_constant<int, 4> w4{};
+        constexpr std::integral_constant<int, 8> w8{};
+        switch ((N + 31) / 32) {
+            case 2: return run(w4, std::integral_constant<int, 2>{});
+            case 3: return run(w4, std::integral_constant<int, 3>{});
+            case 4: return run(w4, std::integral_constant<int, 4>{});
+            case 5: return run(w8, std::integral_constant<int, 5>{});
+            case 6: return run(w8, std::integral_constant<int, 6>{});
+            case 7: return run(w8, std::integral_constant<int, 7>{});
+            default: return run(w8, std::integral_constant<int, 8>{});
+        }
     });
 }
 

@@ -244,3 +244,12 @@ def test_whole_heads_match_the_oracle_and_the_two_phases(B, H, N, f16, causal, p
     av.attn_bwd_dkdv(q, k, v, out["lse"], dO, dk, dv, w.scale, ws)
     for n, t in (("dq", dq), ("dk", dk), ("dv", dv)):
         assert torch.equal(out[n].contiguous().view(torch.int16), t.view(torch.int16)), n
+
+
+# Every instance of the whole-head kernel (blocks of 32 tokens 2..8, mask, format) at its shortest and its longest length
+@pytest.mark.parametrize("blocks", range(2, 9))
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("f16", [False, True])
+def test_every_whole_head_instance_at_both_ends_of_its_lengths(blocks, causal, f16):
+    for N in (32 * blocks - 31, 32 * blocks):
+        test_whole_heads_match_the_oracle_and_the_two_phases(1, 3, N, f16, causal, False)
