@@ -145,10 +145,10 @@ DEVINL void avion_fwd_safe_pass(char* smem, const SliceView& kh, const SliceView
     }
 }
 
-// (The causal instance carries a per-lane key bound and a few more scalars: it is sized for one
-// wavefront per SIMD less than the register file would otherwise hold, which keeps it free of spills.)
+// (The causal instances too fit 128 registers without a spill at d = 64; at 136 and three wavefronts per SIMD 16384 heads x 77
+// took 153 us instead of 135, x 40 99 instead of 85, 384 x 1568 192 instead of 179.)
 template <int D, int NW, int KG, typename E, bool CAUSAL>
-__global__ void __launch_bounds__((FwdCfg<D, NW, KG>::NT), (FwdCfg<D, NW, KG>::WAVES_PER_SIMD - (KG == 1 && CAUSAL && FwdCfg<D, NW, KG>::WAVES_PER_SIMD > 3 ? 1 : 0)))
+__global__ void __launch_bounds__((FwdCfg<D, NW, KG>::NT), (FwdCfg<D, NW, KG>::WAVES_PER_SIMD))
 avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const raw16* __restrict__ v,
                  raw16* __restrict__ o, float* __restrict__ lse, int H, int N, int rs_qkv, int rs_o, int nqb, int nblocks,
                  float cs)
