@@ -219,54 +219,66 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
             s = E::mfma(nat_frag(kt, STRIDE, 32 * hk + l32, ks, g), qf[ks], ks == 0 && !RAGGED ? f32x16_zero() : s);
         return s;
     };
-    // reference maximum: over the first 32 keys (of this group's)
+    // reference maximum: over the first 32 keys (of this group's); their scores serve the first unit too, one of three
+    // at 77 tokens (forming them twice: 8 heads x 77 causal 5.44 -> 5.13 us, 16384 x 40 84.0 -> 80.7, x 77 134.4 -> 132.7,
+    // 3072 x 196 84.3 -> 82.8, d = 80 113.8 -> 112.0)
+    f32x16 first = f32x16_zero();
     if (wave_active && (KG == 1 || t0 < t1)) {
-        m_used = both_halves_max(max16(scores(std::true_type{}, ring.buf(t0), 0, t0 * BN))) * cs;
+        first = scores(std::true_type{}, ring.buf(t0), 0, t0 * BN);
+        m_used = both_halves_max(max16(first)) * cs;
         // a query that sees none of them (causal, a later group): any finite reference will do, its weights
         // must come out as 0
         if (KG > 1 && CAUSAL) m_used = t0 * BN < key_limit ? m_used : 0.f;
     }
-
-    for (int t = t0; t < t0 + per; ++t) {
+    // weights of one unit from its scores, and their product with V
+    auto weigh = [&](f32x16 s, const char* vt, int hk) {
+        // the V^T operands are requested before the vector work so that they are there after it
+        frag8 vf[2][CT];
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) vf[half][ct] = tr_frag(vt, STRIDE, tr_off, ct, 2 * hk + half);
+        u32x4 pf[2];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float p = fast_exp2(fmaf(s[i], cs, -m_used));
+            s[i] = p;
+            lsum += p;
+            if (i % 2 == 1) pf[i / 8][(i / 2) % 4] = E::pack(s[i - 1], p);
+        }
+        // the second row sum runs over the weights as rounded to the element format, i.e. the numbers the
+        // second contraction multiplies V with; O is divided by it.  Summed by products with ones: 8 cycles of
+        // the matrix cores for four weights, where two packed additions keep the vector issue port, which is
+        // the scarcer of the two here, for 16.  384 heads x 1568 293 -> 281 us, causal 192 -> 182.
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rs4 = E::add_four(u32x2{pf[i / 2][2 * (i % 2)], pf[i / 2][2 * (i % 2) + 1]}, rs4);
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) oacc[ct] = E::mfma(vf[half][ct], as_frag8(pf[half]), oacc[ct]);
+    };
+    auto tile = [&](auto first_tile, int t) {
         if (KG == 1 || t + 1 < t1) ring.fetch(t + 1);  // into the buffer of tile t-1, which nobody reads any more
         if (wave_active && (KG == 1 || t < t1)) {
             const char* kt = ring.buf(t);
-            const char* vt = kt + Ring::OFF_B;
 #pragma unroll
             for (int hk = 0; hk < 2; ++hk) {
                 const int key_base = t * BN + 32 * hk;
                 if (key_base >= wave_key_end) continue;  // past the last key, or (causal) seen by no query of this wavefront
+                if (decltype(first_tile)::value && hk == 0) {
+                    weigh(first, kt + Ring::OFF_B, hk);
+                    continue;
+                }
                 f32x16 s;
                 if (key_base + 32 > mask_from) s = scores(std::true_type{}, kt, hk, key_base);
                 else s = scores(std::false_type{}, kt, hk, key_base);
-                // the V^T operands are requested before the vector work so that they are there after it
-                frag8 vf[2][CT];
-#pragma unroll
-                for (int half = 0; half < 2; ++half)
-#pragma unroll
-                    for (int ct = 0; ct < CT; ++ct) vf[half][ct] = tr_frag(vt, STRIDE, tr_off, ct, 2 * hk + half);
-                u32x4 pf[2];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float p = fast_exp2(fmaf(s[i], cs, -m_used));
-                    s[i] = p;
-                    lsum += p;
-                    if (i % 2 == 1) pf[i / 8][(i / 2) % 4] = E::pack(s[i - 1], p);
-                }
-                // the second row sum runs over the weights as rounded to the element format, i.e. the numbers the
-                // second contraction multiplies V with; O is divided by it.  Summed by products with ones: 8 cycles of
-                // the matrix cores for four weights, where two packed additions keep the vector issue port, which is
-                // the scarcer of the two here, for 16.  384 heads x 1568 293 -> 281 us, causal 192 -> 182.
-#pragma unroll
-                for (int i = 0; i < 4; ++i) rs4 = E::add_four(u32x2{pf[i / 2][2 * (i % 2)], pf[i / 2][2 * (i % 2) + 1]}, rs4);
-#pragma unroll
-                for (int half = 0; half < 2; ++half)
-#pragma unroll
-                    for (int ct = 0; ct < CT; ++ct) oacc[ct] = E::mfma(vf[half][ct], as_frag8(pf[half]), oacc[ct]);
+                weigh(s, kt + Ring::OFF_B, hk);
             }
         }
         Ring::landed_barrier();  // tile t+1 has landed; tile t is no longer read
-    }
+    };
+    tile(std::true_type{}, t0);
+    for (int t = t0 + 1; t < t0 + per; ++t) tile(std::false_type{}, t);
 
     float rsum = rs4[0];
     // overflow of the fixed reference: redo this workgroup's rows with the running maximum
