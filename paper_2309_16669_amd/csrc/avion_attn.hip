@@ -557,10 +557,17 @@ int gelu_bwd_impl(const void* x, const float* bias, const void* dy, void* dx, vo
     const GeluGrid g = gelu_grid(M, F);
     const bool f16 = (flags & AVION_FLAG_F16) != 0, stream_past_cache = gelu_streams(M, F);
     auto launch = [&](auto fmt, auto streaming) {
-        hipLaunchKernelGGL((avion_bias_gelu_bwd_kernel<typename decltype(fmt)::type, decltype(streaming)::value, WITH_Y>),
-                           dim3((unsigned)(g.ncb * g.nrg)), dim3(kGeluThreads), 0, st, static_cast<const raw16*>(x), bias,
-                           static_cast<const raw16*>(dy), static_cast<raw16*>(dx), static_cast<raw16*>(y), part, (long)M, F,
-                           g.ncb);
+        using E = typename decltype(fmt)::type;
+        constexpr bool STREAM = decltype(streaming)::value;
+        const dim3 grid((unsigned)(g.ncb * g.nrg)), block(kGeluThreads);
+        const raw16 *xx = static_cast<const raw16*>(x), *dyy = static_cast<const raw16*>(dy);
+        raw16* dxx = static_cast<raw16*>(dx);
+        if constexpr (WITH_Y)
+            hipLaunchKernelGGL((avion_bias_gelu_bwd_y_kernel<E, STREAM>), grid, block, 0, st, xx, bias, dyy, dxx,
+                               static_cast<raw16*>(y), part, (long)M, F, g.ncb);
+        else
+            hipLaunchKernelGGL((avion_bias_gelu_bwd_kernel<E, STREAM>), grid, block, 0, st, xx, bias, dyy, dxx, part, (long)M, F,
+                               g.ncb);
     };
     begin_launch();
     if (f16 && stream_past_cache) launch(TypeTag<F16>{}, std::true_type{});

@@ -102,12 +102,10 @@ avion_bias_gelu_fwd_kernel(const raw16* __restrict__ x, const float* __restrict_
 
 // dx, and this row group's partial sums of dbias into part[row group][F].  With WITH_Y also the activation's output,
 // which the second product's weight gradient needs: 8 bytes an element in one pass instead of 10 in two (a forward
-// and this): [12544, 3072] 31 + 55 -> 62 us with dx in dy's place, [50176, 3072] 124 + 190 -> 251.  dx may be dy: an
-// element is read and written by one thread.
+// and this): [12544, 3072] 31 + 55 -> 62 us with dx in dy's place, [50176, 3072] 124 + 190 -> 251.
 template <typename E, bool STREAM, bool WITH_Y>
-__global__ void __launch_bounds__(kGeluThreads)
-avion_bias_gelu_bwd_kernel(const raw16* __restrict__ x, const float* __restrict__ bias, const raw16* dy, raw16* dx,
-                           raw16* __restrict__ y, float* __restrict__ part, long M, int F, int ncb)
+DEVINL void gelu_bwd_body(const raw16* x, const float* bias, const raw16* dy, raw16* dx, raw16* y, float* part, long M, int F,
+                          int ncb)
 {
     const int cb = blockIdx.x % ncb;
     const long rg = blockIdx.x / ncb, nrg = gridDim.x / ncb;
@@ -157,6 +155,22 @@ avion_bias_gelu_bwd_kernel(const raw16* __restrict__ x, const float* __restrict_
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) part[rg * F + col + e] = acc[e];
+}
+
+template <typename E, bool STREAM>
+__global__ void __launch_bounds__(kGeluThreads)
+avion_bias_gelu_bwd_kernel(const raw16* __restrict__ x, const float* __restrict__ bias, const raw16* __restrict__ dy,
+                           raw16* __restrict__ dx, float* __restrict__ part, long M, int F, int ncb)
+{
+    gelu_bwd_body<E, STREAM, false>(x, bias, dy, dx, nullptr, part, M, F, ncb);
+}
+// dx may be dy: an element is read and written by one thread
+template <typename E, bool STREAM>
+__global__ void __launch_bounds__(kGeluThreads)
+avion_bias_gelu_bwd_y_kernel(const raw16* __restrict__ x, const float* __restrict__ bias, const raw16* dy, raw16* dx,
+                             raw16* __restrict__ y, float* __restrict__ part, long M, int F, int ncb)
+{
+    gelu_bwd_body<E, STREAM, true>(x, bias, dy, dx, y, part, M, F, ncb);
 }
 
 // Column sums of a [M, F] tensor of 16-bit elements, in fp32, rounded once: the gradient of a bias that is added to
