@@ -297,21 +297,29 @@ int by_variant(Variant var, int d, F f)
 //                           instead of 333.  From six tiles on (below, the exchange costs what the shorter
 //                           walk gains); four groups from 16 tiles on, in the forward at d = 64 (registers
 //                           of the backward and LDS at d = 80 allow two)
-//   64 rows, 2 groups       when even 64-row blocks do
+//   96 rows, 4 groups       when 96-row blocks do, forward at d = 64, from 16 tiles on: a quarter less work per compute unit
+//   64 rows, 2 or 4 groups  when even 64-row blocks do; four, at d = 64, from 11 tiles on in the forward (at 8 they lose 3 %, at
+//                           13 they are equal) and from 15 in the backward (11: equal, 13: 2.5 % slower)
 // Measured, us, one group -> this rule (forward; whole backward): 12 heads x 1568 30.4 -> 21.3; 65 -> 52,
 // 32 x 785 16.9 -> 14.8; 39 -> 35, 16 x 785 backward 37 -> 28, 16 x 500 11.7 -> 8.8, 8 x 200 forward 7.9 -> 6.9,
 // 12 x 785 (d = 80) 20.1 -> 14.3; 48 -> 35.  On the other side of the lines two groups lose:
 // 24 x 1568 85 -> 99 (backward), 64 x 785 22.4 -> 22.4; 53 -> 60, 64 x 300 21.0 -> 21.2, 240 x 77 6.5 -> 6.9.
+// 128 -> 96 rows, forward: 12 x 1568 21.4 -> 19.6 (fp16), 18.8 -> 16.3 (causal), 16 x 1400 18.5 -> 16.6, 8 x 3000 30.2 -> 27.4; 13
+// tiles equal, 9 tiles 11.1 -> 11.5; the backward in three blocks of rows gives 50.8 -> 51.5 at 12 x 1568.
+// 64 rows, two -> four groups (forward; whole backward): 8 x 900 11.9 -> 11.2; 29.5 -> 28.2, 8 x 1568 17.3 -> 16.0; 41.6 -> 38.9,
+// 4 x 2000 19.7 -> 17.1; 49.3 -> 43.6, 6 x 3000 29.6 -> 26.0; 84 -> 75.
 // `min_tiles`: the backward's two phases keep one group where the whole backward is one launch, whose bits
-// they give: up to 256 tokens at 64 channels, 128 at 80.
+// they give: up to 256 tokens at 64 channels, 128 at 80.  `min_tiles4`: the line between two and four groups of 64 rows.
 template <typename F>
-int by_split(long long heads, int N, int min_tiles, F f)
+int by_split(long long heads, int N, int min_tiles, int min_tiles4, F f)
 {
     constexpr std::integral_constant<int, 1> one{};
     constexpr std::integral_constant<int, 2> two{};
+    constexpr std::integral_constant<int, 3> three{};
     constexpr std::integral_constant<int, 4> four{};
     const int tiles = (N + 63) / 64;
-    if (tiles >= min_tiles && heads * tiles <= kComputeUnits) return f(two, two);
+    if (tiles >= min_tiles && heads * tiles <= kComputeUnits) return tiles >= min_tiles4 ? f(two, four) : f(two, two);
+    if (tiles >= 16 && heads * ((N + 95) / 96) <= kComputeUnits) return f(three, four);
     if (tiles >= 6 && heads * ((N + 127) / 128) <= kComputeUnits) return tiles >= 16 ? f(four, four) : f(four, two);
     return f(four, one);
 }
@@ -332,10 +340,13 @@ int fwd_impl(const void* q, const void* k, const void* v, void* o, float* lse, i
             return launch_win_fwd<decltype(dim)::value, typename decltype(fmt)::type, decltype(causal)::value>(
                 qq, kk, vv, oo, lse, B, H, N, rs, scale, st);
         });
-    return by_split((long long)B * H, N, 2, [&](auto nw, auto kg) {
+    return by_split((long long)B * H, N, 2, 11, [&](auto nw, auto kg) {
         return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
-            constexpr int KG = decltype(dim)::value == 64 ? decltype(kg)::value : std::min(decltype(kg)::value, 2);
-            return launch_fwd<decltype(dim)::value, decltype(nw)::value, KG, typename decltype(fmt)::type,
+            // at 80 channels LDS holds two groups
+            constexpr bool D64 = decltype(dim)::value == 64;
+            constexpr int NW = D64 || decltype(nw)::value == 2 ? decltype(nw)::value : 4;
+            constexpr int KG = D64 ? decltype(kg)::value : std::min(decltype(kg)::value, 2);
+            return launch_fwd<decltype(dim)::value, NW, KG, typename decltype(fmt)::type,
                       decltype(causal)::value>(qq, kk, vv, oo, lse, B, H, N, rs, scale, st);
         });
     });
@@ -382,6 +393,14 @@ int head_impl(const void* q, const void* k, const void* v, const void* o, const 
 
 int split_tiles(int d) { return d == 64 ? kHeadMaxN / 64 + 1 : BwdSmallCfg<80, 4>::MAX_N / 64 + 1; }
 
+// The backward's form of a cut: three blocks of rows become four, and more than two groups fit two blocks at 64
+// channels only (registers, LDS)
+template <int D, int NW_, int KG_>
+struct BwdCut {
+    static constexpr int NW = NW_ == 2 ? 2 : 4;
+    static constexpr int KG = D == 64 && NW == 2 ? KG_ : std::min(KG_, 2);
+};
+
 int dq_impl(const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dO, void* dq, int B,
             int H, int N, int d, int packed, Variant var, float scale, void* workspace, size_t workspace_bytes, void* stream)
 {
@@ -401,10 +420,10 @@ int dq_impl(const void* q, const void* k, const void* v, const void* o, const fl
     // the lengths of the head kernel: avion_attn_bwd_dq alone comes here with them, and only its form is built
     if (by_head(N, d) && (var.f16 || var.causal)) return AVION_EUNSUPPORTED;
     if (by_head(N, d)) return launch_dq<64, 4, 1, Bf16, false, true>(qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
-    return by_split((long long)B * H, N, split_tiles(d), [&](auto nw, auto kg) {
+    return by_split((long long)B * H, N, split_tiles(d), 15, [&](auto nw, auto kg) {
         return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
-            constexpr int KG = std::min(decltype(kg)::value, 2);
-            return launch_dq<decltype(dim)::value, decltype(nw)::value, KG, typename decltype(fmt)::type,
+            using Cut = BwdCut<decltype(dim)::value, decltype(nw)::value, decltype(kg)::value>;
+            return launch_dq<decltype(dim)::value, Cut::NW, Cut::KG, typename decltype(fmt)::type,
                       decltype(causal)::value, decltype(dim)::value == 80>(qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
         });
     });
@@ -427,10 +446,10 @@ int dkdv_impl(const void* q, const void* k, const void* v, const float* lse, con
     const raw16 *qq = static_cast<const raw16*>(q), *kk = static_cast<const raw16*>(k), *vv = static_cast<const raw16*>(v),
                *gg = static_cast<const raw16*>(dO);
     raw16 *dkk = static_cast<raw16*>(dk), *dvv = static_cast<raw16*>(dv);
-    return by_split((long long)B * H, N, split_tiles(d), [&](auto nw, auto kg) {
+    return by_split((long long)B * H, N, split_tiles(d), 15, [&](auto nw, auto kg) {
         return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
-            constexpr int KG = std::min(decltype(kg)::value, 2);
-            return launch_dkdv<decltype(dim)::value, decltype(nw)::value, KG, typename decltype(fmt)::type,
+            using Cut = BwdCut<decltype(dim)::value, decltype(nw)::value, decltype(kg)::value>;
+            return launch_dkdv<decltype(dim)::value, Cut::NW, Cut::KG, typename decltype(fmt)::type,
                       decltype(causal)::value>(qq, kk, vv, gg, rowsc, dkk, dvv, B, H, N, rs, scale, st);
         });
     });

@@ -253,3 +253,15 @@ def test_whole_heads_match_the_oracle_and_the_two_phases(B, H, N, f16, causal, p
 def test_every_whole_head_instance_at_both_ends_of_its_lengths(blocks, causal, f16):
     for N in (32 * blocks - 31, 32 * blocks):
         test_whole_heads_match_the_oracle_and_the_two_phases(1, 3, N, f16, causal, False)
+
+
+# Cuts of small launches into blocks of 64 and 96 rows with four groups (by_split): both sides of the lines in tiles, groups of
+# unequal and of no tiles (11 tiles in four groups: 3, 3, 3, 2; 13: 4, 4, 4, 1), ragged last rows and keys
+@pytest.mark.parametrize("B,H,N,f16,causal,packed", [
+    (1, 3, 640, False, False, False), (1, 3, 641, True, False, True), (1, 2, 705, False, True, False), (1, 2, 833, False, False, True),
+    (1, 2, 896, True, True, False), (1, 2, 897, False, False, False), (2, 2, 1281, False, True, True), (1, 12, 1409, False, False, False),
+    (1, 16, 1025, True, False, True), (1, 15, 1024, False, True, False), (1, 12, 1569, False, True, False)])
+def test_small_launches_cut_into_four_groups(B, H, N, f16, causal, packed):
+    w = si.small_workload(B, H, N, 64, seed=9700 + N)
+    x = si.make_inputs(w, fmt="f16" if f16 else "bf16")
+    check(w, x, run_ex(w, x, f16, causal, packed), f16, causal)
