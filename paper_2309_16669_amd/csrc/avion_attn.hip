@@ -17,6 +17,7 @@
 #include "avion_fwd.h"
 #include "avion_head.h"
 #include "avion_ln.h"
+#include "avion_pair.h"
 #include "avion_small.h"
 #include "avion_gelu.h"
 
@@ -156,6 +157,23 @@ int launch_dq(const raw16* q, const raw16* k, const raw16* v, const raw16* o, co
     hipLaunchKernelGGL((avion_dq_kernel<D, NW, KG, E, CAUSAL, TILE16>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, o, dO, lse, dq,
                        rowsc, H, N, rs.qkv, rs.o, nqb, (int)nblocks, scale * kLog2e, scale);
     return end_launch("launch avion_dq_kernel");
+}
+
+template <typename E>
+int launch_dq_pair(const raw16* q, const raw16* k, const raw16* v, const raw16* o, const raw16* dO, const float* lse, raw16* dq,
+                   float* rowsc, int B, int H, int N, Strides rs, float scale, hipStream_t st)
+{
+    static std::atomic<bool> lds_allowed{false};
+    const hipError_t attr = allow_lds(avion_dq_pair_kernel<E>, PairRing::LDS_BYTES, lds_allowed);
+    if (attr != hipSuccess) return hip_fail(attr, "hipFuncSetAttribute(dq_pair)");
+    const int nqb = ((N + 31) / 32 + kPairBlocks - 1) / kPairBlocks;
+    const long long nblocks = (long long)nqb * B * H;
+    unsigned grid;
+    if (!grid_for(nblocks, &grid)) return AVION_EUNSUPPORTED;
+    begin_launch();
+    hipLaunchKernelGGL((avion_dq_pair_kernel<E>), dim3(grid), dim3(256), PairRing::LDS_BYTES, st, q, k, v, o, dO, lse, dq,
+                       rowsc, H, N, rs.qkv, rs.o, nqb, (int)nblocks, scale * kLog2e, scale);
+    return end_launch("launch avion_dq_pair_kernel");
 }
 
 template <int D, int NW, int KG, typename E, bool CAUSAL>
@@ -401,6 +419,19 @@ struct BwdCut {
     static constexpr int KG = D == 64 && NW == 2 ? KG_ : std::min(KG_, 2);
 };
 
+// dQ in two blocks of queries per wavefront (avion_pair.h) on the full chip: 256-row workgroups, two to a compute unit, are
+// a coarse cut, so it is taken where the last round of them is well filled (the chip's share of work per compute
+// unit, rounded up, exceeds it by at most a fifth) and the sequence is long enough for its prologue.  Measured, us, three
+// wavefronts per SIMD of one block -> this: 384 x 1568 409 -> 385, 64 x 3528 333 -> 316, 96 x 1200 71.9 -> 64.7, 96 x 2000
+// 169 -> 156, 128 x 1000 67.2 -> 64.3; on the other side of the lines 96 x 1568 (2.3 workgroups each) 112 -> 126, 64 x 1200 (1.2)
+// 51 -> 55, 48 x 2000 (1.5) 88 -> 92, 384 x 785 126 -> 129.
+bool by_pair(long long heads, int N, int d, Variant var)
+{
+    if (d != 64 || var.causal || N < 1000 || heads * ((N + 127) / 128) <= kComputeUnits) return false;
+    const long long blocks = heads * ((N + 31) / 32), chip = kComputeUnits * kPairBlocks;
+    return 5 * ((blocks + chip - 1) / chip) * chip <= 6 * blocks;
+}
+
 int dq_impl(const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dO, void* dq, int B,
             int H, int N, int d, int packed, Variant var, float scale, void* workspace, size_t workspace_bytes, void* stream)
 {
@@ -420,6 +451,10 @@ int dq_impl(const void* q, const void* k, const void* v, const void* o, const fl
     // the lengths of the head kernel: avion_attn_bwd_dq alone comes here with them, and only its form is built
     if (by_head(N, d) && (var.f16 || var.causal)) return AVION_EUNSUPPORTED;
     if (by_head(N, d)) return launch_dq<64, 4, 1, Bf16, false, true>(qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
+    if (by_pair((long long)B * H, N, d, var)) {
+        if (var.f16) return launch_dq_pair<F16>(qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
+        return launch_dq_pair<Bf16>(qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
+    }
     return by_split((long long)B * H, N, split_tiles(d), 15, [&](auto nw, auto kg) {
         return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
             using Cut = BwdCut<decltype(dim)::value, decltype(nw)::value, decltype(kg)::value>;

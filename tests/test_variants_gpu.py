@@ -265,3 +265,21 @@ def test_small_launches_cut_into_four_groups(B, H, N, f16, causal, packed):
     w = si.small_workload(B, H, N, 64, seed=9700 + N)
     x = si.make_inputs(w, fmt="f16" if f16 else "bf16")
     check(w, x, run_ex(w, x, f16, causal, packed), f16, causal)
+
+
+# dQ in two blocks per wavefront (by_pair): last workgroups of one and two blocks (shared by four and two wavefronts) to eight,
+# last tiles of one unit and two, ragged and full.  Oracle on a first, a middle and a last head; dK, dV read the scalars it leaves.
+@pytest.mark.parametrize("B,H,N,f16", [(16, 4, 1000, False), (16, 4, 1024, True), (31, 4, 1025, False), (30, 4, 1088, False),
+                                       (39, 3, 1119, True), (55, 2, 1153, False), (35, 3, 1248, False), (3, 32, 1300, True)])
+def test_dq_in_pairs_of_blocks(B, H, N, f16):
+    import torch
+    w = si.small_workload(B, H, N, 64, seed=9800 + N)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    dt = torch.float16 if f16 else torch.bfloat16
+    bits = lambda: torch.randn(B, N, H, 64, device="cuda", generator=gen).to(dt).view(torch.int16).cpu().numpy().view(np.uint16)
+    x = {n: bits() for n in ("q", "k", "v", "dO")}
+    out = run_ex(w, x, f16, False, False)
+    for n in ("dq", "dk", "dv"):
+        assert bool(torch.isfinite(out[n]).all()), n
+    slices = [(0, 0), (B // 2, H // 2), (B - 1, H - 1)]
+    (gh.check_f16_against_oracle if f16 else gh.check_against_oracle)(w, x, out, slices)
