@@ -4,7 +4,7 @@
 // delta_i = sum_c dO_ic O_ic:
 //     dV = P^T dO ,  dP = dO V^T ,  dS = P o (dP - delta) ,  dQ = scale dS K ,  dK = scale dS^T Q.
 //
-// Two kernels, both free of atomics (results are bit-reproducible):
+// Two kernels, both free of atomics (results are bit-reproducible; dQ on a full chip and long sequences: avion_pair.h):
 //   avion_dq_kernel   : query-stationary.  Also computes delta from O and dO and leaves it, with a
 //                       rescaled copy of LSE, for the second kernel.  Same shape as the forward:
 //                       S^T = K Q^T and dP^T = V dO^T land with lane = query, so LSE and delta are
