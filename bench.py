@@ -37,18 +37,18 @@ MEASURED_HBM_BYTES_PER_LAUNCH = {
     # (workload, dtype, kernel) -> (bytes per launch, summary under profiles/ that holds the counters):
     # (2.0 x FETCH_SIZE + 1.0 x WRITE_SIZE) KiB, the factors being what the same counters read for a plain copy of
     # known size.  Measured offline on separate q/k/v tensors with N(0,1) operands; any other run prints null.
-    ("vitb_batch", "bf16", "avion_fwd_kernel"): (3.1111e+08, "profiles/vitb_batch_bf16.txt"),
-    ("vitb_batch", "bf16", "avion_dq_kernel"): (4.7261e+08, "profiles/vitb_batch_bf16.txt"),
-    ("vitb_batch", "bf16", "avion_dkdv_kernel"): (4.7019e+08, "profiles/vitb_batch_bf16.txt"),
-    ("vitb_batch", "f16", "avion_fwd_kernel"): (3.1113e+08, "profiles/vitb_batch_f16.txt"),
-    ("vitb_batch", "f16", "avion_dq_kernel"): (4.7275e+08, "profiles/vitb_batch_f16.txt"),
-    ("vitb_batch", "f16", "avion_dkdv_kernel"): (4.7021e+08, "profiles/vitb_batch_f16.txt"),
-    ("vith_d80", "bf16", "avion_fwd_kernel"): (1.3784e+08, "profiles/vith_d80.txt"),
-    ("vith_d80", "bf16", "avion_dq_kernel"): (2.1204e+08, "profiles/vith_d80.txt"),
-    ("vith_d80", "bf16", "avion_dkdv_kernel"): (2.1958e+08, "profiles/vith_d80.txt"),
-    ("vitb_long", "bf16", "avion_fwd_kernel"): (1.5766e+08, "profiles/vitb_long.txt"),
-    ("vitb_long", "bf16", "avion_dq_kernel"): (2.4581e+08, "profiles/vitb_long.txt"),
-    ("vitb_long", "bf16", "avion_dkdv_kernel"): (2.4423e+08, "profiles/vitb_long.txt"),
+    ("vitb_batch", "bf16", "avion_fwd_kernel"): (3.1100e+08, "profiles/vitb_batch_bf16.txt"),
+    ("vitb_batch", "bf16", "avion_dq_kernel"): (4.8630e+08, "profiles/vitb_batch_bf16.txt"),
+    ("vitb_batch", "bf16", "avion_dkdv_kernel"): (4.7000e+08, "profiles/vitb_batch_bf16.txt"),
+    ("vitb_batch", "f16", "avion_fwd_kernel"): (3.1100e+08, "profiles/vitb_batch_f16.txt"),
+    ("vitb_batch", "f16", "avion_dq_kernel"): (4.8950e+08, "profiles/vitb_batch_f16.txt"),
+    ("vitb_batch", "f16", "avion_dkdv_kernel"): (4.7000e+08, "profiles/vitb_batch_f16.txt"),
+    ("vith_d80", "bf16", "avion_fwd_kernel"): (1.3830e+08, "profiles/vith_d80.txt"),
+    ("vith_d80", "bf16", "avion_dq_kernel"): (2.1190e+08, "profiles/vith_d80.txt"),
+    ("vith_d80", "bf16", "avion_dkdv_kernel"): (2.2060e+08, "profiles/vith_d80.txt"),
+    ("vitb_long", "bf16", "avion_fwd_kernel"): (1.5810e+08, "profiles/vitb_long.txt"),
+    ("vitb_long", "bf16", "avion_dq_kernel"): (2.5400e+08, "profiles/vitb_long.txt"),
+    ("vitb_long", "bf16", "avion_dkdv_kernel"): (2.4400e+08, "profiles/vitb_long.txt"),
 }
 PREWARM_SECONDS = 0.3
 
