@@ -178,7 +178,8 @@ avion_bias_gelu_bwd_y_kernel(const raw16* __restrict__ x, const float* __restric
 // 8 rows; its 8 row lanes meet in LDS.  With one row group the sums leave as they are, otherwise as fp32 partials that
 // avion_ln_param_reduce_kernel adds in a fixed order.
 // Bound by memory where M is large, by two launches where it is small: calls of 12544 x 768 20.6 (torch's sum) -> 12.8 us,
-// 50176 x 768 34.8 -> 16.4, 12544 x 3072 29.5 -> 15.3; 77 x 512 5.4 -> 12 (both sides through Python).
+// 50176 x 768 34.8 -> 16.4, 12544 x 3072 29.5 -> 15.3.  77 x 512 alone is the other way, 5.4 -> 12 through Python; within
+// the MLP, where a call is bound by the host and saves a forward pass, 77 x 2048 -> 512 forward + backward is 166 -> 151.
 constexpr int kSumCols = 256, kSumRows = 8, kSumFly = 4, kSumOneLaunch = 256;
 template <typename E, bool ONLY>
 __global__ void __launch_bounds__(kSumCols / 8 * kSumRows)
