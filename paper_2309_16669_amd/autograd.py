@@ -188,7 +188,9 @@ class _BiasGeluLinear(torch.autograd.Function):
         x2, bias, weight = ctx.saved_tensors
         M, F = x2.shape
         d2 = dout.contiguous().view(M, weight.shape[0])
-        dx = d2 @ weight                                 # with respect to the activation's output; then, in its place, to x
+        # with respect to the activation's output; then, in its place, to x: .data, as neither the product's node
+        # (create_graph) nor its tangent is that of the gradient of x
+        dx = (d2 @ weight).data
         y, dbias = torch.empty_like(x2), torch.empty_like(bias)
         bias_gelu_bwd_y(x2, bias.contiguous(), dx, dx, y, dbias, _workspace_of(bias_gelu_bwd_workspace_bytes(M, F), x2.device))
         return dx.view(ctx.shape), dbias, d2.t() @ y, (_column_sum(d2) if ctx.has_out_bias else None)

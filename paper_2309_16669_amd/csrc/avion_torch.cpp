@@ -362,7 +362,9 @@ struct BiasGeluLinear : torch::autograd::Function<BiasGeluLinear> {
         require(x, "x", {M, F}, ctx->saved_data["format"].toScalarType(), grad[0]);
         require(bias.contiguous(), "bias", {F}, at::kFloat, grad[0]);
         const Tensor d2 = grad[0].contiguous().view({M, weight.size(0)});
-        const Tensor dy = at::matmul(d2, weight);
+        // variable_data: the product's storage without its node (create_graph) or tangent, which are not those of the
+        // gradient of x that the kernel writes into it
+        const Tensor dy = at::matmul(d2, weight).variable_data();
         require(dy, "dy", {M, F}, x.scalar_type(), grad[0]);  // under autocast a product comes in autocast's format
         // the gradient of x takes dy's place; y is rebuilt beside it, not kept
         const Tensor b = bias.contiguous(), y = at::empty_like(x), dbias = at::empty_like(b);

@@ -191,6 +191,34 @@ def test_products_under_autocast_behave_as_in_the_class(own, auto, inside):
         assert a is b
 
 
+ROUTES = {"native": lambda ag: ag.bias_gelu_linear, "class": lambda ag: ag._BiasGeluLinear.apply}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("route", ROUTES)
+def test_the_activation_gradients_are_not_differentiated_as_the_products_they_overwrite(route):
+    # dx is formed in the storage of the incoming gradient's product with the weight: neither that product's node
+    # (create_graph) nor its tangent (forward mode over the backward) may come along
+    import torch
+    import torch.autograd.forward_ad as fwad
+    from paper_2309_16669_amd import autograd as ag
+    f = ROUTES[route](ag)
+    x, bias, weight, out_bias = (a.detach().requires_grad_() for a in _calls()["bias_gelu_linear"][2])
+    out = f(x, bias, weight, out_bias)
+    dy = torch.randn_like(out).requires_grad_()
+    plain = torch.autograd.grad(out, (x, bias), dy.detach(), retain_graph=True)
+    recorded = torch.autograd.grad(out, (x, bias), dy, create_graph=True)
+    for g, ref in zip(recorded, plain):
+        assert torch.equal(g, ref) and not g.requires_grad
+        with pytest.raises(RuntimeError, match="does not require grad"):
+            g.float().square().sum().backward()
+    with fwad.dual_level():
+        dual = fwad.make_dual(dy.detach(), torch.randn_like(dy))
+        for g, ref in zip(torch.autograd.grad(out, (x, bias), dual), plain):
+            primal, tangent = fwad.unpack_dual(g)
+            assert torch.equal(primal, ref) and tangent is None
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", ["attention", "qkvpacked", "layer_norm", "bias_gelu", "bias_gelu_linear"])
 def test_other_threads_run_during_a_call(name):
