@@ -158,9 +158,11 @@ class _BiasGelu(torch.autograd.Function):
 
 
 def _column_sum(d):
-    """d.sum(0); torch's where the rows are no multiple of 16 bytes."""
+    """d.sum(0); torch's where the rows are no multiple of 16 bytes, and where the sum is to be differentiated itself
+    (create_graph, a tangent): it is linear in d."""
     need = column_sum_workspace_bytes(*d.shape)
-    if need == 0 or d.data_ptr() % 16 != 0:
+    recorded = torch.is_grad_enabled() and d.requires_grad
+    if need == 0 or d.data_ptr() % 16 != 0 or recorded or torch.autograd.forward_ad.unpack_dual(d).tangent is not None:
         return d.sum(0)
     out = torch.empty((d.shape[1],), dtype=d.dtype, device=d.device)
     column_sum(d, out, _workspace_of(need, d.device))

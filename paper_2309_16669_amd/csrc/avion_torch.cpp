@@ -304,12 +304,15 @@ void gelu_bwd(const Tensor& x, const Tensor& bias_, const Tensor& dy, Tensor& dx
                               x.size(0), (int)x.size(1), format_flag(x), ws.data_ptr(), need, stream()));
 }
 
-// d.sum(0); torch's where the rows are no multiple of 16 bytes
+// d.sum(0); torch's where the rows are no multiple of 16 bytes, and where the sum is to be differentiated itself
+// (create_graph, a tangent): it is linear in d
 Tensor column_sum(const Tensor& d)
 {
     const int64_t M = d.size(0), F = d.size(1);
     const size_t need = F <= INT32_MAX ? avion_column_sum_workspace_bytes(M, (int)F) : 0;
-    if (need == 0 || !element_format(d) || reinterpret_cast<uintptr_t>(d.data_ptr()) % 16 != 0) return d.sum(0);
+    if (need == 0 || !element_format(d) || reinterpret_cast<uintptr_t>(d.data_ptr()) % 16 != 0 || records({&d}) ||
+        d._fw_grad(0).defined())
+        return d.sum(0);
     const Tensor sum = at::empty({F}, d.options());
     check(avion_column_sum(d.data_ptr(), sum.data_ptr(), M, (int)F, format_flag(d), workspace(need, d).data_ptr(), need, stream()));
     return sum;

@@ -220,6 +220,27 @@ def test_the_activation_gradients_are_not_differentiated_as_the_products_they_ov
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("route", ROUTES)
+def test_the_output_bias_gradient_can_be_differentiated(route):
+    # the sum of the incoming gradient's rows, linear in it, with a node and a tangent of its own
+    import torch
+    import torch.autograd.forward_ad as fwad
+    from paper_2309_16669_amd import autograd as ag
+    f = ROUTES[route](ag)
+    x, bias, weight, out_bias = (a.detach().requires_grad_() for a in _calls()["bias_gelu_linear"][2])
+    out = f(x, bias, weight, out_bias)
+    dy = torch.randn_like(out).requires_grad_()
+    db, = torch.autograd.grad(out, out_bias, dy, create_graph=True)
+    v = torch.randn_like(db)
+    ddy, = torch.autograd.grad(db, dy, v, retain_graph=True)
+    assert torch.equal(ddy, v.expand_as(dy))
+    with fwad.dual_level():
+        t = torch.randn_like(dy)
+        db, = torch.autograd.grad(out, out_bias, fwad.make_dual(dy.detach(), t))
+        assert torch.equal(fwad.unpack_dual(db).tangent, t.sum(0))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("name", ["attention", "qkvpacked", "layer_norm", "bias_gelu", "bias_gelu_linear"])
 def test_other_threads_run_during_a_call(name):
     # with a switch interval longer than the test another thread runs only when a call gives up the interpreter lock
