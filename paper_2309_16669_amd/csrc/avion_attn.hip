@@ -420,16 +420,21 @@ struct BwdCut {
 };
 
 // dQ in two blocks of queries per wavefront (avion_pair.h) on the full chip: 256-row workgroups, two to a compute unit, are
-// a coarse cut, so it is taken where the last round of them is well filled (the chip's share of work per compute
-// unit, rounded up, exceeds it by at most a fifth) and the sequence is long enough for its prologue.  Measured, us, three
+// a coarse cut, so it is taken where the last round of them is well filled and the sequence is long enough for its
+// prologue: the chip's share of blocks per compute unit, rounded up to whole rounds of 8, exceeds it by at most a fifth, and so
+// rounded in workgroups, of which a head's last may be short, by at most a quarter.  Measured, us, three
 // wavefronts per SIMD of one block -> this: 384 x 1568 409 -> 385, 64 x 3528 333 -> 316, 96 x 1200 71.9 -> 64.7, 96 x 2000
 // 169 -> 156, 128 x 1000 67.2 -> 64.3; on the other side of the lines 96 x 1568 (2.3 workgroups each) 112 -> 126, 64 x 1200 (1.2)
-// 51 -> 55, 48 x 2000 (1.5) 88 -> 92, 384 x 785 126 -> 129.
+// 51 -> 55, 48 x 2000 (1.5) 88 -> 92, 384 x 785 126 -> 129, and, within a fifth in blocks, where short workgroups open another
+// round, 52 x 1025 (0.84 in blocks, 1.02 in workgroups) 34.2 -> 46.6, 44 x 1300 39.3 -> 53.1, 38 x 1568 45.4 -> 61.5, 33 x 1800
+// 51.8 -> 70.7, 68 x 1800 (1.89, 2.12) 99 -> 113, 173 x 1300 (3.46, 4.05) 131 -> 136; from 1.2 to 1.25 in workgroups 0.96 of the time in the
+// mean of 101 shapes (1.01 at most), from 1.3 to 1.36 0.975 with one in six slower.
 bool by_pair(long long heads, int N, int d, Variant var)
 {
     if (d != 64 || var.causal || N < 1000 || heads * ((N + 127) / 128) <= kComputeUnits) return false;
-    const long long blocks = heads * ((N + 31) / 32), chip = kComputeUnits * kPairBlocks;
-    return 5 * ((blocks + chip - 1) / chip) * chip <= 6 * blocks;
+    const int nb = (N + 31) / 32;
+    const long long blocks = heads * nb, chip = kComputeUnits * kPairBlocks, wgs = heads * ((nb + kPairBlocks - 1) / kPairBlocks);
+    return 5 * ((blocks + chip - 1) / chip) * chip <= 6 * blocks && 4 * ((wgs + kComputeUnits - 1) / kComputeUnits) * chip <= 5 * blocks;
 }
 
 int dq_impl(const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dO, void* dq, int B,

@@ -268,18 +268,49 @@ def test_small_launches_cut_into_four_groups(B, H, N, f16, causal, packed):
 
 
 # dQ in two blocks per wavefront (by_pair): last workgroups of one and two blocks (shared by four and two wavefronts) to eight,
-# last tiles of one unit and two, ragged and full.  Oracle on a first, a middle and a last head; dK, dV read the scalars it leaves.
-@pytest.mark.parametrize("B,H,N,f16", [(16, 4, 1000, False), (16, 4, 1024, True), (31, 4, 1025, False), (30, 4, 1088, False),
-                                       (39, 3, 1119, True), (55, 2, 1153, False), (35, 3, 1248, False), (3, 32, 1300, True)])
-def test_dq_in_pairs_of_blocks(B, H, N, f16):
+# last tiles of one unit and two, ragged and full, both layouts (packed: Q, K, V, dQ rows three times as far apart as those of O,
+# dO), one round of workgroups and several.  Oracle on a first, a middle and a last head; dK, dV read the scalars it leaves.
+# (The first six rows are just beyond the line in workgroups.)
+@pytest.mark.parametrize("B,H,N,f16,packed", [
+    (31, 4, 1025, False, False), (30, 4, 1088, False, False), (39, 3, 1119, True, False), (55, 2, 1153, False, False),
+    (35, 3, 1248, False, False), (3, 32, 1300, True, False),
+    (16, 4, 1000, False, False), (16, 4, 1024, True, True), (17, 3, 1060, False, True), (17, 3, 1060, True, False),
+    (17, 3, 1119, True, False), (17, 3, 1124, False, True), (25, 2, 1153, False, False), (17, 3, 1185, True, True),
+    (17, 3, 1248, False, False), (14, 3, 1300, True, True), (14, 3, 1312, False, False), (61, 3, 1200, False, True)])
+def test_dq_in_pairs_of_blocks(B, H, N, f16, packed):
     import torch
     w = si.small_workload(B, H, N, 64, seed=9800 + N)
     gen = torch.Generator(device="cuda").manual_seed(N)
     dt = torch.float16 if f16 else torch.bfloat16
     bits = lambda: torch.randn(B, N, H, 64, device="cuda", generator=gen).to(dt).view(torch.int16).cpu().numpy().view(np.uint16)
     x = {n: bits() for n in ("q", "k", "v", "dO")}
-    out = run_ex(w, x, f16, False, False)
+    out = run_ex(w, x, f16, False, packed)
     for n in ("dq", "dk", "dv"):
         assert bool(torch.isfinite(out[n]).all()), n
     slices = [(0, 0), (B // 2, H // 2), (B - 1, H - 1)]
     (gh.check_f16_against_oracle if f16 else gh.check_against_oracle)(w, x, out, slices)
+
+
+# On the other side of by_pair's lines dQ is avion_dq_kernel's, whose bits do not depend on the other heads of the launch; the
+# pair form adds up a last block that wavefronts share in another order.  Heads whose short last workgroup would open another
+# round have the former's bits (those of a launch that fills the chip badly in blocks too), heads within the lines have not.
+@pytest.mark.parametrize("heads,more,N,paired", [(52, 78, 1050, False), (44, 66, 1300, False), (33, 50, 1800, False),
+                                                 (68, 80, 1800, False), (42, 66, 1300, True), (51, 78, 1060, True)])
+def test_short_last_workgroups_do_not_open_another_round(heads, more, N, paired):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(N + heads)
+    x = [torch.randn(more, N, 1, 64, device="cuda", generator=gen).bfloat16() for _ in range(4)]
+    got = [_dq_of(*(t[:h] for t in x)) for h in (heads, more)]
+    assert torch.equal(got[0].view(torch.int16), got[1][:heads].view(torch.int16)) != paired
+
+
+def _dq_of(q, k, v, dO):
+    import torch
+    import paper_2309_16669_amd as av
+    B, N, H, d = q.shape
+    o, dq, lse = torch.empty_like(q), torch.full_like(q, float("nan")), torch.empty(B, H, N, device="cuda")
+    ws = torch.empty(av.attn_bwd_workspace_bytes(B, H, N, d), dtype=torch.uint8, device="cuda")
+    av.attn_fwd_ex(q, k, v, o, lse, 0.125, False)
+    av.attn_bwd_dq(q, k, v, o, lse, dO, dq, 0.125, ws)
+    torch.cuda.synchronize()
+    return dq
