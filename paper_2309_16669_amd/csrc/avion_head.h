@@ -52,6 +52,9 @@ struct HeadCfg {
                          OFF_SC = OFF_DS + (WALK || 2 * DS_BYTES > TILE_BYTES ? 2 * DS_BYTES : TILE_BYTES);
     static constexpr int LDS_BYTES = OFF_SC + 2 * MAX_N * 4;  // LSE*log2e and -delta per query
     static constexpr int WAVES_PER_SIMD = WALK || NB > 3 ? 2 : 3;
+    // transposed operands requested ahead of the vector work; with 168 registers (three wavefronts per SIMD) behind it.  Behind it
+    // at four blocks: 8 x 128 9.10 us instead of 8.95, causal 9.77 (9.67), 513 x 128 21.9 (21.6), 513 x 97 causal 21.64 (21.39).
+    static constexpr bool EARLY_TR = WAVES_PER_SIMD == 2;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
     static_assert(!WALK || ROWS % 64 == 0, "walking workgroups fetch 64 rows at a time");
     static_assert(NB * RowStore<D, Bf16>::BYTES <= 2 * DS_BYTES, "the epilogue stages its rows in the dS buffers");
@@ -75,7 +78,6 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
     const long rs = rs_qkv;
     const int k0 = wave * 32;  // first key, and for the per-query scalars first query, of this wavefront
-    constexpr int nb = NB;  // (N + 31) / 32
     const int nslots = (N + 63) / 64;
     const bool wave_active = k0 < N;
     const char *qt = smem, *gt = smem + Cfg::OFF_G, *kt = smem + Cfg::OFF_K;
@@ -231,7 +233,7 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
                         tq[ct] = tr_frag(qt, STRIDE, tr_off, ct, 2 * j + half);
                     }
                 };
-                if (Cfg::WALK) load_tr();
+                if (Cfg::EARLY_TR) load_tr();
                 u32x4 pf, df;
 #pragma unroll
                 for (int e = 8 * half; e < 8 * half + 8; ++e) {
@@ -243,7 +245,7 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
                         df[(e / 2) % 4] = E::pack(dp[e - 1], dp[e]);
                     }
                 }
-                if (!Cfg::WALK) {
+                if (!Cfg::EARLY_TR) {
                     __builtin_amdgcn_sched_barrier(0);
                     load_tr();
                 }
