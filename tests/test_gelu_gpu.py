@@ -333,6 +333,15 @@ def test_column_sums(M, F, fmt):
     ws = torch.full((av.column_sum_workspace_bytes(M, F),), 255, dtype=torch.uint8, device="cuda")
     av.column_sum(x, out, ws)
     ref, mag = x.double().sum(0), x.double().abs().sum(0)
-    # the rounding of the result, and of the fp32 additions: a sum passes at most M / 8 + 64 of them one after the other
-    bound = u * ref.abs() + (M / 8 + 64) * 2.0 ** -24 * mag + 1e-7
+    # the rounding of the result, and of the fp32 additions one after the other: a thread's rows (8 row lanes in each of the row
+    # groups, whose number follows from the workspace), 7 row lanes, then a 64th of the row groups, 6 lane exchanges, 16 wavefronts
+    groups = 1 if M <= 256 else ws.numel() // (4 * F)
+    depth = -(-M // (8 * groups)) + 4 + 7 + -(-groups // 64) + 6 + 16
+    bound = u * ref.abs() + depth * 2.0 ** -24 * mag + 1e-7
     assert bool(((out.double() - ref).abs() <= bound).all())
+    # sums that the format holds exactly: a row left out or added twice shows, the first and the last (all 5, all 3) in every column
+    x = torch.randint(-1, 2, (M, F), device="cuda", generator=gen) * (torch.rand(M, F, device="cuda", generator=gen) < 300 / M)
+    x[0], x[-1] = 5, 3
+    assert int(x.sum(0).abs().max()) <= 256
+    av.column_sum(x.to(dt), out, ws)
+    assert torch.equal(out.double(), x.sum(0).double())

@@ -201,7 +201,8 @@ def test_the_running_maximum_fallback_in_launches_of_one_group(d, f16, causal):
     assert np.abs(lg - rl).max() <= 2e-6 * np.abs(rl).max() + 1e-3
 
 
-@pytest.mark.parametrize("H,N,sink", [(2, 300, 250), (2, 300, 40), (17, 1025, 1000)])
+# cuts (blocks of 32 rows, groups): (2, 2) twice, (3, 4), (2, 4) with the last and with the first group overflowing, (4, 4) likewise
+@pytest.mark.parametrize("H,N,sink", [(2, 300, 250), (2, 300, 40), (17, 1025, 1000), (2, 900, 890), (2, 900, 40), (24, 1153, 1100), (24, 1153, 40)])
 def test_a_group_whose_reference_overflows_redoes_the_block(H, N, sink):
     # keys from `sink` on carry scores far above the first 32 keys of their group: 2^15 in fp16 is passed
     w = si.small_workload(1, H, N, 64, seed=9400 + N, scale=1.0)
@@ -255,12 +256,14 @@ def test_every_whole_head_instance_at_both_ends_of_its_lengths(blocks, causal, f
         test_whole_heads_match_the_oracle_and_the_two_phases(1, 3, N, f16, causal, False)
 
 
-# Cuts of small launches into blocks of 64 and 96 rows with four groups (by_split): both sides of the lines in tiles, groups of
+# Cuts of small launches into blocks of 64, 96 and 128 rows with four groups (by_split): both sides of the lines in tiles, groups of
 # unequal and of no tiles (11 tiles in four groups: 3, 3, 3, 2; 13: 4, 4, 4, 1), ragged last rows and keys
 @pytest.mark.parametrize("B,H,N,f16,causal,packed", [
     (1, 3, 640, False, False, False), (1, 3, 641, True, False, True), (1, 2, 705, False, True, False), (1, 2, 833, False, False, True),
     (1, 2, 896, True, True, False), (1, 2, 897, False, False, False), (2, 2, 1281, False, True, True), (1, 12, 1409, False, False, False),
-    (1, 16, 1025, True, False, True), (1, 15, 1024, False, True, False), (1, 12, 1569, False, True, False)])
+    (1, 16, 1025, True, False, True), (1, 15, 1024, False, True, False), (1, 12, 1569, False, True, False),
+    # 128 rows: beyond the line of 96-row blocks
+    (1, 16, 1568, False, False, False), (1, 24, 1153, True, True, True), (1, 32, 1000, False, True, False), (2, 16, 961, True, False, False)])
 def test_small_launches_cut_into_four_groups(B, H, N, f16, causal, packed):
     w = si.small_workload(B, H, N, 64, seed=9700 + N)
     x = si.make_inputs(w, fmt="f16" if f16 else "bf16")
