@@ -37,6 +37,7 @@ MEASURED_HBM_BYTES_PER_LAUNCH = {
     # (workload, dtype, kernel) -> (bytes per launch, summary under profiles/ that holds the counters):
     # (2.0 x FETCH_SIZE + 1.0 x WRITE_SIZE) KiB, the factors being what the same counters read for a plain copy of
     # known size.  Measured offline on separate q/k/v tensors with N(0,1) operands; any other run prints null.
+    # "avion_dq_kernel" stands for the dQ phase: on vitb_batch and vitb_long it runs as avion_dq_pair_kernel.
     ("vitb_batch", "bf16", "avion_fwd_kernel"): (3.1100e+08, "profiles/vitb_batch_bf16.txt"),
     ("vitb_batch", "bf16", "avion_dq_kernel"): (4.8630e+08, "profiles/vitb_batch_bf16.txt"),
     ("vitb_batch", "bf16", "avion_dkdv_kernel"): (4.7000e+08, "profiles/vitb_batch_bf16.txt"),

@@ -253,9 +253,10 @@ int avion_layernorm_bwd(const void *x, const float *gamma, const float *mean, co
  *   (partial sums of dbias: at most 4096 * 1024 floats, independent of M)
  * The backward rebuilds Phi and phi from x and bias, so the activation's output need not be kept
  * for it: with it the MLP keeps F * 2 bytes per token for this step instead of 2 * F * 2 (the
- * second matrix product's own input is rebuilt by one more avion_bias_gelu_fwd when its weight
- * gradient is formed).  erf by a five-term rational approximation with absolute error < 1.5e-7,
- * arithmetic in fp32, outputs rounded once; no atomics, results are bit-reproducible.
+ * second matrix product's own input is rebuilt when its weight gradient is formed, by
+ * avion_bias_gelu_bwd_y or one more avion_bias_gelu_fwd).  erf by a five-term rational
+ * approximation with absolute error < 1.5e-7, arithmetic in fp32, outputs rounded once; no atomics,
+ * results are bit-reproducible.
  * Pointers 16-byte aligned; same stream, error and ownership rules as every entry point above.
  */
 int avion_bias_gelu_fwd(const void *x, const float *bias, void *y, long long M, int F,

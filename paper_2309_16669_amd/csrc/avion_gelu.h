@@ -177,9 +177,10 @@ avion_bias_gelu_bwd_y_kernel(const raw16* __restrict__ x, const float* __restric
 // every row (the second product's).  A workgroup takes 256 columns (32 threads of 16 bytes) and every nrg-th group of
 // 8 rows; its 8 row lanes meet in LDS.  With one row group the sums leave as they are, otherwise as fp32 partials that
 // avion_ln_param_reduce_kernel adds in a fixed order.
-// Bound by memory where M is large, by two launches where it is small: calls of 12544 x 768 20.6 (torch's sum) -> 12.8 us,
-// 50176 x 768 34.8 -> 16.4, 12544 x 3072 29.5 -> 15.3.  77 x 512 alone is the other way, 5.4 -> 12 through Python; within
-// the MLP, where a call is bound by the host and saves a forward pass, 77 x 2048 -> 512 forward + backward is 166 -> 151.
+// Bound by memory where M is large, by its launches where it is small.  Calls one after the other, torch's sum -> this:
+// 12544 x 768 19.8 -> 7.3 us, 50176 x 768 34.4 -> 16.1, 12544 x 3072 29.1 -> 15.6, 1024 x 768 9.8 -> 6.4, 77 x 512 5.3 -> 3.3.
+// One launch instead of two up to 256 rows, at 768 columns (in brackets without the host, in a graph): 128 rows 3.6 us against 6.3
+// (3.5; 4.5), 256 4.7 against 6.3 (4.8; 4.6), 384 6.2 against 6.3 (6.3; 4.6), 1024 13.7 against 6.4; the same from 64 to 8192 columns.
 constexpr int kSumCols = 256, kSumRows = 8, kSumFly = 4, kSumOneLaunch = 256;
 template <typename E, bool ONLY>
 __global__ void __launch_bounds__(kSumCols / 8 * kSumRows)
