@@ -13,10 +13,11 @@
 // rows (8 consecutive channels per lane), and operands whose contraction index is a token are read
 // from a transposed LDS tile whose token positions are permuted to match the accumulator rows.
 //
-// LDS tile: R token rows of D two-byte elements in their natural order, row stride D*2+16 bytes for D = 64 and
-// D*2+48 for D = 80 (an odd multiple of 16 bytes, so the 16-byte fragment reads of 16 consecutive
-// lanes hit distinct banks; for D = 80 the zeroed pad also covers the reads of the channel tile
-// that reaches past channel 79).
+// LDS tile: R token rows of D two-byte elements in their natural order, row stride D*2+16 bytes (an odd multiple of 16
+// bytes, so the 16-byte fragment reads of 16 consecutive lanes hit distinct banks).  At D = 80 the third channel tile
+// reaches past channel 79: what it reads there, the pad and the next row's first channels, only ever enters accumulator
+// rows of channels 80..95, which nothing stores, so it may be anything.  (With a pad of 48 bytes, zeros for all of them,
+// a tile is 13 KB instead of 11: 128 heads x 1568 forward 130.4 -> 128.2 us, dQ 168.5 -> 166.3, dK/dV 218.6 -> 216.0.)
 //   natural fragment   : lane = token row, 8 consecutive channels -> one ds_read_b128.
 //   transposed fragment: lane = channel, 8 tokens.  Read from the same tile with two
 //                        ds_read_b64_tr_b16.  Within a group of 16 lanes that instruction hands
@@ -316,7 +317,7 @@ DEVINL unsigned padded_block_voff(int blk, int lane, unsigned row_bytes);
 template <int D>
 constexpr int tile_stride()
 {
-    return D == 64 ? 144 : D * 2 + 48;
+    return D * 2 + 16;
 }
 
 template <int D>
@@ -447,13 +448,6 @@ struct TileStage {
             if (TOTAL % NT == 0 || idx < TOTAL) *reinterpret_cast<u32x4*>(tile + row * STRIDE + ch * 16) = r[i];
         }
     }
-    // the pad of every row reads as zeros (only D = 80 ever reads it)
-    DEVINL static void zero_pad(char* tile, int tid)
-    {
-        constexpr int PADW = (STRIDE - D * 2) / 4;
-        for (int i = tid; i < R * PADW; i += NT)
-            *reinterpret_cast<unsigned*>(tile + (i / PADW) * STRIDE + D * 2 + (i % PADW) * 4) = 0u;
-    }
 };
 
 // Initial value of a transposed score accumulator (lane = query, register i = key
@@ -500,7 +494,8 @@ struct TileRing {
     static constexpr int NTI = TILE_BYTES / 1024, NBLK = 2 * NTI + (SCALARS ? 1 : 0), NPW = (NBLK + NW - 1) / NW;
     static constexpr int OFF_B = TILE_BYTES, OFF_SCALARS = 2 * TILE_BYTES;
     static constexpr int BUF_BYTES = NBLK * 1024;
-    static constexpr int LDS_BYTES = NBUF * BUF_BYTES;
+    // (D = 80: the third channel tile of the last row ends 16 bytes past the tile)
+    static constexpr int LDS_BYTES = NBUF * BUF_BYTES + (D % 32 != 0 ? 64 : 0);
 
     char* smem;
     unsigned smem_addr;

@@ -79,10 +79,6 @@ DEVINL void avion_fwd_safe_pass(char* smem, const SliceView& kh, const SliceView
     for (int ct = 0; ct < CT; ++ct) oacc[ct] = f32x16_zero();
     Stage kst, vst;
     __syncthreads();
-    if constexpr (D % 32 != 0) {
-        Stage::zero_pad(vbuf(0), tid);
-        Stage::zero_pad(vbuf(1), tid);
-    }
     kst.load(kh, 0, tid);
     vst.load(vh, 0, tid);
     kst.store(kbuf(0), tid);

@@ -60,15 +60,6 @@ struct RowFrags {
     }
 };
 
-// the pads of a wavefront's tiles read as zeros (D = 80 reads them as channels 80..95)
-template <int D>
-DEVINL void win_zero_pads(char* tiles, int ntiles, int lane)
-{
-    constexpr int STRIDE = tile_stride<D>(), PADW = (STRIDE - D * 2) / 4;
-    for (int i = lane; i < ntiles * 32 * PADW; i += 64)
-        *reinterpret_cast<unsigned*>(tiles + (i / PADW) * STRIDE + D * 2 + (i % PADW) * 4) = 0u;
-}
-
 // Which of the 16 accumulator rows 8*(i/4) + 4*g + i%4 (bit i) this lane's column may be combined
 // with: same problem (row / N == col / N) and, for causal attention, key at or before query.
 // lane_is_query: the lane's column is a query and the rows are keys (transposed scores), else the
@@ -111,7 +102,6 @@ avion_win_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, c
     const int tr_off = tr_lane_offset(lane, STRIDE);
     const unsigned allow = win_allow_bits<CAUSAL>(l32, g, N, true);
     const long rs = rs_qkv;
-    if constexpr (D % 32 != 0) win_zero_pads<D>(vtile, 1, lane);
 
     struct Window {
         RowFrags<D> q, k, v;
@@ -226,7 +216,6 @@ avion_win_bwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, c
     const unsigned allow_t = win_allow_bits<CAUSAL>(l32, g, N, true);   // lane = query, rows = keys
     const unsigned allow_n = win_allow_bits<CAUSAL>(l32, g, N, false);  // lane = key, rows = queries
     const long rs = rs_qkv;
-    if constexpr (D % 32 != 0) win_zero_pads<D>(qtile, 3, lane);
 
     for (int item = blockIdx.x * Cfg::NW + wave; item < nitems; item += gridDim.x * Cfg::NW) {
         const int win = item / H, h = item % H, b0 = win * G;
