@@ -4,25 +4,33 @@
 // That kernel runs a 32 x 32 block as a serial chain -- 8 products, the vector work, 4 products -- and leaves it to three
 // wavefronts per SIMD to overlap; they do so poorly (its cycles are the sum of its matrix and its vector cycles).
 // Here the overlap is in the code: while block A's scores of a 32-key step go through the vector work, the products
-// of block B's (S, dP, and dQ of its previous step) stand beside it, then the other way round.  255 registers, two
+// of block B's (S, dP, and dQ of its previous step) stand beside it, then the other way round.  256 registers, two
 // wavefronts per SIMD.  Both blocks read one K^T fragment, and 256 queries share a tile: half the transposed LDS
 // reads and half the tile traffic.
 // Workgroup = 4 wavefronts = 8 blocks; the last one of a head has the remaining blocks, of which one or two are shared
 // by wavefronts that take every second or fourth 32-key unit and are added through LDS in a fixed order.
 //
-// Tiles are 64 rows of 128 bytes without padding, 16-byte chunks permuted within a row by a XOR with bits of the row
-// number: 16 consecutive rows at one chunk, and 4 consecutive rows at 4 chunks (a transposing read's half wavefront), hit
-// distinct banks; conflicts fall from a third of the LDS cycles to 4 %, a tile from 18 KB to 16.  Four buffers: the
-// products run one step ahead into the next tile, and a fetch has a whole tile's time beyond that to land.
-// Measured, us, avion_dq_kernel -> this: 384 heads x 1568 409 -> 385 (389 -> 367 on another card), x 3000 1367 -> 1227,
-// 64 x 3528 333 -> 316.  What bounds it now: matrix cores 55 % and vector issue 70 % of the cycles busy at 1.75 GHz.
-// The same form of the forward gives nothing over four wavefronts per SIMD (281 -> 279), of dK/dV (one block, pipelined
-// over half steps) 431 -> 478: it reads twice the LDS operands per product.
+// Tiles are 64 rows of 128 bytes without padding (quad_at: four rows by four chunks at a time, the chunks permuted by a XOR
+// with bits of the row number).  16 consecutive rows at one chunk, and 4 consecutive rows at 4 chunks (a transposing read's
+// half wavefront), hit distinct banks: conflicts are 4 % of the LDS cycles instead of a third, a tile 16 KB instead of 18.
+// The XOR touches two bits of the chunk, of which a lane's reads vary one, so four addresses per lane serve every read with
+// the rest in the instruction's offset; they move on with the tile.  (With the chunks of a row permuted over all eight
+// places each read needed an addition of its own, 12 % of the vector instructions.)  Four buffers: the
+// products run one step ahead into the next tile, and a fetch has a whole tile's time beyond that to land.  Row operands
+// are requested six products ahead.
+// Measured, us, avion_dq_kernel -> this with an addition per read and operands three products ahead -> this: 384 heads x 1568
+// 409 -> 385; 368.4 -> 358.2, 96 x 3000 317.5 -> 308.6, 96 x 1200 71.9 -> 64.7; 60.0 -> 58.7.  Not what binds: the order of the
+// three products of a step (358 to 360 in three orders).  On all-zero operands 289 -> 276: on real ones the card's power
+// limit takes a third of the clock.
+// The same form of the forward gives nothing over four wavefronts per SIMD (281 -> 279).  dK/dV, one block per wavefront with the
+// operands requested eight products ahead, is no faster at two wavefronts per SIMD than avion_dkdv_kernel at three (96 x 3000 390.7 ->
+// 389.6, 384 x 1568 447.7 -> 466.5), and at one, with two blocks and half the LDS reads, slower (384 x 1568 456 -> 502): one
+// wavefront issues an instruction every 4.6 cycles at most.
 #pragma once
 #include "avion_bwd.h"
 
-// chunk permutation of a row
-DEVINL int swz(int row) { const int p = row >> 1; return (p & 1) << 2 | (p & 2) | (p >> 2 & 1); }
+// Byte offset of 16-byte chunk `ch` of row `row` in a tile
+DEVINL unsigned quad_at(int row, int ch) { return (row >> 2) * 512 + (ch >> 2) * 256 + (row & 3) * 64 + (((ch & 3) ^ (row >> 2 & 3)) * 16); }
 // K and V tiles; every wavefront issues four loads a tile
 struct PairRing {
     static constexpr int TILE = 64 * 128, BUF = 2 * TILE, NBUF = 4, LDS_BYTES = NBUF * BUF;
@@ -34,8 +42,9 @@ struct PairRing {
         da = ab.words;
         db = bb.words;
         smem_addr = lds_address(smem) + wave * 1024;
-        const int row = 8 * wave + lane / 8;
-        va = row * (unsigned)(rs_a * 2) + ((lane % 8) ^ swz(row)) * 16;
+        // the chunk at offset 16 * lane of 8 rows
+        const int row = 8 * wave + lane / 32 * 4 + lane / 4 % 4, ch = lane / 16 % 2 * 4 + ((lane ^ (row >> 2)) & 3);
+        va = row * (unsigned)(rs_a * 2) + ch * 16;
         half = 32 * (unsigned)(rs_a * 2);
     }
     DEVINL void fetch(int ti) const
@@ -47,25 +56,39 @@ struct PairRing {
     DEVINL static void landed_barrier() { asm volatile("s_waitcnt vmcnt(4)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
     DEVINL static void all_landed_barrier() { asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 };
-// this lane's addresses in a tile
+// This lane's addresses in the present buffer: natural fragments by the step's low bit, transposed ones by which four of
+// their eight tokens.
 struct PairLane {
-    unsigned nat0, tr0;
-    DEVINL PairLane(int lane)
+    unsigned nat[2], tr[2];
+    DEVINL PairLane(int lane, unsigned buf)
     {
-        const int l32 = lane % 32, g = lane / 32, G = lane >> 4, j = lane & 15, r = 4 * (G >> 1) + (j >> 2);
-        nat0 = l32 * 128 + (g ^ swz(l32)) * 16;
-        tr0 = r * 128 + ((2 * (G & 1) + ((j & 3) >> 1)) ^ swz(r)) * 16 + (j & 1) * 8;
+        const int l32 = lane % 32, g = lane / 32, G = lane >> 4, j = lane & 15, r = 4 * (G >> 1) + (j >> 2), c = 2 * (G & 1) + ((j & 3) >> 1);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            nat[i] = buf + quad_at(l32, 2 * i + g);
+            tr[i] = buf + quad_at(r + 8 * i, c) + (j & 1) * 8;
+        }
     }
-    // the XORs below stay at their uses instead of living in registers of their own
-    DEVINL frag8 natural(unsigned tile, int hk, int ks) const
+    // (opaque, or the compiler adds the uniform parts first and each address once more)
+    DEVINL void move_nat(int by)
+    {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) { nat[i] += by; asm volatile("" : "+v"(nat[i])); }
+    }
+    DEVINL void move_tr(int by)
+    {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) { tr[i] += by; asm volatile("" : "+v"(tr[i])); }
+    }
+    DEVINL frag8 natural(int of_v, int hk, int ks) const
     {
         typedef const __attribute__((address_space(3))) frag8* ptr;
-        return *(ptr)((nat0 ^ (unsigned)(ks * 32)) + tile + hk * 4096);
+        return *(ptr)(nat[ks & 1] + (of_v * PairRing::TILE + hk * 4096 + (ks >> 1) * 256));
     }
-    DEVINL frag8 transposed(unsigned tile, int ct, int step) const
+    DEVINL frag8 transposed(int ct, int step) const
     {
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((tr0 ^ (unsigned)(ct * 64)) + tile + step * 2048));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)((tr0 ^ (unsigned)(ct * 64 + 16)) + tile + step * 2048 + 1024));
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tr[0] + (step * 2048 + ct * 256)));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tr[1] + (step * 2048 + ct * 256)));
         const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
         return as_frag8(u32x4{l2[0], l2[1], h2[0], h2[1]});
     }
@@ -113,8 +136,7 @@ avion_dq_pair_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, c
     const PairSplit sp(N, qb, wave, logical);
     const int ntiles = (N + BN - 1) / BN, nb = (N + 31) / 32;
     const PairRing ring(k + head_off, rs, v + head_off, rs, N, smem, wave, lane);
-    const PairLane ln(lane);
-    const unsigned lds0 = lds_address(smem);
+    PairLane ln(lane, lds_address(smem));
     ring.fetch(0);
     ring.fetch(1);
     ring.fetch(2);
@@ -155,7 +177,8 @@ avion_dq_pair_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, c
     init(B, sp.blk0 + (sp.mine > 1), sp.mine > 1);
     hold(A.qf); hold(B.qf); hold(A.gf); hold(B.gf);
     PairRing::all_landed_barrier();
-    auto buf = [&](int ti) { return lds0 + (unsigned)(ti & 3) * PairRing::BUF; };
+    // from tile ti's buffer to the next one
+    auto onward = [](int ti) { return (ti & 3) == 3 ? -3 * PairRing::BUF : PairRing::BUF; };
     auto grad = [&](Blk& x, int i0, int i1) {
 #pragma unroll
         for (int i = i0; i < i1; ++i) {
@@ -164,69 +187,82 @@ avion_dq_pair_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, c
             if (i % 2 == 1) x.df[i / 8][(i / 2) % 4] = E::pack(x.s[i - 1], x.s[i]);
         }
     };
-    auto unit = [&](Blk& x, int t, int hk) {
-        const int key_base = t * BN + 32 * hk;
+    auto unit = [&](Blk& x, int key_base, int hk) {
         if (key_base >= N) return;
-        const unsigned kt = buf(t);
         x.s = key_base + 32 > N ? key_mask_block(key_base, lane_from_exec() / 32, N) : f32x16_zero();
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            x.s = E::mfma(ln.natural(kt, hk, ks), x.qf[ks], x.s);
-            x.dp = E::mfma(ln.natural(kt + PairRing::TILE, hk, ks), x.gf[ks], ks == 0 ? f32x16_zero() : x.dp);
+            x.s = E::mfma(ln.natural(0, hk, ks), x.qf[ks], x.s);
+            x.dp = E::mfma(ln.natural(1, hk, ks), x.gf[ks], ks == 0 ? f32x16_zero() : x.dp);
         }
         grad(x, 0, 16);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x.acc[i % 2] = E::mfma(ln.transposed(kt, i % 2, 2 * hk + i / 2), as_frag8(x.df[i / 2]), x.acc[i % 2]);
+        for (int i = 0; i < 4; ++i) x.acc[i % 2] = E::mfma(ln.transposed(i % 2, 2 * hk + i / 2), as_frag8(x.df[i / 2]), x.acc[i % 2]);
     };
     const int nfast = N / BN;
     if (sp.mine == 2) {
-        frag8 kf[4];
+        frag8 kf[4], fk[2], fv[2];
 #pragma unroll
         for (int i = 0; i < 4; ++i) kf[i] = frag8{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            A.s = E::mfma(ln.natural(buf(0), 0, ks), A.qf[ks], ks == 0 ? f32x16_zero() : A.s);
-            A.dp = E::mfma(ln.natural(buf(0) + PairRing::TILE, 0, ks), A.gf[ks], ks == 0 ? f32x16_zero() : A.dp);
+            A.s = E::mfma(ln.natural(0, 0, ks), A.qf[ks], ks == 0 ? f32x16_zero() : A.s);
+            A.dp = E::mfma(ln.natural(1, 0, ks), A.gf[ks], ks == 0 ? f32x16_zero() : A.dp);
         }
-        frag8 fk = ln.natural(buf(0), 0, 0), fv = ln.natural(buf(0) + PairRing::TILE, 0, 0);
-        // one phase: x's vector work beside y's products
-        auto phase = [&](auto reload, Blk& x, Blk& y, unsigned kt, int hk, unsigned ktn, int hkn) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            fk[ks] = ln.natural(0, 0, ks);
+            fv[ks] = ln.natural(1, 0, ks);
+        }
+        // One phase: x's vector work beside y's products.  hk: the half tile y's scores are of; hkn: the one after it, to
+        // whose buffer the addresses move by `by`.  Natural operands are requested two steps ahead.
+        auto phase = [&](auto first, Blk& x, Blk& y, auto hk, auto hkn, int by) {
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 __builtin_amdgcn_sched_barrier(0);
-                const frag8 ck = fk, cv = fv;
-                fk = ks + 1 < KS ? ln.natural(kt, hk, (ks + 1) % KS) : ln.natural(ktn, hkn, 0);
-                fv = ks + 1 < KS ? ln.natural(kt + PairRing::TILE, hk, (ks + 1) % KS) : ln.natural(ktn + PairRing::TILE, hkn, 0);
-                y.s = E::mfma(ck, y.qf[ks], ks == 0 ? f32x16_zero() : y.s);
-                y.dp = E::mfma(cv, y.gf[ks], ks == 0 ? f32x16_zero() : y.dp);
+                if (ks == 2 && by != 0) ln.move_nat(by);
                 y.acc[ks % 2] = E::mfma(kf[ks], as_frag8(y.df[ks / 2]), y.acc[ks % 2]);
-                if (decltype(reload)::value) kf[ks] = ln.transposed(kt, ks % 2, 2 * hk + ks / 2);
+                if (decltype(first)::value) kf[ks] = ln.transposed(ks % 2, 2 * hk + ks / 2);
+                y.s = E::mfma(fk[ks & 1], y.qf[ks], ks == 0 ? f32x16_zero() : y.s);
+                y.dp = E::mfma(fv[ks & 1], y.gf[ks], ks == 0 ? f32x16_zero() : y.dp);
+                fk[ks & 1] = ln.natural(0, ks < 2 ? hk : hkn, (ks + 2) % 4);
+                fv[ks & 1] = ln.natural(1, ks < 2 ? hk : hkn, (ks + 2) % 4);
                 grad(x, 4 * ks, 4 * ks + 4);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        auto step = [&](unsigned kt, int hk, unsigned ktn, int hkn) {
-            phase(std::true_type{}, A, B, kt, hk, ktn, hkn);
-            phase(std::false_type{}, B, A, ktn, hkn, ktn, hkn);
+        constexpr std::integral_constant<int, 0> lo{};
+        constexpr std::integral_constant<int, 1> hi{};
+        auto step = [&](auto hk, auto hkn, int by) {
+            phase(std::true_type{}, A, B, hk, hkn, by);
+            phase(std::false_type{}, B, A, hkn, hkn, 0);
         };
         for (int t = 0; t < nfast; ++t) {
             ring.fetch(t + 3);
-            step(buf(t), 0, buf(t), 1);
-            step(buf(t), 1, buf(t + 1), 0);
+            step(lo, hi, 0);
+            step(hi, lo, onward(t));
+            ln.move_tr(onward(t));
             PairRing::landed_barrier();
         }
-        if (N % BN >= 32) step(buf(nfast), 0, buf(nfast), 1);
+        if (N % BN >= 32) step(lo, hi, 0);
 #pragma unroll
         for (int i = 0; i < 4; ++i) B.acc[i % 2] = E::mfma(kf[i], as_frag8(B.df[i / 2]), B.acc[i % 2]);
-        const int t = N / 64, hk = N / 32 % 2;
-        unit(A, t, hk);
-        unit(B, t, hk);
+        const int last = N / 32 * 32;
+        if (N % BN >= 32) {
+            unit(A, last, 1);
+            unit(B, last, 1);
+        } else {
+            unit(A, last, 0);
+            unit(B, last, 0);
+        }
     } else {
         for (int t = 0; t < ntiles; ++t) {
             if (t < nfast) ring.fetch(t + 3);
 #pragma unroll
             for (int hk = 0; hk < 2; ++hk)
-                if (sp.mine == 1 && ((2 * t + hk) & (sp.parts - 1)) == sp.part) unit(A, t, hk);
+                if (sp.mine == 1 && ((2 * t + hk) & (sp.parts - 1)) == sp.part) unit(A, t * BN + 32 * hk, hk);
+            ln.move_nat(onward(t));
+            ln.move_tr(onward(t));
             if (t < nfast) PairRing::landed_barrier();
         }
     }
