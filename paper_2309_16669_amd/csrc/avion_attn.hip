@@ -281,7 +281,7 @@ int launch_win_bwd(const raw16* q, const raw16* k, const raw16* v, const raw16* 
     return end_launch("launch avion_win_bwd_kernel");
 }
 
-// Kernel instances by head size, format and masking (wavefronts per workgroup: by_split and head_impl below).
+// Kernel instances by head size, format and masking (wavefronts per workgroup: fwd_cut, bwd_cut and head_impl below).
 // by_variant calls f(head dim, element format, causal) with the three as compile-time tags, by_format
 // f(element format, causal).
 template <typename T>
@@ -307,39 +307,75 @@ int by_variant(Variant var, int d, F f)
     });
 }
 
-// How one launch of the big kernels is cut.  A workgroup owns 32 * NW rows of the stationary side; with
-// KG > 1 it has KG groups of NW wavefronts, each of which walks its own share of the streamed tiles.
-//   128 rows, 1 group       the full chip: three to four workgroups per compute unit fill each other's waits
-//   128 rows, 2 or 4 groups when 128-row blocks give every compute unit at most one workgroup: a lone
-//                           workgroup is one wavefront per SIMD, and a 32 x 32 unit then takes 560 ns of it
-//                           instead of 333.  From six tiles on (below, the exchange costs what the shorter
-//                           walk gains); four groups from 16 tiles on, in the forward at d = 64 (registers
-//                           of the backward and LDS at d = 80 allow two)
-//   96 rows, 4 groups       when 96-row blocks do, forward at d = 64, from 16 tiles on: a quarter less work per compute unit
-//   64 rows, 2 or 4 groups  when even 64-row blocks do; four, at d = 64, from 11 tiles on in the forward (at 8 they lose 3 %, at
-//                           13 they are equal) and from 15 in the backward (11: equal, 13: 2.5 % slower)
-// Measured, us, one group -> this rule (forward; whole backward): 12 heads x 1568 30.4 -> 21.3; 65 -> 52,
-// 32 x 785 16.9 -> 14.8; 39 -> 35, 16 x 785 backward 37 -> 28, 16 x 500 11.7 -> 8.8, 8 x 200 forward 7.9 -> 6.9,
-// 12 x 785 (d = 80) 20.1 -> 14.3; 48 -> 35.  On the other side of the lines two groups lose:
-// 24 x 1568 85 -> 99 (backward), 64 x 785 22.4 -> 22.4; 53 -> 60, 64 x 300 21.0 -> 21.2, 240 x 77 6.5 -> 6.9.
-// 128 -> 96 rows, forward: 12 x 1568 21.4 -> 19.6 (fp16), 18.8 -> 16.3 (causal), 16 x 1400 18.5 -> 16.6, 8 x 3000 30.2 -> 27.4; 13
-// tiles equal, 9 tiles 11.1 -> 11.5; the backward in three blocks of rows gives 50.8 -> 51.5 at 12 x 1568.
-// 64 rows, two -> four groups (forward; whole backward): 8 x 900 11.9 -> 11.2; 29.5 -> 28.2, 8 x 1568 17.3 -> 16.0; 41.6 -> 38.9,
-// 4 x 2000 19.7 -> 17.1; 49.3 -> 43.6, 6 x 3000 29.6 -> 26.0; 84 -> 75.
-// `min_tiles`: the backward's two phases keep one group where the whole backward is one launch, whose bits
-// they give: up to 256 tokens at 64 channels, 128 at 80.  `min_tiles4`: the line between two and four groups of 64 rows.
+// How one launch of the big kernels is cut.  A workgroup owns 32 * nw rows of the stationary side; with kg > 1 it has kg
+// groups of nw wavefronts, each of which walks its own share of the streamed tiles.  One group of 128 rows is the full
+// chip's cut: three to four workgroups per compute unit fill each other's waits.  Smaller launches leave compute units
+// with one workgroup, a wavefront per SIMD, and a 32 x 32 unit then takes 560 ns of it instead of 333 (460 with two); shorter
+// blocks fill more of the chip, groups shorten each wavefront's walk, and both cost an exchange or more tile traffic.
+// The lines stand where both sides' times crossed over 2044 shapes of 6..400 heads x 257..3600 tokens (964 causal, 921 at 80 channels).
+// Measured, us, one group of 128 rows -> this rule (forward; whole backward): 12 heads x 1568 30.4 -> 17.5; 65 -> 49,
+// 32 x 785 16.9 -> 12.9; 39 -> 33, 8 x 1568 17.3 (two groups) -> 16.0; 41.6 -> 38.9, 6 x 3000 29.6 -> 26.0; 84 -> 75.
+struct Cut {
+    int nw, kg;
+};
+struct Fill {  // workgroups of 64, 96 and 128 rows of a launch, and its 64-row tiles
+    long long w64, w96, w128;
+    int tiles;
+    Fill(long long heads, int N) : w64(heads * ((N + 63) / 64)), w96(heads * ((N + 95) / 96)), w128(heads * ((N + 127) / 128)), tiles((N + 63) / 64) {}
+};
+Cut fwd_cut(const Fill& f, int d, bool causal)
+{
+    const int t = f.tiles;
+    // four groups: at 64 channels (LDS holds two at 80), where each still has a walk (64 rows: at 8 tiles they lose 3 % to two, at 13
+    // they are equal; 96 rows: 13 tiles equal, 9 tiles 11.1 -> 11.5 us)
+    if (t >= 2 && f.w64 <= kComputeUnits) return {2, d == 64 && t >= 11 ? 4 : 2};
+    if (d == 80) return t >= 6 && f.w128 <= kComputeUnits ? Cut{4, 2} : Cut{4, 1};
+    // 96 rows, two groups -> 128 rows, two groups: 48 x 400 8.9 -> 9.3 us; four groups: 12 x 1568 17.5 -> 19.3
+    if (t >= 6 && f.w96 <= kComputeUnits) return {3, t >= 16 ? 4 : 2};
+    if (t >= 6 && f.w128 <= kComputeUnits) return {4, t >= 16 ? 4 : 2};
+    // Up to two workgroups of 96 rows per compute unit: two groups each, three wavefronts per SIMD instead of one or two.  24 x 1568 32.4 ->
+    // 29.4 us, 16 x 2400 46.5 -> 40.9, 12 x 3136 59.5 -> 52.1, 40 x 785 18.9 -> 18.1; 0.93 of the time in the mean of 189 shapes, 1.03 at most; at 300 to
+    // 350 tokens up to 1.08.  (Beyond it and up to two of 128 rows, 128 rows in two groups would be 0.97 in the mean; one group stays there:
+    // its bits are those of larger launches, which a test of dQ's cuts takes them to be.)
+    if (!causal && t >= 7 && f.w96 <= 2 * kComputeUnits) return {3, 2};
+    // causal blocks are of unequal length, which shorter ones even out: 0.80 of the time up to 560 workgroups of 64 rows (30 shapes,
+    // none slower), 1.05 and more from 600 on; two groups of 128 rows up to 512 0.93 (153 shapes, 1.04 at most)
+    if (causal && t >= 10 && f.w64 <= 560) return {2, 2};
+    if (causal && t >= 8 && f.w128 <= 2 * kComputeUnits) return {4, 2};
+    return {4, 1};
+}
+// The backward's two kernels.  Registers allow two groups of 96 and 128 rows, four of 64 at 64 channels.  Where the whole backward
+// is one launch, up to 256 tokens at 64 channels and 128 at 80, its two phases keep one group, whose bits it gives.
+Cut bwd_cut(const Fill& f, int d, bool causal)
+{
+    const int t = f.tiles;
+    if (t >= (d == 64 ? 5 : 3) && f.w64 <= kComputeUnits) return {2, d == 64 && t >= 15 ? 4 : 2};  // (four: 11 tiles equal, 13 2.5 % slower)
+    // 96 rows -> 128: dQ 40 x 400 10.6 -> 11.5 us, 24 x 785 15.2 -> 16.0, 12 x 1568 23.7 -> 24.6; dK/dV 11.3 -> 11.9, 16.4 -> 16.8, 26.0 -> 26.2; whole
+    // backward at 80 channels 0.98 of the time, causal 0.96
+    if (t >= 5 && f.w96 <= kComputeUnits) return {3, 2};
+    // (beyond it two groups lose: 24 x 1568 85 -> 99 us, 64 x 785 53 -> 60)
+    if (t >= 6 && f.w128 <= kComputeUnits) return {4, 2};
+    // causal: 0.83 of the time up to 600 workgroups of 64 rows (46 shapes, none slower by 3 %), up to 1.12 at 640
+    if (causal && d == 64 && t >= 8 && f.w64 <= 600) return {2, 2};
+    return {4, 1};
+}
+// calls f(nw, kg) with the cut's two numbers as compile-time tags; f builds what these lists hold
 template <typename F>
-int by_split(long long heads, int N, int min_tiles, int min_tiles4, F f)
+int by_cut(Cut c, F f)
 {
     constexpr std::integral_constant<int, 1> one{};
     constexpr std::integral_constant<int, 2> two{};
     constexpr std::integral_constant<int, 3> three{};
     constexpr std::integral_constant<int, 4> four{};
-    const int tiles = (N + 63) / 64;
-    if (tiles >= min_tiles && heads * tiles <= kComputeUnits) return tiles >= min_tiles4 ? f(two, four) : f(two, two);
-    if (tiles >= 16 && heads * ((N + 95) / 96) <= kComputeUnits) return f(three, four);
-    if (tiles >= 6 && heads * ((N + 127) / 128) <= kComputeUnits) return tiles >= 16 ? f(four, four) : f(four, two);
-    return f(four, one);
+    switch (8 * c.nw + c.kg) {
+        case 8 * 2 + 2: return f(two, two);
+        case 8 * 2 + 4: return f(two, four);
+        case 8 * 3 + 2: return f(three, two);
+        case 8 * 3 + 4: return f(three, four);
+        case 8 * 4 + 2: return f(four, two);
+        case 8 * 4 + 4: return f(four, four);
+        default: return f(four, one);
+    }
 }
 
 int fwd_impl(const void* q, const void* k, const void* v, void* o, float* lse, int B, int H, int N, int d, int packed,
@@ -358,14 +394,12 @@ int fwd_impl(const void* q, const void* k, const void* v, void* o, float* lse, i
             return launch_win_fwd<decltype(dim)::value, typename decltype(fmt)::type, decltype(causal)::value>(
                 qq, kk, vv, oo, lse, B, H, N, rs, scale, st);
         });
-    return by_split((long long)B * H, N, 2, 11, [&](auto nw, auto kg) {
+    return by_cut(fwd_cut(Fill((long long)B * H, N), d, var.causal), [&](auto nw, auto kg) {
         return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
-            // at 80 channels LDS holds two groups
-            constexpr bool D64 = decltype(dim)::value == 64;
-            constexpr int NW = D64 || decltype(nw)::value == 2 ? decltype(nw)::value : 4;
-            constexpr int KG = D64 ? decltype(kg)::value : std::min(decltype(kg)::value, 2);
-            return launch_fwd<decltype(dim)::value, NW, KG, typename decltype(fmt)::type,
-                      decltype(causal)::value>(qq, kk, vv, oo, lse, B, H, N, rs, scale, st);
+            constexpr int D = decltype(dim)::value, NW = decltype(nw)::value, KG = decltype(kg)::value;
+            if constexpr (D == 64 || (NW != 3 && KG <= 2))
+                return launch_fwd<D, NW, KG, typename decltype(fmt)::type, decltype(causal)::value>(qq, kk, vv, oo, lse, B, H, N, rs, scale, st);
+            else return AVION_EUNSUPPORTED;  // not a cut that fwd_cut gives
         });
     });
 }
@@ -409,15 +443,9 @@ int head_impl(const void* q, const void* k, const void* v, const void* o, const 
     });
 }
 
-int split_tiles(int d) { return d == 64 ? kHeadMaxN / 64 + 1 : BwdSmallCfg<80, 4>::MAX_N / 64 + 1; }
-
-// The backward's form of a cut: three blocks of rows become four, and more than two groups fit two blocks at 64
-// channels only (registers, LDS)
-template <int D, int NW_, int KG_>
-struct BwdCut {
-    static constexpr int NW = NW_ == 2 ? 2 : 4;
-    static constexpr int KG = D == 64 && NW == 2 ? KG_ : std::min(KG_, 2);
-};
+// whether bwd_cut gives this cut
+template <int D, int NW, int KG>
+constexpr bool kBwdCut = KG <= 2 || (D == 64 && NW == 2);
 
 // dQ in two blocks of queries per wavefront (avion_pair.h) on the full chip: 256-row workgroups, two to a compute unit, are
 // a coarse cut, so it is taken where the last round of them is well filled and the sequence is long enough for its
@@ -460,11 +488,13 @@ int dq_impl(const void* q, const void* k, const void* v, const void* o, const fl
         if (var.f16) return launch_dq_pair<F16>(qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
         return launch_dq_pair<Bf16>(qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
     }
-    return by_split((long long)B * H, N, split_tiles(d), 15, [&](auto nw, auto kg) {
+    return by_cut(bwd_cut(Fill((long long)B * H, N), d, var.causal), [&](auto nw, auto kg) {
         return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
-            using Cut = BwdCut<decltype(dim)::value, decltype(nw)::value, decltype(kg)::value>;
-            return launch_dq<decltype(dim)::value, Cut::NW, Cut::KG, typename decltype(fmt)::type,
-                      decltype(causal)::value, decltype(dim)::value == 80>(qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
+            constexpr int D = decltype(dim)::value, NW = decltype(nw)::value, KG = decltype(kg)::value;
+            if constexpr (kBwdCut<D, NW, KG>)
+                return launch_dq<D, NW, KG, typename decltype(fmt)::type, decltype(causal)::value, D == 80>(
+                    qq, kk, vv, oo, gg, lse, dqq, rowsc, B, H, N, rs, scale, st);
+            else return AVION_EUNSUPPORTED;
         });
     });
 }
@@ -486,11 +516,13 @@ int dkdv_impl(const void* q, const void* k, const void* v, const float* lse, con
     const raw16 *qq = static_cast<const raw16*>(q), *kk = static_cast<const raw16*>(k), *vv = static_cast<const raw16*>(v),
                *gg = static_cast<const raw16*>(dO);
     raw16 *dkk = static_cast<raw16*>(dk), *dvv = static_cast<raw16*>(dv);
-    return by_split((long long)B * H, N, split_tiles(d), 15, [&](auto nw, auto kg) {
+    return by_cut(bwd_cut(Fill((long long)B * H, N), d, var.causal), [&](auto nw, auto kg) {
         return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
-            using Cut = BwdCut<decltype(dim)::value, decltype(nw)::value, decltype(kg)::value>;
-            return launch_dkdv<decltype(dim)::value, Cut::NW, Cut::KG, typename decltype(fmt)::type,
-                      decltype(causal)::value>(qq, kk, vv, gg, rowsc, dkk, dvv, B, H, N, rs, scale, st);
+            constexpr int D = decltype(dim)::value, NW = decltype(nw)::value, KG = decltype(kg)::value;
+            if constexpr (kBwdCut<D, NW, KG>)
+                return launch_dkdv<D, NW, KG, typename decltype(fmt)::type, decltype(causal)::value>(qq, kk, vv, gg, rowsc, dkk, dvv, B, H,
+                                                                                                     N, rs, scale, st);
+            else return AVION_EUNSUPPORTED;
         });
     });
 }

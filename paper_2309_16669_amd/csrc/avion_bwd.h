@@ -26,7 +26,7 @@
 //
 // Small launches.  With KG > 1 a workgroup holds KG groups of NW wavefronts for the same 32*NW rows, each
 // of which walks its own share of the streamed tiles through its own two buffers; group 0 adds the
-// accumulators in a fixed order at the end (the rule and both sides' times stand at by_split in
+// accumulators in a fixed order at the end (the rule and both sides' times stand at bwd_cut in
 // avion_attn.hip).
 //
 // Template parameters of both kernels: head dim D, wavefronts per group NW, groups KG, element format E

@@ -34,7 +34,7 @@
 // and group 0 adds the others' accumulators and sums, rescaled to the larger reference, in a fixed
 // order at the end.  What bounds a launch that leaves compute units with one workgroup is the serial
 // chain of one wavefront per SIMD, which this shortens (the rule and both sides' times stand at
-// by_split in avion_attn.hip).
+// fwd_cut in avion_attn.hip).
 //
 // Template parameters: head dim D, wavefronts per group NW, groups KG, element format E (Bf16 or F16),
 // CAUSAL (query i sees keys 0..i; the reference m is then the maximum over the visible ones of the

@@ -30,7 +30,7 @@
 // causal 18.4 -> 15.5, 513 x 64 14.9 -> 11.1, 513 x 33 12.7 -> 8.5, 8 x 77 8.3 -> 8.1.  At 16384 x 77 causal, three
 // workgroups with dQ beside the scores (spills) 352, two 284.
 // Against two kernels of avion_bwd.h of one group each it was 0.60 to 0.99 of their time at 1 to 768 heads x 129..256 before
-// that; two kernels of two groups each (by_split's form for at most 256 64-row blocks) were faster by 0 to 4 % at 196..224
+// that; two kernels of two groups each (64-row blocks, two groups) were faster by 0 to 4 % at 196..224
 // tokens and 8 to 14 % at 240..256 below 96 heads.
 // dQ in 32 x 32 tiles after every fourth block (fewer barriers, longer chains): 226 at 3072 x 196.
 #pragma once

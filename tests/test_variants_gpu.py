@@ -256,7 +256,7 @@ def test_every_whole_head_instance_at_both_ends_of_its_lengths(blocks, causal, f
         test_whole_heads_match_the_oracle_and_the_two_phases(1, 3, N, f16, causal, False)
 
 
-# Cuts of small launches into blocks of 64, 96 and 128 rows with four groups (by_split): both sides of the lines in tiles, groups of
+# Cuts of small launches into blocks of 64, 96 and 128 rows with four groups (fwd_cut, bwd_cut): both sides of the lines in tiles, groups of
 # unequal and of no tiles (11 tiles in four groups: 3, 3, 3, 2; 13: 4, 4, 4, 1), ragged last rows and keys
 @pytest.mark.parametrize("B,H,N,f16,causal,packed", [
     (1, 3, 640, False, False, False), (1, 3, 641, True, False, True), (1, 2, 705, False, True, False), (1, 2, 833, False, False, True),
@@ -268,6 +268,36 @@ def test_small_launches_cut_into_four_groups(B, H, N, f16, causal, packed):
     w = si.small_workload(B, H, N, 64, seed=9700 + N)
     x = si.make_inputs(w, fmt="f16" if f16 else "bf16")
     check(w, x, run_ex(w, x, f16, causal, packed), f16, causal)
+
+
+# Cuts of launches around one and two workgroups per compute unit (fwd_cut, bwd_cut): 96 rows in two groups within one per
+# unit (forward from 6 tiles, backward from 5) and, forward, within two; causal 64 and 128 rows in two groups beyond one; both
+# sides of the lines in tiles (7, 8, 10) and workgroups.  Ragged last rows and keys, groups with a tile less.
+@pytest.mark.parametrize("B,H,N,d,f16,causal", [
+    (1, 43, 385, 64, False, False), (1, 43, 385, 64, True, True), (1, 43, 385, 80, False, True), (2, 26, 321, 64, False, False),
+    (1, 64, 384, 64, True, False), (1, 65, 385, 64, False, False), (2, 40, 448, 64, True, False), (1, 65, 512, 64, False, True),
+    (1, 52, 600, 64, False, False), (1, 53, 610, 64, False, True), (1, 56, 640, 64, True, True), (1, 57, 577, 64, False, True),
+    (1, 75, 577, 64, False, False), (2, 43, 620, 64, True, False), (3, 27, 639, 80, False, False)])
+def test_cuts_around_one_and_two_workgroups_per_compute_unit(B, H, N, d, f16, causal):
+    import torch
+    w = si.small_workload(B, H, N, d, seed=9750 + N + d)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    dt = torch.float16 if f16 else torch.bfloat16
+    x = {n: torch.randn(B, N, H, d, device="cuda", generator=gen).to(dt).view(torch.int16).cpu().numpy().view(np.uint16)
+         for n in ("q", "k", "v", "dO")}
+    out = run_ex(w, x, f16, causal, False)
+    for n in ("o", "lse", "dq", "dk", "dv"):
+        assert bool(torch.isfinite(out[n]).all()), n
+    if causal:
+        check(w, x, out, f16, causal)
+    else:
+        (gh.check_f16_against_oracle if f16 else gh.check_against_oracle)(w, x, out, [(0, 0), (B // 2, H // 2), (B - 1, H - 1)])
+
+
+# The running-maximum fallback where the last and where the first of two groups of 96 and of 128 rows overflows
+@pytest.mark.parametrize("H,N,sink", [(43, 385, 370), (43, 385, 40), (50, 600, 590), (50, 600, 40), (70, 448, 440)])
+def test_an_overflowing_group_of_two_redoes_the_block(H, N, sink):
+    test_a_group_whose_reference_overflows_redoes_the_block(H, N, sink)
 
 
 # dQ in two blocks per wavefront (by_pair): last workgroups of one and two blocks (shared by four and two wavefronts) to eight,
