@@ -447,22 +447,20 @@ int head_impl(const void* q, const void* k, const void* v, const void* o, const 
 template <int D, int NW, int KG>
 constexpr bool kBwdCut = KG <= 2 || (D == 64 && NW == 2);
 
-// dQ in two blocks of queries per wavefront (avion_pair.h) on the full chip: 256-row workgroups, two to a compute unit, are
-// a coarse cut, so it is taken where the last round of them is well filled and the sequence is long enough for its
-// prologue: the chip's share of blocks per compute unit, rounded up to whole rounds of 8, exceeds it by at most a fifth, and so
-// rounded in workgroups, of which a head's last may be short, by at most a quarter.  Measured, us, three
-// wavefronts per SIMD of one block -> this: 384 x 1568 409 -> 385, 64 x 3528 333 -> 316, 96 x 1200 71.9 -> 64.7, 96 x 2000
-// 169 -> 156, 128 x 1000 67.2 -> 64.3; on the other side of the lines 96 x 1568 (2.3 workgroups each) 112 -> 126, 64 x 1200 (1.2)
-// 51 -> 55, 48 x 2000 (1.5) 88 -> 92, 384 x 785 126 -> 129, and, within a fifth in blocks, where short workgroups open another
-// round, 52 x 1025 (0.84 in blocks, 1.02 in workgroups) 34.2 -> 46.6, 44 x 1300 39.3 -> 53.1, 38 x 1568 45.4 -> 61.5, 33 x 1800
-// 51.8 -> 70.7, 68 x 1800 (1.89, 2.12) 99 -> 113, 173 x 1300 (3.46, 4.05) 131 -> 136; from 1.2 to 1.25 in workgroups 0.96 of the time in the
-// mean of 101 shapes (1.01 at most), from 1.3 to 1.36 0.975 with one in six slower.
+// dQ in two blocks of queries per wavefront (avion_pair.h), for launches beyond one workgroup of 128 rows per compute unit.  Its
+// workgroups take 256 rows, and a compute unit does one in the time of 1.75 of avion_dq_kernel's 128-row ones, whether it has
+// one at a time or two; both launches end with the unit that has most.  So it is taken where its share of workgroups per unit, rounded
+// up, is at most 7/12 of the other kernel's.  Measured over 1100 shapes, time over avion_dq_kernel's by the two shares: 1 of 2 0.92 (341 shapes),
+// 2 of 4 0.86 (121), 3 of 6 0.91, 4 of 7 0.96, 5 of 9 0.95, 7 of 12 0.96; on the other side 2 of 2 1.43, 2 of 3 1.10, 3 of 4 1.17, 3 of 5 1.03, 5 of 8
+// 1.00, 6 of 10 0.98, 7 of 11 1.03.  A head's short last workgroup counts as one.  Us: 32 x 3136 152.8 -> 121.5, 64 x 1568 81.4 -> 67.8, 24 x
+// 1568 40.5 -> 36.3, 80 x 1200 66.2 -> 56.1, 384 x 1568 400 -> 363.  Below 500 tokens (700 from five shares on) its longer prologue
+// takes what it gives: at 400 0.97 to 1.04 of the time, at 500 to 700 and six shares 1.00.
 bool by_pair(long long heads, int N, int d, Variant var)
 {
-    if (d != 64 || var.causal || N < 1000 || heads * ((N + 127) / 128) <= kComputeUnits) return false;
-    const int nb = (N + 31) / 32;
-    const long long blocks = heads * nb, chip = kComputeUnits * kPairBlocks, wgs = heads * ((nb + kPairBlocks - 1) / kPairBlocks);
-    return 5 * ((blocks + chip - 1) / chip) * chip <= 6 * blocks && 4 * ((wgs + kComputeUnits - 1) / kComputeUnits) * chip <= 5 * blocks;
+    const long long wgs = heads * ((N + 127) / 128), pair_wgs = heads * (((N + 31) / 32 + kPairBlocks - 1) / kPairBlocks);
+    if (d != 64 || var.causal || wgs <= kComputeUnits) return false;
+    const long long share = (wgs + kComputeUnits - 1) / kComputeUnits, pair_share = (pair_wgs + kComputeUnits - 1) / kComputeUnits;
+    return N >= (share <= 4 ? 500 : 700) && 12 * pair_share <= 7 * share;
 }
 
 int dq_impl(const void* q, const void* k, const void* v, const void* o, const float* lse, const void* dO, void* dq, int B,

@@ -324,6 +324,14 @@ def test_dq_in_pairs_of_blocks(B, H, N, f16, packed):
     (gh.check_f16_against_oracle if f16 else gh.check_against_oracle)(w, x, out, slices)
 
 
+# The shortest sequences that take it, with one or two and with several workgroups per compute unit, and the ones below them
+@pytest.mark.parametrize("B,H,N,f16,packed", [
+    (16, 5, 500, False, False), (16, 5, 499, True, False), (17, 5, 540, True, True), (80, 3, 700, False, False), (80, 3, 699, False, True),
+    (120, 2, 736, True, False)])
+def test_dq_in_pairs_of_blocks_at_its_shortest(B, H, N, f16, packed):
+    test_dq_in_pairs_of_blocks(B, H, N, f16, packed)
+
+
 # On the other side of by_pair's lines dQ is avion_dq_kernel's, whose bits do not depend on the other heads of the launch; the
 # pair form adds up a last block that wavefronts share in another order.  Heads whose short last workgroup would open another
 # round have the former's bits (those of a launch that fills the chip badly in blocks too), heads within the lines have not.
