@@ -14,6 +14,7 @@
 #include <mutex>
 
 #include "avion_bwd.h"
+#include "avion_flow.h"
 #include "avion_fwd.h"
 #include "avion_head.h"
 #include "avion_ln.h"
@@ -192,6 +193,24 @@ int launch_dkdv(const raw16* q, const raw16* k, const raw16* v, const raw16* dO,
     hipLaunchKernelGGL((avion_dkdv_kernel<D, NW, KG, E, CAUSAL>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, st, q, k, v, dO, rowsc, dk,
                        dv, H, N, rs.qkv, rs.o, nkb, (int)nblocks, scale * kLog2e, scale);
     return end_launch("launch avion_dkdv_kernel");
+}
+
+template <int NW, typename E>
+int launch_dkdv_flow(const raw16* q, const raw16* k, const raw16* v, const raw16* dO, const float* rowsc, raw16* dk, raw16* dv,
+                     int B, int H, int N, Strides rs, float scale, hipStream_t st)
+{
+    constexpr int LDS_BYTES = 2 * FlowRing<NW>::LDS_BYTES;
+    static std::atomic<bool> lds_allowed{false};
+    const hipError_t attr = allow_lds(avion_dkdv_flow_kernel<NW, E>, LDS_BYTES, lds_allowed);
+    if (attr != hipSuccess) return hip_fail(attr, "hipFuncSetAttribute(dkdv_flow)");
+    const int nkb = (N + 32 * NW - 1) / (32 * NW);
+    const long long nblocks = (long long)nkb * B * H;
+    unsigned grid;
+    if (!grid_for(nblocks, &grid)) return AVION_EUNSUPPORTED;
+    begin_launch();
+    hipLaunchKernelGGL((avion_dkdv_flow_kernel<NW, E>), dim3(grid), dim3(NW * 128), LDS_BYTES, st, q, k, v, dO, rowsc, dk, dv, H, N, rs.qkv,
+                       rs.o, nkb, (int)nblocks, scale * kLog2e, scale);
+    return end_launch("launch avion_dkdv_flow_kernel");
 }
 
 template <int D, int NW, typename E, bool CAUSAL>
@@ -497,6 +516,14 @@ int dq_impl(const void* q, const void* k, const void* v, const void* o, const fl
     });
 }
 
+// dK and dV by the pipelined kernel (avion_flow.h): always two groups.  Its time over avion_dkdv_kernel's, 400 shapes: 64 rows 0.97 (5 tiles) to
+// 0.88 (14) against two groups and 0.89 to 0.93 against four; 96 rows 1.11 at 5 tiles, 0.98 (1.02 at most) at 6 to 8, 0.97 at 9, 0.91 at 30 and
+// more; 128 rows 1.03 at 6 to 8 tiles, 0.99 at 12 to 14, 0.98 at 15, 0.95 at 30 (its longer start).
+bool by_flow(Cut c, const Fill& f, int d, Variant var)
+{
+    return d == 64 && !var.causal && c.kg > 1 && f.tiles >= (c.nw == 2 ? 0 : c.nw == 3 ? 8 : 15);
+}
+
 int dkdv_impl(const void* q, const void* k, const void* v, const float* lse, const void* dO, void* dk, void* dv, int B,
               int H, int N, int d, int packed, Variant var, float scale, const void* workspace, size_t workspace_bytes,
               void* stream)
@@ -514,10 +541,22 @@ int dkdv_impl(const void* q, const void* k, const void* v, const float* lse, con
     const raw16 *qq = static_cast<const raw16*>(q), *kk = static_cast<const raw16*>(k), *vv = static_cast<const raw16*>(v),
                *gg = static_cast<const raw16*>(dO);
     raw16 *dkk = static_cast<raw16*>(dk), *dvv = static_cast<raw16*>(dv);
-    return by_cut(bwd_cut(Fill((long long)B * H, N), d, var.causal), [&](auto nw, auto kg) {
+    const Fill fill((long long)B * H, N);
+    const Cut cut = bwd_cut(fill, d, var.causal);
+    if (by_flow(cut, fill, d, var)) {
+        auto flow = [&](auto nw) {
+            constexpr int NW = decltype(nw)::value;
+            if (var.f16) return launch_dkdv_flow<NW, F16>(qq, kk, vv, gg, rowsc, dkk, dvv, B, H, N, rs, scale, st);
+            return launch_dkdv_flow<NW, Bf16>(qq, kk, vv, gg, rowsc, dkk, dvv, B, H, N, rs, scale, st);
+        };
+        if (cut.nw == 2) return flow(std::integral_constant<int, 2>{});
+        if (cut.nw == 3) return flow(std::integral_constant<int, 3>{});
+        return flow(std::integral_constant<int, 4>{});
+    }
+    return by_cut(cut, [&](auto nw, auto kg) {
         return by_variant(var, d, [&](auto dim, auto fmt, auto causal) {
             constexpr int D = decltype(dim)::value, NW = decltype(nw)::value, KG = decltype(kg)::value;
-            if constexpr (kBwdCut<D, NW, KG>)
+            if constexpr (kBwdCut<D, NW, KG> && (D != 64 || NW != 2 || decltype(causal)::value))
                 return launch_dkdv<D, NW, KG, typename decltype(fmt)::type, decltype(causal)::value>(qq, kk, vv, gg, rowsc, dkk, dvv, B, H,
                                                                                                      N, rs, scale, st);
             else return AVION_EUNSUPPORTED;

@@ -138,6 +138,11 @@ DEVINL void avion_dq_body(char* smem, const raw16* __restrict__ q, const raw16* 
             float* ws = rowsc + (long)bh * 2 * npad;
             ws[qrow] = qrow < N ? lc : INFINITY;
             ws[npad + qrow] = qrow < N ? -dl : 0.f;
+            // blocks of 96 rows may end half way through the last 64
+            if (NW % 2 == 1 && q0 < N && q0 + 32 >= N && q0 % 64 == 0) {
+                ws[qrow + 32] = INFINITY;
+                ws[npad + qrow + 32] = 0.f;
+            }
         }
     }
     const float nlc = -lc;

@@ -80,15 +80,16 @@ struct PairLane {
 #pragma unroll
         for (int i = 0; i < 2; ++i) { tr[i] += by; asm volatile("" : "+v"(tr[i])); }
     }
-    DEVINL frag8 natural(int of_v, int hk, int ks) const
+    // tensor: where its tile lies in the buffer
+    DEVINL frag8 natural(int tensor, int hk, int ks) const
     {
         typedef const __attribute__((address_space(3))) frag8* ptr;
-        return *(ptr)(nat[ks & 1] + (of_v * PairRing::TILE + hk * 4096 + (ks >> 1) * 256));
+        return *(ptr)(nat[ks & 1] + (tensor + hk * 4096 + (ks >> 1) * 256));
     }
-    DEVINL frag8 transposed(int ct, int step) const
+    DEVINL frag8 transposed(int tensor, int ct, int step) const
     {
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tr[0] + (step * 2048 + ct * 256)));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tr[1] + (step * 2048 + ct * 256)));
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tr[0] + (tensor + step * 2048 + ct * 256)));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tr[1] + (tensor + step * 2048 + ct * 256)));
         const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
         return as_frag8(u32x4{l2[0], l2[1], h2[0], h2[1]});
     }
@@ -193,11 +194,11 @@ avion_dq_pair_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, c
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             x.s = E::mfma(ln.natural(0, hk, ks), x.qf[ks], x.s);
-            x.dp = E::mfma(ln.natural(1, hk, ks), x.gf[ks], ks == 0 ? f32x16_zero() : x.dp);
+            x.dp = E::mfma(ln.natural(PairRing::TILE, hk, ks), x.gf[ks], ks == 0 ? f32x16_zero() : x.dp);
         }
         grad(x, 0, 16);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x.acc[i % 2] = E::mfma(ln.transposed(i % 2, 2 * hk + i / 2), as_frag8(x.df[i / 2]), x.acc[i % 2]);
+        for (int i = 0; i < 4; ++i) x.acc[i % 2] = E::mfma(ln.transposed(0, i % 2, 2 * hk + i / 2), as_frag8(x.df[i / 2]), x.acc[i % 2]);
     };
     const int nfast = N / BN;
     if (sp.mine == 2) {
@@ -207,12 +208,12 @@ avion_dq_pair_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, c
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             A.s = E::mfma(ln.natural(0, 0, ks), A.qf[ks], ks == 0 ? f32x16_zero() : A.s);
-            A.dp = E::mfma(ln.natural(1, 0, ks), A.gf[ks], ks == 0 ? f32x16_zero() : A.dp);
+            A.dp = E::mfma(ln.natural(PairRing::TILE, 0, ks), A.gf[ks], ks == 0 ? f32x16_zero() : A.dp);
         }
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             fk[ks] = ln.natural(0, 0, ks);
-            fv[ks] = ln.natural(1, 0, ks);
+            fv[ks] = ln.natural(PairRing::TILE, 0, ks);
         }
         // One phase: x's vector work beside y's products.  hk: the half tile y's scores are of; hkn: the one after it, to
         // whose buffer the addresses move by `by`.  Natural operands are requested two steps ahead.
@@ -222,11 +223,11 @@ avion_dq_pair_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, c
                 __builtin_amdgcn_sched_barrier(0);
                 if (ks == 2 && by != 0) ln.move_nat(by);
                 y.acc[ks % 2] = E::mfma(kf[ks], as_frag8(y.df[ks / 2]), y.acc[ks % 2]);
-                if (decltype(first)::value) kf[ks] = ln.transposed(ks % 2, 2 * hk + ks / 2);
+                if (decltype(first)::value) kf[ks] = ln.transposed(0, ks % 2, 2 * hk + ks / 2);
                 y.s = E::mfma(fk[ks & 1], y.qf[ks], ks == 0 ? f32x16_zero() : y.s);
                 y.dp = E::mfma(fv[ks & 1], y.gf[ks], ks == 0 ? f32x16_zero() : y.dp);
                 fk[ks & 1] = ln.natural(0, ks < 2 ? hk : hkn, (ks + 2) % 4);
-                fv[ks & 1] = ln.natural(1, ks < 2 ? hk : hkn, (ks + 2) % 4);
+                fv[ks & 1] = ln.natural(PairRing::TILE, ks < 2 ? hk : hkn, (ks + 2) % 4);
                 grad(x, 4 * ks, 4 * ks + 4);
                 __builtin_amdgcn_sched_barrier(0);
             }

@@ -294,6 +294,18 @@ def test_cuts_around_one_and_two_workgroups_per_compute_unit(B, H, N, d, f16, ca
         (gh.check_f16_against_oracle if f16 else gh.check_against_oracle)(w, x, out, [(0, 0), (B // 2, H // 2), (B - 1, H - 1)])
 
 
+# dK and dV of the pipelined form (by_flow): 64, 96 and 128 rows, both sides of the lines in tiles (8, 15), one tile per group to
+# many, groups with a tile less (odd numbers of tiles: its zero rows must add nothing), last tiles of one unit and two, keys past the end
+@pytest.mark.parametrize("B,H,N,f16,packed", [
+    (1, 3, 257, False, False), (2, 2, 320, True, True), (1, 2, 385, False, True), (1, 3, 833, True, False), (1, 2, 1025, False, False),
+    (1, 28, 449, False, False), (1, 28, 448, True, False), (1, 30, 481, True, True), (1, 16, 1030, False, True), (1, 9, 1569, False, False),
+    (1, 30, 897, False, False), (1, 29, 896, False, True), (1, 20, 1250, True, False), (1, 24, 1024, False, False)])
+def test_pipelined_dk_dv_of_small_launches(B, H, N, f16, packed):
+    w = si.small_workload(B, H, N, 64, seed=9770 + N)
+    x = si.make_inputs(w, fmt="f16" if f16 else "bf16")
+    check(w, x, run_ex(w, x, f16, False, packed), f16, False)
+
+
 # The running-maximum fallback where the last and where the first of two groups of 96 and of 128 rows overflows
 @pytest.mark.parametrize("H,N,sink", [(43, 385, 370), (43, 385, 40), (50, 600, 590), (50, 600, 40), (70, 448, 440)])
 def test_an_overflowing_group_of_two_redoes_the_block(H, N, sink):
