@@ -306,6 +306,18 @@ DEVINL void load_to_lds16_x4(const RawBuffer& b0, const RawBuffer& b1, const Raw
         : "memory", "m0", "scc");
 }
 
+// Two such loads
+template <unsigned step>
+DEVINL void load_to_lds16_x2(const RawBuffer& b0, const RawBuffer& b1, unsigned lds_addr, unsigned v0, unsigned v1)
+{
+    asm volatile(
+        "s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %3, 0 offen lds\n\t"
+        "s_add_u32 m0, m0, %5\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %4, 0 offen lds"
+        :
+        : "s"(lds_addr), "v"(v0), "v"(v1), "s"(b0.words), "s"(b1.words), "i"(step)
+        : "memory", "m0", "scc");
+}
+
 // Byte offset, relative to the tile's first row, that `lane` fetches for 1 KB block `blk` of a padded
 // LDS tile (row stride tile_stride<D>(), D/8 data chunks of 16 bytes per row, the rest padding): the
 // block holds chunks 64*blk .. 64*blk+63 of the tile in row-major order.  Lanes that land on a pad
@@ -351,6 +363,71 @@ DEVINL frag8 tr_frag(const char* tile, int stride, int lane_off, int ct, int ste
     return as_frag8(r);
 }
 
+// The other layout of a tile (64 channels): rows of 128 bytes without padding, four rows by four 16-byte chunks at a time, the
+// four chunks permuted by a XOR with bits of the row number.  A 1 KB block is 8 rows.  16 consecutive rows at one chunk, and 4
+// consecutive rows at 4 chunks (a transposing read's half wavefront), hit distinct banks.
+// Byte offset of chunk `ch` of row `row`:
+DEVINL unsigned quad_at(int row, int ch) { return (row >> 2) * 512 + (ch >> 2) * 256 + (row & 3) * 64 + (((ch & 3) ^ (row >> 2 & 3)) * 16); }
+// What `lane` fetches for 1 KB block `blk` (8 rows) of such a tile: the chunk that lies at 16 * lane
+DEVINL unsigned quad_voff(int blk, int lane, unsigned row_bytes)
+{
+    const unsigned row = 8 * blk + lane / 32 * 4 + lane / 4 % 4, ch = lane / 16 % 2 * 4 + ((lane ^ (row >> 2)) & 3);
+    return row * row_bytes + ch * 16;
+}
+// This lane's addresses in such a tile, whose buffer they move with: the XOR touches two bits of the chunk, of which a lane's
+// reads vary one, so natural fragments have two (by the step's low bit) and transposed ones two (by which four of their eight
+// tokens); the rest is in the instruction's offset.
+struct QuadLane {
+    unsigned nat[2], tr[2];
+    DEVINL QuadLane(int lane, unsigned buf)
+    {
+        const int l32 = lane % 32, g = lane / 32, G = lane >> 4, j = lane & 15, r = 4 * (G >> 1) + (j >> 2), c = 2 * (G & 1) + ((j & 3) >> 1);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            nat[i] = buf + quad_at(l32, 2 * i + g);
+            tr[i] = buf + quad_at(r + 8 * i, c) + (j & 1) * 8;
+        }
+    }
+    // (opaque, or the compiler adds the uniform parts first and each address once more)
+    DEVINL void move_nat(int by)
+    {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) { nat[i] += by; asm volatile("" : "+v"(nat[i])); }
+    }
+    DEVINL void move_tr(int by)
+    {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) { tr[i] += by; asm volatile("" : "+v"(tr[i])); }
+    }
+    // tensor: where its tile lies in the buffer
+    DEVINL frag8 natural(int tensor, int hk, int ks) const
+    {
+        typedef const __attribute__((address_space(3))) frag8* ptr;
+        return *(ptr)(nat[ks & 1] + (tensor + hk * 4096 + (ks >> 1) * 256));
+    }
+    // the same at a run-time (uniform) place `at`: the row of the 32 rows at 128 bytes a row, and the tensor
+    DEVINL frag8 natural_row(int at, int ks) const
+    {
+        typedef const __attribute__((address_space(3))) frag8* ptr;
+        return *(ptr)(nat[ks & 1] + at + (ks >> 1) * 256);
+    }
+    DEVINL frag8 transposed_row(int at, int ct, int half) const
+    {
+        const unsigned lo_at = tr[0] + at, hi_at = tr[1] + at;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lo_at + (half * 2048 + ct * 256)));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(hi_at + (half * 2048 + ct * 256)));
+        const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+        return as_frag8(u32x4{l2[0], l2[1], h2[0], h2[1]});
+    }
+    DEVINL frag8 transposed(int tensor, int ct, int step) const
+    {
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tr[0] + (tensor + step * 2048 + ct * 256)));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tr[1] + (tensor + step * 2048 + ct * 256)));
+        const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+        return as_frag8(u32x4{l2[0], l2[1], h2[0], h2[1]});
+    }
+};
+
 // v_mfma_f32_16x16x32: A (16 x 32) and B (32 x 16) hold row / column l%16 and 8 contraction slots of lane
 // group G = l/16, the accumulator column l%16 and rows 4G..4G+3.  Slots 0..3 of group G stand for the
 // 32-step's tokens 4G..4G+3, slots 4..7 for 16+4G..16+4G+3.
@@ -364,6 +441,16 @@ DEVINL frag8 tr16_frag(const char* tile, int stride, int lane, int c0, int step)
     const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
     const u32x4 r = {l2[0], l2[1], h2[0], h2[1]};
     return as_frag8(r);
+}
+// the same from a tile in quad_at's layout
+DEVINL frag8 quad_tr16(unsigned tile, int lane, int c0, int step)
+{
+    const int G = lane >> 4, j = lane & 15;
+    const unsigned p = tile + quad_at(4 * G + (j >> 2), c0 / 8 + ((j & 3) >> 1)) + (j & 1) * 8 + step * 4096;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 2048));
+    const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
+    return as_frag8(u32x4{l2[0], l2[1], h2[0], h2[1]});
 }
 // 16 x 16 tile of transposed accumulators: lane = row l%16 of the result (`row` points at its 16 channels),
 // 4 channels of group G

@@ -35,12 +35,11 @@ struct FlowRing {
         ds = sb.words;
         ra = (unsigned)(rs_a * 2);
         rb = (unsigned)(rs_b * 2);
-        // the chunk at offset 16 * lane of 8 rows, by the block's parity (which four rows they are decides the permutation)
+        // by the block's parity, less its own rows (which four rows they are decides the permutation)
 #pragma unroll
         for (int odd = 0; odd < 2; ++odd) {
-            const unsigned row = lane / 32 * 4 + lane / 4 % 4, ch = lane / 16 % 2 * 4 + ((lane ^ (2 * odd + lane / 32)) & 3);
-            va[odd] = row * ra + ch * 16;
-            vb[odd] = row * rb + ch * 16;
+            va[odd] = quad_voff(odd, lane, ra) - 8 * odd * ra;
+            vb[odd] = quad_voff(odd, lane, rb) - 8 * odd * rb;
         }
         vs = lane * 4;
         smem_addr = lds_address(smem) + wave * 1024;
@@ -103,7 +102,7 @@ avion_dkdv_flow_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k,
     const int per = (ntiles + KG - 1) / KG, t0 = grp * per;
     char* mine = smem + grp * Ring::LDS_BYTES;
     const Ring ring(q + head_off, rs, dO + head_off_o, rs_o, N, rowsc + (long)bh * 2 * npad, npad, mine, wave, lane);
-    PairLane ln(lane, lds_address(mine));
+    QuadLane ln(lane, lds_address(mine));
     ring.fetch(t0, 0);
     // K and V fragments (B operands: lane = key); keys past the end are computed and not stored
     frag8 kf[KS], vf[KS];

@@ -16,7 +16,7 @@
 // partial sums in memory.  avion_dq_body's TILE16 form takes the same operands in the same order, so the
 // backward's two phases give this kernel's bits.
 //
-// 8 wavefronts (129..256 tokens): 146 KB of LDS, one workgroup per compute unit, so nothing else covers its
+// 8 wavefronts (129..256 tokens): 134 KB of LDS, one workgroup per compute unit, so nothing else covers its
 // loads.  It walks the heads: K's tile is free once the operands are in registers, 64 rows of Q and dO once
 // their two blocks are done, and the next head's rows are fetched into them right then, without registers
 // (LDS-direct loads); O, V and LSE follow in registers.
@@ -29,6 +29,10 @@
 // x 64 244 -> 216, x 40 205 -> 157, 4000 x 128 117 -> 114; few heads: 8 x 200 15.0 -> 14.1, 384 x 200 32.8 -> 30.5, 768 x 77
 // causal 18.4 -> 15.5, 513 x 64 14.9 -> 11.1, 513 x 33 12.7 -> 8.5, 8 x 77 8.3 -> 8.1.  At 16384 x 77 causal, three
 // workgroups with dQ beside the scores (spills) 352, two 284.
+// Tiles in rows of 144 bytes and descriptors made per request -> quad_at's layout (a block's offset is an addition, a fragment's
+// address a register and the instruction's offset) and descriptors once per head: 3072 x 196 180 -> 166 (3.7 TB/s), x 160
+// 130 -> 121, x 130 114 -> 104, x 224 196 -> 184, x 256 225 -> 218, 8000 x 200 causal 416 -> 394, 16384 x 77 causal 267 -> 261,
+// x 64 221 -> 216, x 40 153 -> 146; 8 x 200 14.0 -> 12.6, 384 x 200 29.0 -> 27.7, 768 x 128 causal 26.0 -> 25.0, the smallest equal.
 // Against two kernels of avion_bwd.h of one group each it was 0.60 to 0.99 of their time at 1 to 768 heads x 129..256 before
 // that; two kernels of two groups each (64-row blocks, two groups) were faster by 0 to 4 % at 196..224
 // tokens and 8 to 14 % at 240..256 below 96 heads.
@@ -39,13 +43,11 @@
 template <int NW, int NB>
 struct HeadCfg {
     static constexpr int D = 64, NT = NW * 64, MAX_N = 32 * NW;
-    static constexpr int STRIDE = tile_stride<D>();
     static constexpr int DS_STRIDE = 72;                 // 32 queries of 2 bytes, padded so that 32 rows hit distinct banks
     // one workgroup per compute unit: it walks several heads
     static constexpr bool WALK = NW == 8;
     static constexpr int ROWS = WALK ? MAX_N : 32 * NB;
-    static constexpr int BLOCKS = (ROWS * STRIDE + 1023) / 1024;  // 1 KB blocks of one tensor
-    static constexpr int TILE_BYTES = BLOCKS * 1024;     // Q, dO, K: all rows of the head
+    static constexpr int TILE_BYTES = ROWS * 128;        // Q, dO, K: all rows of the head (quad_at)
     static constexpr int DS_BYTES = ROWS * DS_STRIDE;    // one key per row
     // dS lies where K was, unless the next head's K is on its way there
     static constexpr int OFF_G = TILE_BYTES, OFF_K = 2 * TILE_BYTES, OFF_DS = WALK ? 3 * TILE_BYTES : OFF_K,
@@ -71,8 +73,10 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
                       int nheads, float cs, float scale)
 {
     using Cfg = HeadCfg<NW, NB>;
-    constexpr int D = 64, KS = 4, CT = 2, STRIDE = Cfg::STRIDE, QT = 8 / NW;  // QT: 16-query tiles of dQ per wavefront
-    constexpr int SUB_BLOCKS = 64 * STRIDE / 1024;                            // 1 KB blocks of 64 rows of one tensor
+    constexpr int D = 64, KS = 4, CT = 2, QT = 8 / NW;  // QT: 16-query tiles of dQ per wavefront
+    // Masked instances of 6 to 8 blocks need up to 44 bytes of scratch with the early request: 8000 heads x 200 435 us instead of
+    // 394, 1024 x 256 70.1 instead of 61.4.  The other walking instances do not: behind it, 3072 x 196 174 instead of 166.
+    constexpr bool EARLY_TR = Cfg::EARLY_TR && !(CAUSAL && Cfg::WALK && NB >= 6);
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, lane = tid % 64, l32 = lane % 32, g = lane / 32;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -80,33 +84,37 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
     const int k0 = wave * 32;  // first key, and for the per-query scalars first query, of this wavefront
     const int nslots = (N + 63) / 64;
     const bool wave_active = k0 < N;
-    const char *qt = smem, *gt = smem + Cfg::OFF_G, *kt = smem + Cfg::OFF_K;
     char* ds = smem + Cfg::OFF_DS;
     float* sc = reinterpret_cast<float*>(smem + Cfg::OFF_SC);
     const unsigned lds0 = lds_address(smem);
     const int row_in = min(k0 + l32, N - 1);
-    const int tr_off = tr_lane_offset(lane, STRIDE);
+    const QuadLane ln(lane, lds0);
     const int c0 = 16 * (wave % 4), q16 = NW == 8 ? 16 * (wave / 4) : 0;  // this wavefront's dQ tile(s)
 
     auto head_off = [&](int bh) { return (long)(bh / H) * N * rs + (long)(bh % H) * D; };
     auto head_off_o = [&](int bh) { return (long)(bh / H) * N * rs_o + (long)(bh % H) * D; };
-    // 1 KB blocks dealt round robin to the wavefronts; rows past the end arrive as zeros
-    auto fetch_k = [&](int bh) {
-        const RawBuffer buf(k + head_off(bh), slice_bytes(rs, N, D));
-        for (int idx = wave; idx < (Cfg::WALK ? nslots * SUB_BLOCKS : Cfg::BLOCKS); idx += NW)
-            load_to_lds16(buf, __builtin_amdgcn_readfirstlane(lds0 + Cfg::OFF_K + idx * 1024),
-                          padded_block_voff<D>(idx, lane, (unsigned)(rs * 2)));
+    // Wavefront w fetches 1 KB blocks w, w + NW, ... of a tensor; rows past the end arrive as zeros.  The descriptors are made once per
+    // head and a block's offset is an addition: with 9-chunk rows (a division per block) and descriptors per call the requests
+    // took 13 % of a wavefront's time at 196 tokens.
+    struct Fetch {
+        u32x4 q, g, k;
     };
-    // 64 rows of Q and of dO (slot), or all of them
-    auto fetch_slot = [&](int bh, int slot) {
-        constexpr int SUB_BLOCKS = Cfg::WALK ? 64 * STRIDE / 1024 : Cfg::BLOCKS;
-        const RawBuffer qb(q + head_off(bh), slice_bytes(rs, N, D)), gb(dO + head_off_o(bh), slice_bytes(rs_o, N, D));
-        for (int i = wave; i < 2 * SUB_BLOCKS; i += NW) {
-            const bool of_q = i < SUB_BLOCKS;
-            const int idx = slot * SUB_BLOCKS + (of_q ? i : i - SUB_BLOCKS);
-            load_to_lds16(pick(of_q, qb, gb), __builtin_amdgcn_readfirstlane(lds0 + (of_q ? 0 : Cfg::OFF_G) + idx * 1024),
-                          padded_block_voff<D>(idx, lane, (unsigned)((of_q ? rs : (long)rs_o) * 2)));
-        }
+    const unsigned voff = quad_voff(wave, lane, (unsigned)(rs * 2)), voff_o = quad_voff(wave, lane, (unsigned)(rs_o * 2));
+    auto fetch_of = [&](int bh) {
+        const long off = head_off(bh), off_o = head_off_o(bh);
+        return Fetch{RawBuffer(q + off, slice_bytes(rs, N, D)).words, RawBuffer(dO + off_o, slice_bytes(rs_o, N, D)).words,
+                     RawBuffer(k + off, slice_bytes(rs, N, D)).words};
+    };
+    const unsigned row_step = 8 * NW * (unsigned)(rs * 2), row_step_o = 8 * NW * (unsigned)(rs_o * 2);  // from block w to w + NW
+    constexpr int TURNS = Cfg::ROWS / (8 * NW);
+    const int turns = Cfg::WALK ? nslots : TURNS;
+    const unsigned lds_w = lds0 + wave * 1024;
+    auto fetch_k = [&](const Fetch& f) {
+        for (int i = 0; i < turns; ++i) load_to_lds16(RawBuffer(f.k), lds_w + Cfg::OFF_K + i * NW * 1024, voff + i * row_step);
+    };
+    // the i-th blocks of Q and of dO (walking workgroups: 64 rows)
+    auto fetch_rows = [&](const Fetch& f, int i) {
+        load_to_lds16_x2<Cfg::OFF_G>(RawBuffer(f.q), RawBuffer(f.g), lds_w + i * NW * 1024, voff + i * row_step, voff_o + i * row_step_o);
     };
     frag8 vf[KS], of[KS];
     float lse_in;
@@ -125,8 +133,11 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
     // Walking workgroups take every gridDim-th head; the others one head each, neighbours on one XCD.
     int bh = Cfg::WALK ? (int)blockIdx.x : xcd_local_id(blockIdx.x, nheads);
     if (bh < 0 || bh >= nheads) return;
-    fetch_k(bh);
-    for (int slot = 0; slot < (Cfg::WALK ? nslots : 1); ++slot) fetch_slot(bh, slot);
+    {
+        const Fetch f = fetch_of(bh);
+        fetch_k(f);
+        for (int i = 0; i < turns; ++i) fetch_rows(f, i);
+    }
     load_v(bh);
     load_o(bh);
 
@@ -134,6 +145,7 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
         const int next = bh + gridDim.x;
         const bool more = Cfg::WALK && next < nheads;
         const long off = head_off(bh);
+        const Fetch ahead = fetch_of(more ? next : bh);
         hold(vf);
         hold(of);
         asm volatile("" : "+v"(lse_in));
@@ -145,10 +157,10 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
             float part = 0.f;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                const frag8 gf = nat_frag(gt, STRIDE, k0 + l32, ks, g);
+                const frag8 gf = ln.natural_row(Cfg::OFF_G + k0 * 128, ks);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) part = fmaf(E::widen(of[ks], e), E::widen(gf, e), part);
-                kf[ks] = nat_frag(kt, STRIDE, k0 + l32, ks, g);
+                kf[ks] = ln.natural_row(Cfg::OFF_K + k0 * 128, ks);
             }
             const float dl = both_halves_sum(part);
             const int row = k0 + l32;
@@ -159,7 +171,7 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
         }
         // K^T of this wavefront's dQ tiles: 16 channels, all keys
 #pragma unroll
-        for (int s = 0; s < NB; ++s) ktf[s] = tr16_frag(kt, STRIDE, lane, c0, s);
+        for (int s = 0; s < NB; ++s) ktf[s] = quad_tr16(lds0 + Cfg::OFF_K, lane, c0, s);
         f32x16 dka[CT], dva[CT];
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
@@ -168,7 +180,7 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
         }
         lds_barrier();  // the scalars of every query are in LDS, the K tile is no longer read
         if (more) {
-            fetch_k(next);
+            fetch_k(ahead);
             load_o(next);
         }
 
@@ -213,8 +225,8 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
             if constexpr (MASK) s = query_mask_block(query_base, g, k0 + l32);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                const frag8 aq = nat_frag(qt, STRIDE, query_base + l32, ks, g);
-                const frag8 ag = nat_frag(gt, STRIDE, query_base + l32, ks, g);
+                const frag8 aq = ln.natural_row(query_base * 128, ks);
+                const frag8 ag = ln.natural_row(Cfg::OFF_G + query_base * 128, ks);
                 s = E::mfma(aq, kf[ks], ks == 0 && !MASK ? f32x16_zero() : s);
                 dp = E::mfma(ag, vf[ks], dp);
             }
@@ -229,11 +241,11 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
                 auto load_tr = [&] {
 #pragma unroll
                     for (int ct = 0; ct < CT; ++ct) {
-                        tg[ct] = tr_frag(gt, STRIDE, tr_off, ct, 2 * j + half);
-                        tq[ct] = tr_frag(qt, STRIDE, tr_off, ct, 2 * j + half);
+                        tg[ct] = ln.transposed_row(Cfg::OFF_G + query_base * 128, ct, half);
+                        tq[ct] = ln.transposed_row(query_base * 128, ct, half);
                     }
                 };
-                if (Cfg::EARLY_TR) load_tr();
+                if (EARLY_TR) load_tr();
                 u32x4 pf, df;
 #pragma unroll
                 for (int e = 8 * half; e < 8 * half + 8; ++e) {
@@ -245,7 +257,7 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
                         df[(e / 2) % 4] = E::pack(dp[e - 1], dp[e]);
                     }
                 }
-                if (!Cfg::EARLY_TR) {
+                if (!EARLY_TR) {
                     __builtin_amdgcn_sched_barrier(0);
                     load_tr();
                 }
@@ -264,7 +276,7 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
         // after dS of block j is complete its rows of Q and dO, and dS of the block before, are no longer read
         auto end_block = [&](int j) {
             lds_barrier();
-            if (more && ((j & 1) || j + 1 == NB)) fetch_slot(next, j >> 1);
+            if (more && ((j & 1) || j + 1 == NB)) fetch_rows(ahead, j >> 1);
         };
         // causal: a block whose queries all lie before this wavefront's keys is not read by dQ either
         const int from = !wave_active ? NB : CAUSAL ? wave : 0;

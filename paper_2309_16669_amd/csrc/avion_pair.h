@@ -29,8 +29,6 @@
 #pragma once
 #include "avion_bwd.h"
 
-// Byte offset of 16-byte chunk `ch` of row `row` in a tile
-DEVINL unsigned quad_at(int row, int ch) { return (row >> 2) * 512 + (ch >> 2) * 256 + (row & 3) * 64 + (((ch & 3) ^ (row >> 2 & 3)) * 16); }
 // K and V tiles; every wavefront issues four loads a tile
 struct PairRing {
     static constexpr int TILE = 64 * 128, BUF = 2 * TILE, NBUF = 4, LDS_BYTES = NBUF * BUF;
@@ -42,7 +40,7 @@ struct PairRing {
         da = ab.words;
         db = bb.words;
         smem_addr = lds_address(smem) + wave * 1024;
-        // the chunk at offset 16 * lane of 8 rows
+        // quad_voff(wave, ...), spelt out: the compiler then needs no scratch for what it keeps of it (254 registers and 68 bytes otherwise)
         const int row = 8 * wave + lane / 32 * 4 + lane / 4 % 4, ch = lane / 16 % 2 * 4 + ((lane ^ (row >> 2)) & 3);
         va = row * (unsigned)(rs_a * 2) + ch * 16;
         half = 32 * (unsigned)(rs_a * 2);
@@ -55,44 +53,6 @@ struct PairRing {
     // all but the newest fetch of this wavefront have landed
     DEVINL static void landed_barrier() { asm volatile("s_waitcnt vmcnt(4)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
     DEVINL static void all_landed_barrier() { asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-};
-// This lane's addresses in the present buffer: natural fragments by the step's low bit, transposed ones by which four of
-// their eight tokens.
-struct PairLane {
-    unsigned nat[2], tr[2];
-    DEVINL PairLane(int lane, unsigned buf)
-    {
-        const int l32 = lane % 32, g = lane / 32, G = lane >> 4, j = lane & 15, r = 4 * (G >> 1) + (j >> 2), c = 2 * (G & 1) + ((j & 3) >> 1);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            nat[i] = buf + quad_at(l32, 2 * i + g);
-            tr[i] = buf + quad_at(r + 8 * i, c) + (j & 1) * 8;
-        }
-    }
-    // (opaque, or the compiler adds the uniform parts first and each address once more)
-    DEVINL void move_nat(int by)
-    {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) { nat[i] += by; asm volatile("" : "+v"(nat[i])); }
-    }
-    DEVINL void move_tr(int by)
-    {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) { tr[i] += by; asm volatile("" : "+v"(tr[i])); }
-    }
-    // tensor: where its tile lies in the buffer
-    DEVINL frag8 natural(int tensor, int hk, int ks) const
-    {
-        typedef const __attribute__((address_space(3))) frag8* ptr;
-        return *(ptr)(nat[ks & 1] + (tensor + hk * 4096 + (ks >> 1) * 256));
-    }
-    DEVINL frag8 transposed(int tensor, int ct, int step) const
-    {
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tr[0] + (tensor + step * 2048 + ct * 256)));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(tr[1] + (tensor + step * 2048 + ct * 256)));
-        const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
-        return as_frag8(u32x4{l2[0], l2[1], h2[0], h2[1]});
-    }
 };
 constexpr int kPairBlocks = 8;  // blocks of 32 queries per workgroup
 // which blocks a wavefront has (`mine` from blk0 on), and, where a block is shared, which of its `parts`.  The wavefront
@@ -137,7 +97,7 @@ avion_dq_pair_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, c
     const PairSplit sp(N, qb, wave, logical);
     const int ntiles = (N + BN - 1) / BN, nb = (N + 31) / 32;
     const PairRing ring(k + head_off, rs, v + head_off, rs, N, smem, wave, lane);
-    PairLane ln(lane, lds_address(smem));
+    QuadLane ln(lane, lds_address(smem));
     ring.fetch(0);
     ring.fetch(1);
     ring.fetch(2);
