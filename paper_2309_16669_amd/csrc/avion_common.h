@@ -648,6 +648,86 @@ struct TileRing {
     }
 };
 
+// The same from tiles in quad_at's layout (64 channels, NW wavefronts): of the 8 blocks of either tensor's tile a wavefront fetches
+// every NW-th, all of them in one or two statements; places past 8 are not read.
+template <int NW>
+struct QuadTiles {
+    static constexpr int PER = (8 + NW - 1) / NW, TILE = PER * NW * 1024;
+    unsigned smem_addr, va, vb, ra, rb;
+    int wave;
+    u32x4 da, db;
+    DEVINL QuadTiles(const raw16* a, long rs_a, const raw16* b, long rs_b, int N, const char* smem, int wave_, int lane) : wave(wave_)
+    {
+        da = RawBuffer(a, slice_bytes(rs_a, N, 64)).words;
+        db = RawBuffer(b, slice_bytes(rs_b, N, 64)).words;
+        ra = (unsigned)(rs_a * 2);
+        rb = (unsigned)(rs_b * 2);
+        // of block 0; an odd block's second bit of the chunk is flipped (quad_at; rows are whole multiples of 128 bytes apart)
+        va = quad_voff(0, lane, ra) ^ (NW % 2 == 0 ? 32 * (wave & 1) : 0);
+        vb = quad_voff(0, lane, rb) ^ (NW % 2 == 0 ? 32 * (wave & 1) : 0);
+        smem_addr = lds_address(smem) + wave * 1024;
+    }
+    // this wavefront's loads of tile ti; rows past the end arrive as zeros
+    DEVINL void fetch_tiles(int ti, unsigned base) const
+    {
+        unsigned oa[PER], ob[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int blk = wave + NW * j;
+            const unsigned row = 64 * ti + 8 * blk;
+            const unsigned flip = NW % 2 == 0 ? 0 : 32 * (blk & 1);
+            oa[j] = (va ^ flip) + row * ra;
+            ob[j] = (vb ^ flip) + row * rb;
+        }
+        if constexpr (NW == 4) {
+            load_to_lds16_x4<4096>(RawBuffer(da), RawBuffer(da), RawBuffer(db), RawBuffer(db), base, oa[0], oa[1], ob[0], ob[1]);
+        } else if constexpr (NW == 2) {
+            load_to_lds16_x4<2048>(RawBuffer(da), RawBuffer(da), RawBuffer(da), RawBuffer(da), base, oa[0], oa[1], oa[2], oa[3]);
+            load_to_lds16_x4<2048>(RawBuffer(db), RawBuffer(db), RawBuffer(db), RawBuffer(db), base + TILE, ob[0], ob[1], ob[2], ob[3]);
+        } else {
+            load_to_lds16_x4<3072>(RawBuffer(da), RawBuffer(da), RawBuffer(da), RawBuffer(db), base, oa[0], oa[1], oa[2], ob[0]);
+            load_to_lds16_x2<3072>(RawBuffer(db), RawBuffer(db), base + 4 * 3072, ob[1], ob[2]);
+        }
+    }
+};
+// Two buffers of them
+template <int NW>
+struct QuadRing : QuadTiles<NW> {
+    using QuadTiles<NW>::TILE;
+    static constexpr int OFF_B = TILE, BUF_BYTES = 2 * TILE, LDS_BYTES = 2 * BUF_BYTES;
+    char* smem;
+    DEVINL QuadRing(const raw16* a, long rs_a, const raw16* b, long rs_b, int N, const float*, int, int, char* smem_, int wave_, int lane)
+        : QuadTiles<NW>(a, rs_a, b, rs_b, N, smem_, wave_, lane), smem(smem_)
+    {
+    }
+    DEVINL char* buf(int ti) const { return smem + (ti & 1) * BUF_BYTES; }
+    DEVINL void fetch(int ti) const { this->fetch_tiles(ti, this->smem_addr + (ti & 1) * BUF_BYTES); }
+    DEVINL static void landed_barrier() { asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+};
+// A lane's fragments in a ring's buffer: in padded tiles from the buffer's address, in quad_at's from addresses that move with it
+template <typename Ring>
+struct RingLane {
+    const char* at;
+    int row, group, tr_off;
+    DEVINL RingLane(const Ring& ring, int lane, int t) : at(ring.buf(t)), row(lane % 32), group(lane / 32), tr_off(tr_lane_offset(lane, Ring::STRIDE)) {}
+    DEVINL void enter(const Ring& ring, int t) { at = ring.buf(t); }
+    DEVINL void leave(int) {}
+    DEVINL frag8 natural(int tensor, int hk, int ks) const { return nat_frag(at + tensor, Ring::STRIDE, 32 * hk + row, ks, group); }
+    DEVINL frag8 transposed(int tensor, int ct, int step) const { return tr_frag(at + tensor, Ring::STRIDE, tr_off, ct, step); }
+};
+template <int NW>
+struct RingLane<QuadRing<NW>> : QuadLane {
+    using Ring = QuadRing<NW>;
+    DEVINL RingLane(const Ring& ring, int lane, int t) : QuadLane(lane, lds_address(ring.buf(t))) {}
+    DEVINL void enter(const Ring&, int) {}
+    DEVINL void leave(int t)
+    {
+        const int by = t & 1 ? -Ring::BUF_BYTES : Ring::BUF_BYTES;
+        move_nat(by);
+        move_tr(by);
+    }
+};
+
 // Workgroup id -> logical tile id such that tiles with consecutive logical ids run on the same XCD
 // (workgroups are dealt to the 8 XCDs round robin, and each XCD has its own L2): tiles of one
 // (batch, head) then share the K/V (or Q/dO) lines they all read.  Returns -1 for the padding ids.

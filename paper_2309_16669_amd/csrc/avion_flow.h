@@ -19,57 +19,27 @@
 
 // Q, dO and the per-query scalars for one group of NW wavefronts
 template <int NW>
-struct FlowRing {
-    static constexpr int PER = (8 + NW - 1) / NW;       // 1 KB blocks (8 rows) of one tensor per wavefront; the places past 8 are not read
-    static constexpr int TILE = PER * NW * 1024, OFF_SC = 2 * TILE, BUF = OFF_SC + 1024, NBUF = 4, LDS_BYTES = NBUF * BUF;
+struct FlowRing : QuadTiles<NW> {
+    using QuadTiles<NW>::PER;
+    using QuadTiles<NW>::TILE;
+    static constexpr int OFF_SC = 2 * TILE, BUF = OFF_SC + 1024, NBUF = 4, LDS_BYTES = NBUF * BUF;
     static constexpr int LOADS = 2 * PER + 1;
-    unsigned smem_addr, va[2], vb[2], ra, rb, vs;
-    int wave;
-    u32x4 da, db, ds;
+    unsigned vs;
+    u32x4 ds;
     DEVINL FlowRing(const raw16* a, long rs_a, const raw16* b, long rs_b, int N, const float* scalars, int npad, const char* smem, int wave_, int lane)
-        : wave(wave_)
+        : QuadTiles<NW>(a, rs_a, b, rs_b, N, smem, wave_, lane)
     {
-        const RawBuffer ab(a, slice_bytes(rs_a, N, 64)), bb(b, slice_bytes(rs_b, N, 64)), sb(scalars + (wave & 1) * npad, npad * 4u);
-        da = ab.words;
-        db = bb.words;
-        ds = sb.words;
-        ra = (unsigned)(rs_a * 2);
-        rb = (unsigned)(rs_b * 2);
-        // by the block's parity, less its own rows (which four rows they are decides the permutation)
-#pragma unroll
-        for (int odd = 0; odd < 2; ++odd) {
-            va[odd] = quad_voff(odd, lane, ra) - 8 * odd * ra;
-            vb[odd] = quad_voff(odd, lane, rb) - 8 * odd * rb;
-        }
+        ds = RawBuffer(scalars + (wave_ & 1) * npad, npad * 4u).words;
         vs = lane * 4;
-        smem_addr = lds_address(smem) + wave * 1024;
     }
     // the loads of one wavefront; rows and scalars past the end arrive as zeros
     DEVINL void fetch(int ti, unsigned buf) const
     {
-        const unsigned base = smem_addr + buf;
-        unsigned oa[PER], ob[PER];
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int blk = wave + NW * j;
-            const unsigned row = 64 * ti + 8 * blk;
-            const bool odd = NW % 2 == 0 ? wave & 1 : blk & 1;
-            oa[j] = (odd ? va[1] : va[0]) + row * ra;
-            ob[j] = (odd ? vb[1] : vb[0]) + row * rb;
-        }
-        if constexpr (NW == 4) {
-            load_to_lds16_x4<4096>(RawBuffer(da), RawBuffer(da), RawBuffer(db), RawBuffer(db), base, oa[0], oa[1], ob[0], ob[1]);
-        } else if constexpr (NW == 2) {
-            load_to_lds16_x4<2048>(RawBuffer(da), RawBuffer(da), RawBuffer(da), RawBuffer(da), base, oa[0], oa[1], oa[2], oa[3]);
-            load_to_lds16_x4<2048>(RawBuffer(db), RawBuffer(db), RawBuffer(db), RawBuffer(db), base + TILE, ob[0], ob[1], ob[2], ob[3]);
-        } else {
-            load_to_lds16_x4<3072>(RawBuffer(da), RawBuffer(da), RawBuffer(da), RawBuffer(db), base, oa[0], oa[1], oa[2], ob[0]);
-            load_to_lds16(RawBuffer(db), base + 4 * 3072, ob[1]);
-            load_to_lds16(RawBuffer(db), base + 5 * 3072, ob[2]);
-        }
+        const unsigned base = this->smem_addr + buf;
+        this->fetch_tiles(ti, base);
         // LSE by even wavefronts, -delta by odd ones, 256 bytes each
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dword %1, %2, 0 offen lds"
-                     : : "s"(base + OFF_SC - wave * 768), "v"(vs + (unsigned)ti * 256), "s"(ds) : "memory", "m0");
+                     : : "s"(base + OFF_SC - this->wave * 768), "v"(vs + (unsigned)ti * 256), "s"(ds) : "memory", "m0");
     }
     // all but the newest fetch of this wavefront have landed
     DEVINL static void landed_barrier() { asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"i"(LOADS) : "memory"); }

@@ -6,7 +6,8 @@
 // Each wavefront owns 32 queries and keeps
 //   Q as MFMA B-operand fragments (lane = query, 8 channels per 16-deep step),
 //   O^T accumulators (lane = query, registers = channels), the reference maximum and row sums.
-// Keys and values come in LDS tiles of 64 tokens in their natural row layout, two (K | V) buffers,
+// Keys and values come in LDS tiles of 64 tokens, two (K | V) buffers, rows in quad_at's order at 64 channels (padded
+// ones at 80),
 // filled straight from global memory by LDS-direct loads (no staging registers, no LDS writes):
 // K rows are the A operand of S^T = K Q^T, and V is read through transposing LDS loads as the A
 // operand of O^T = V^T P^T.  Computing the transposed products keeps every score of a query inside
@@ -36,6 +37,12 @@
 // chain of one wavefront per SIMD, which this shortens (the rule and both sides' times stand at
 // fwd_cut in avion_attn.hip).
 //
+// What bounds it on a full chip: vector issue and, behind it, LDS.  Padded rows of 144 bytes -> quad_at's layout (no bank conflicts,
+// an eighth less deposited, a tile's loads in one statement), us, same bits: 384 heads x 1568 285.7 -> 280.9, causal 172.1 -> 168.7, 96 x
+// 3000 253.8 -> 249.3, 3072 x 196 78.1 -> 76.0, 16384 x 77 183.4 -> 175.6 (causal 176.4), x 40 causal 101.5 -> 95.8, 8 x 77 causal 5.63 -> 5.26,
+// 8 x 1568 15.3 -> 14.8, 16 x 400 8.10 -> 7.63; 0.93 to 1.007 of the time over 31 shapes.  (dK/dV in it, at three wavefronts per SIMD,
+// 452.7 -> 465.2: the two addresses more take registers that keep operands in flight.)
+//
 // Template parameters: head dim D, wavefronts per group NW, groups KG, element format E (Bf16 or F16),
 // CAUSAL (query i sees keys 0..i; the reference m is then the maximum over the visible ones of the
 // first 32 keys -- key 0 is visible to every query).
@@ -47,31 +54,33 @@ struct FwdCfg {
     static constexpr int BN = 64;
     static constexpr int NT = NW * KG * 64;
     static constexpr int BM = 32 * NW;
-    using Ring = TileRing<D, NW, 2, false>;
+    using Ring = std::conditional_t<D == 64, QuadRing<NW>, TileRing<D, NW, 2, false>>;
     using Stage = TileStage<D, BN, NT>;  // the fallback pass stages its tiles through registers
-    static_assert(Ring::TILE_BYTES == Stage::BYTES, "both movers use the same tile layout");
-    static constexpr int LDS_BYTES = KG * Ring::LDS_BYTES;
+    // the fallback's two buffers of padded tiles (its last row's reads too), or the groups' rings
+    static constexpr int SAFE_BYTES = 4 * Stage::BYTES + (D % 32 != 0 ? 64 : 0);
+    static constexpr int LDS_BYTES = KG * Ring::LDS_BYTES > SAFE_BYTES ? KG * Ring::LDS_BYTES : SAFE_BYTES;
     // wavefronts per SIMD the register budget is sized for: what LDS lets a compute unit hold, at most 4;
-    // with several groups one workgroup per compute unit
+    // with several groups one workgroup per compute unit, with two groups up to two: six wavefronts each may put four on one SIMD
+    // (40 heads x 785 18.4 -> 22.4 us at 130 registers instead of 128)
     static constexpr int WG_PER_CU = 160 * 1024 / LDS_BYTES;
-    static constexpr int WAVES_PER_SIMD = KG > 1 ? (NW * KG + 3) / 4 : WG_PER_CU * NW / 4 > 4 ? 4 : WG_PER_CU * NW / 4;
+    static constexpr int WAVES_PER_SIMD = KG == 2 && D == 64 ? 4 : KG > 1 ? (NW * KG + 3) / 4 : WG_PER_CU * NW / 4 > 4 ? 4 : WG_PER_CU * NW / 4;
 };
 
 // Classic online softmax with a running maximum, one 64-key tile at a time, staged through
-// registers into the ring's two buffers.  Used only as the fallback described above; same register
+// registers into two buffers of padded tiles.  Used only as the fallback described above; same register
 // layouts as the main loop.
 // key_limit: this lane's query sees keys below it (N, or query + 1 for causal attention).
 template <int D, int NW, int KG, typename E>
 DEVINL void avion_fwd_safe_pass(char* smem, const SliceView& kh, const SliceView& vh, const frag8 (&qf)[D / 16],
                                 f32x16 (&oacc)[(D + 31) / 32], float& m_used, float& lsum, float& rsum, int N,
-                                int key_limit, float cs, bool wave_active, int tid, int l32, int g, int tr_off)
+                                int key_limit, float cs, bool wave_active, int tid, int lane)
 {
     using Cfg = FwdCfg<D, NW, KG>;
     using Stage = typename Cfg::Stage;
-    using Ring = typename Cfg::Ring;
     constexpr int BN = 64, STRIDE = Stage::STRIDE, KS = D / 16, CT = (D + 31) / 32;
-    auto kbuf = [&](int i) { return smem + i * Ring::BUF_BYTES; };
-    auto vbuf = [&](int i) { return smem + i * Ring::BUF_BYTES + Ring::OFF_B; };
+    const int l32 = lane % 32, g = lane / 32, tr_off = tr_lane_offset(lane, STRIDE);
+    auto kbuf = [&](int i) { return smem + i * 2 * Stage::BYTES; };
+    auto vbuf = [&](int i) { return smem + (2 * i + 1) * Stage::BYTES; };
     m_used = -INFINITY;
     lsum = 0.f;
     rsum = 0.f;
@@ -151,7 +160,7 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
 {
     using Cfg = FwdCfg<D, NW, KG>;
     using Ring = typename Cfg::Ring;
-    constexpr int BN = Cfg::BN, BM = Cfg::BM, STRIDE = Ring::STRIDE;
+    constexpr int BN = Cfg::BN, BM = Cfg::BM;
     constexpr int KS = D / 16;         // 16-deep steps over the channels
     constexpr int CT = (D + 31) / 32;  // 32-channel tiles of O^T
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -174,7 +183,6 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
     const SliceView vh(v + head_off, rs, N, D);
     const int q0 = qb * BM + wave * 32;  // first query of this wavefront
     const bool wave_active = q0 < N;
-    const int tr_off = tr_lane_offset(lane, STRIDE);
     // Keys this lane's query sees: all N, or 0..query for causal attention.  For the whole wavefront:
     // units that start at or beyond wave_key_end are skipped, units that reach beyond mask_from start
     // their scores from the mask; the workgroup streams the tiles up to its last query only.
@@ -188,6 +196,7 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
 
     const Ring ring(k + head_off, rs, v + head_off, rs, N, nullptr, 0, ntiles, smem + grp * Ring::LDS_BYTES, wave, lane);
     if (KG == 1 || t0 < t1) ring.fetch(t0);
+    RingLane<Ring> ln(ring, lane, t0);
 
     // Q fragments stay in registers for the whole kernel
     frag8 qf[KS];
@@ -208,13 +217,13 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
 
     // S^T of one unit (32 keys starting at row 32*hk of the K tile); RAGGED units reach past the
     // last key and start from the key mask instead of zero
-    auto scores = [&](auto ragged, const char* kt, int hk, int key_base) -> f32x16 {
+    auto scores = [&](auto ragged, int hk, int key_base) -> f32x16 {
         constexpr bool RAGGED = decltype(ragged)::value;
         f32x16 s;
         if constexpr (RAGGED) s = key_mask_block(key_base, g, key_limit);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-            s = E::mfma(nat_frag(kt, STRIDE, 32 * hk + l32, ks, g), qf[ks], ks == 0 && !RAGGED ? f32x16_zero() : s);
+            s = E::mfma(ln.natural(0, hk, ks), qf[ks], ks == 0 && !RAGGED ? f32x16_zero() : s);
         return s;
     };
     // reference maximum: over the first 32 keys (of this group's); their scores serve the first unit too, one of three
@@ -222,20 +231,20 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
     // 3072 x 196 84.3 -> 82.8, d = 80 113.8 -> 112.0)
     f32x16 first = f32x16_zero();
     if (wave_active && (KG == 1 || t0 < t1)) {
-        first = scores(std::true_type{}, ring.buf(t0), 0, t0 * BN);
+        first = scores(std::true_type{}, 0, t0 * BN);
         m_used = both_halves_max(max16(first)) * cs;
         // a query that sees none of them (causal, a later group): any finite reference will do, its weights
         // must come out as 0
         if (KG > 1 && CAUSAL) m_used = t0 * BN < key_limit ? m_used : 0.f;
     }
     // weights of one unit from its scores, and their product with V
-    auto weigh = [&](f32x16 s, const char* vt, int hk) {
+    auto weigh = [&](f32x16 s, int hk) {
         // the V^T operands are requested before the vector work so that they are there after it
         frag8 vf[2][CT];
 #pragma unroll
         for (int half = 0; half < 2; ++half)
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) vf[half][ct] = tr_frag(vt, STRIDE, tr_off, ct, 2 * hk + half);
+            for (int ct = 0; ct < CT; ++ct) vf[half][ct] = ln.transposed(Ring::OFF_B, ct, 2 * hk + half);
         u32x4 pf[2];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -257,22 +266,23 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
     };
     auto tile = [&](auto first_tile, int t) {
         if (KG == 1 || t + 1 < t1) ring.fetch(t + 1);  // into the buffer of tile t-1, which nobody reads any more
+        ln.enter(ring, t);
         if (wave_active && (KG == 1 || t < t1)) {
-            const char* kt = ring.buf(t);
 #pragma unroll
             for (int hk = 0; hk < 2; ++hk) {
                 const int key_base = t * BN + 32 * hk;
                 if (key_base >= wave_key_end) continue;  // past the last key, or (causal) seen by no query of this wavefront
                 if (decltype(first_tile)::value && hk == 0) {
-                    weigh(first, kt + Ring::OFF_B, hk);
+                    weigh(first, hk);
                     continue;
                 }
                 f32x16 s;
-                if (key_base + 32 > mask_from) s = scores(std::true_type{}, kt, hk, key_base);
-                else s = scores(std::false_type{}, kt, hk, key_base);
-                weigh(s, kt + Ring::OFF_B, hk);
+                if (key_base + 32 > mask_from) s = scores(std::true_type{}, hk, key_base);
+                else s = scores(std::false_type{}, hk, key_base);
+                weigh(s, hk);
             }
         }
+        ln.leave(t);
         Ring::landed_barrier();  // tile t+1 has landed; tile t is no longer read
     };
     tile(std::true_type{}, t0);
@@ -285,7 +295,7 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
     const bool redo = __syncthreads_or(bad ? 1 : 0);
     if (redo)
         avion_fwd_safe_pass<D, NW, KG, E>(smem, kh, vh, qf, oacc, m_used, lsum, rsum, N, key_limit, cs,
-                                          wave_active && grp == 0, tid, l32, g, tr_off);
+                                          wave_active && grp == 0, tid, lane_from_exec());
     if constexpr (KG > 1) {
         // The groups' results meet in LDS (behind the row-store areas of the epilogue) as [value][lane]
         // floats and are added in group order, each scaled to the larger of the two references.  After a
@@ -294,7 +304,7 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
         static_assert(NW * RowStore<D, E>::BYTES + (KG - 1) * NW * WAVE_BYTES <= Cfg::LDS_BYTES, "exchange area");
         char* area = smem + NW * RowStore<D, E>::BYTES;
         if (grp > 0 && wave_active && !redo) {
-            float* mine = reinterpret_cast<float*>(area + ((grp - 1) * NW + wave) * WAVE_BYTES) + lane;
+            float* mine = reinterpret_cast<float*>(area + ((grp - 1) * NW + wave) * WAVE_BYTES) + lane_from_exec();
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
@@ -309,7 +319,7 @@ avion_fwd_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, const
         if (wave_active && !redo) {
 #pragma unroll
             for (int og = 0; og < KG - 1; ++og) {
-                const float* other = reinterpret_cast<const float*>(area + (og * NW + wave) * WAVE_BYTES) + lane;
+                const float* other = reinterpret_cast<const float*>(area + (og * NW + wave) * WAVE_BYTES) + lane_from_exec();
                 const float m2 = other[(VALS - 1) * 64];
                 const float mn = fmaxf(m_used, m2), a1 = fast_exp2(m_used - mn), a2 = fast_exp2(m2 - mn);
                 lsum = lsum * a1 + other[(VALS - 3) * 64] * a2;
