@@ -93,7 +93,10 @@ DEVINL void avion_dq_body(char* smem, const raw16* __restrict__ q, const raw16* 
     const int b = bh / H, h = bh % H;
     const int tid = threadIdx.x, lane = tid % 64, l32 = lane % 32, g = lane / 32;
     const int wave_id = __builtin_amdgcn_readfirstlane(tid / 64);
-    const int wave = KG == 1 ? wave_id : wave_id % NW, grp = KG == 1 ? 0 : wave_id / NW;
+    // Which wavefront has the last rows, or none, turns with the head, as in the forward, here and in dK/dV.  Whole backward, us, same bits: at 80
+    // channels 4096 heads x 50 98.3 -> 95.1, 2048 x 77 62.9 -> 62.2 (causal 62.5 -> 61.5), 1024 x 196 101.3 -> 100.3; 1024 x 300 causal
+    // 107.8 -> 107.0; equal at 785 tokens and more.
+    const int wave = (wave_id + bh) % NW, grp = KG == 1 ? 0 : wave_id / NW;
     // token rows of Q, K, V, dQ are rs_qkv elements apart, those of O, dO rs_o
     const long rs = rs_qkv;
     const long head_off = (long)b * N * rs + (long)h * D;
@@ -275,7 +278,7 @@ DEVINL void avion_dkdv_body(char* smem, const raw16* __restrict__ q, const raw16
     const int b = bh / H, h = bh % H;
     const int tid = threadIdx.x, lane = tid % 64, l32 = lane % 32, g = lane / 32;
     const int wave_id = __builtin_amdgcn_readfirstlane(tid / 64);
-    const int wave = KG == 1 ? wave_id : wave_id % NW, grp = KG == 1 ? 0 : wave_id / NW;
+    const int wave = (wave_id + bh) % NW, grp = KG == 1 ? 0 : wave_id / NW;
     // token rows of Q, K, V, dK, dV are rs_qkv elements apart, those of dO rs_o
     const long rs = rs_qkv;
     const long head_off = (long)b * N * rs + (long)h * D;
