@@ -67,9 +67,10 @@ avion_dkdv_flow_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k,
     const long head_off_o = (long)b * N * rs_o + (long)h * D;
     const int npad = (N + 63) & ~63, ntiles = npad / 64;
     const int k0 = kb * 32 * NW + wave * 32;  // first key of this wavefront
-    // Tiles t0 .. t0 + per - 1 are this group's.  A tile past the end is zero rows with scalars of 0: weights of 1 for
-    // rows of zeros, and dS = 0.
-    const int per = (ntiles + KG - 1) / KG, t0 = grp * per;
+    // Units of 32 queries of this group, from tile t0 on (at least one: the launch has five tiles or more).  Units that lie wholly past
+    // the end, in the last tile or in a tile that only the first group has, are left out, as avion_dkdv_body does: their rows are zeros, but
+    // zeros times a key's infinite component are not.
+    const int per = (ntiles + KG - 1) / KG, t0 = grp * per, units = min(2 * per, (N + 31) / 32 - 2 * t0);
     char* mine = smem + grp * Ring::LDS_BYTES;
     const Ring ring(q + head_off, rs, dO + head_off_o, rs_o, N, rowsc + (long)bh * 2 * npad, npad, mine, wave, lane);
     QuadLane ln(lane, lds_address(mine));
@@ -158,7 +159,7 @@ avion_dkdv_flow_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k,
     };
     constexpr std::integral_constant<int, 0> lo{};
     constexpr std::integral_constant<int, 1> hi{};
-    for (int i = 0; i < per; ++i) {
+    for (int i = 0; i < units / 2; ++i) {
         const int by = (i & 3) == 3 ? -3 * Ring::BUF : Ring::BUF;  // to the next tile's buffer
         first_half(A, B, lo);
         second_half(A, B, lo);
@@ -171,10 +172,24 @@ avion_dkdv_flow_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k,
         second_half(B, A, hi);
         ln.move_tr(by);
     }
+    for (int i = units / 2; i < per; ++i) Ring::landed_barrier();  // every wavefront passes the same barriers
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         dva[i % 2] = E::mfma(f[2 * i], as_frag8(pf[i / 2]), dva[i % 2]);
         dka[i % 2] = E::mfma(f[2 * i + 1], as_frag8(df[i / 2]), dka[i % 2]);
+    }
+    if (units & 1) {  // half a tile: its scores are in A
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+            const float p0 = fast_exp2(fmaf(A.s[e], cs, -l4[e / 4][e % 4])), p1 = fast_exp2(fmaf(A.s[e + 1], cs, -l4[e / 4][e % 4 + 1]));
+            pf[e / 8][(e / 2) % 4] = E::pack(p0, p1);
+            df[e / 8][(e / 2) % 4] = E::pack(p0 * A.dp[e], p1 * A.dp[e + 1]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            dva[i % 2] = E::mfma(ln.transposed(Ring::TILE, i % 2, i / 2), as_frag8(pf[i / 2]), dva[i % 2]);
+            dka[i % 2] = E::mfma(ln.transposed(0, i % 2, i / 2), as_frag8(df[i / 2]), dka[i % 2]);
+        }
     }
     Ring::all_landed_barrier();  // no load is on its way, no tile is read any more
     const bool wave_active = k0 < N;

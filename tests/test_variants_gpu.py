@@ -306,6 +306,33 @@ def test_pipelined_dk_dv_of_small_launches(B, H, N, f16, packed):
     check(w, x, run_ex(w, x, f16, False, packed), f16, False)
 
 
+# Units of 32 queries that lie wholly past the end, in tiles past the end (an odd number of tiles in two groups) and in half tiles, are
+# left out: a key with an infinite component that no query sees (weights of exactly 0, as for a finite one far below the others) gets dK and
+# dV of 0 and changes nothing of the other keys'.  64, 96 and 128 rows, pipelined; then the other kernels.
+@pytest.mark.parametrize("H,N,f16", [(3, 320, False), (3, 352, True), (30, 576, True), (30, 544, False), (34, 480, False), (30, 960, False),
+                                     (28, 992, True), (48, 480, True), (65, 448, False), (90, 640, True), (3, 160, False)])
+def test_units_past_the_end_leave_keys_with_infinite_components_alone(H, N, f16):
+    import torch
+    import paper_2309_16669_amd as av
+    dt = torch.float16 if f16 else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(N + H)
+    q, k, v, dO = (torch.randn(1, N, H, 64, device="cuda", generator=gen).to(dt) for _ in range(4))
+    q[..., 0] = 1.0
+    ws = torch.empty(av.attn_bwd_workspace_bytes(1, H, N, 64), dtype=torch.uint8, device="cuda")
+    outs = []
+    for low in (-30000.0, float("-inf")):
+        k[:, [40, N - 3], :, 0] = low
+        o, dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(4))
+        lse = torch.full((1, H, N), float("nan"), device="cuda")
+        av.attn_fwd_ex(q, k, v, o, lse, 0.125, False)
+        av.attn_bwd_ex(q, k, v, o, lse, dO, dq, dk, dv, 0.125, ws.fill_(255), False)
+        torch.cuda.synchronize()
+        outs.append((o, lse, dq[..., 1:], dk, dv))      # (dQ of channel 0 is a product of that component with 0)
+    for name, a, b in zip(("o", "lse", "dq", "dk", "dv"), *outs):
+        assert (int((~torch.isfinite(b)).sum()), torch.equal(a, b)) == (0, True), name
+    assert [int(t[:, [40, N - 3]].count_nonzero()) for t in outs[1][3:]] == [0, 0]
+
+
 # The running-maximum fallback where the last and where the first of two groups of 96 and of 128 rows overflows
 @pytest.mark.parametrize("H,N,sink", [(43, 385, 370), (43, 385, 40), (50, 600, 590), (50, 600, 40), (70, 448, 440)])
 def test_an_overflowing_group_of_two_redoes_the_block(H, N, sink):
