@@ -652,6 +652,7 @@ struct TileRing {
 // every NW-th, all of them in one or two statements; places past 8 are not read.
 template <int NW>
 struct QuadTiles {
+    static_assert(NW >= 2 && NW <= 4, "fetch_tiles, and what waits for its loads, know two to four wavefronts");
     static constexpr int PER = (8 + NW - 1) / NW, TILE = PER * NW * 1024;
     unsigned smem_addr, va, vb, ra, rb;
     int wave;
