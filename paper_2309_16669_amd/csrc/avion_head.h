@@ -49,9 +49,9 @@ struct HeadCfg {
     static constexpr int ROWS = WALK ? MAX_N : 32 * NB;
     static constexpr int TILE_BYTES = ROWS * 128;        // Q, dO, K: all rows of the head (quad_at)
     static constexpr int DS_BYTES = ROWS * DS_STRIDE;    // one key per row
-    // dS lies where K was, unless the next head's K is on its way there
-    static constexpr int OFF_G = TILE_BYTES, OFF_K = 2 * TILE_BYTES, OFF_DS = WALK ? 3 * TILE_BYTES : OFF_K,
-                         OFF_SC = OFF_DS + (WALK || 2 * DS_BYTES > TILE_BYTES ? 2 * DS_BYTES : TILE_BYTES);
+    // dS lies where K was (and beyond it: two buffers of 72 bytes a row), unless the next head's K is on its way there
+    static constexpr int OFF_G = TILE_BYTES, OFF_K = 2 * TILE_BYTES, OFF_DS = WALK ? 3 * TILE_BYTES : OFF_K, OFF_SC = OFF_DS + 2 * DS_BYTES;
+    static_assert(2 * DS_BYTES >= TILE_BYTES, "the scalars lie behind K");
     static constexpr int LDS_BYTES = OFF_SC + 2 * MAX_N * 4;  // LSE*log2e and -delta per query
     static constexpr int WAVES_PER_SIMD = WALK || NB > 3 ? 2 : 3;
     // transposed operands requested ahead of the vector work; with 168 registers (three wavefronts per SIMD) behind it.  Behind it
