@@ -28,8 +28,8 @@ def bf16_tensor_to_f64(t):
 
 
 def run_hip(w, x, poison=True, causal=False):
-    """fwd + bwd of workload w on the GPU through the C ABI (the causal entry points if asked).
-    Returns torch tensors."""
+    """fwd + bwd of workload w on the GPU through the C ABI (the causal entry points if asked).  The workspace holds NaNs,
+    here and in the other runs: what the backward reads of it, it has to have written.  Returns torch tensors."""
     import torch
     import paper_2309_16669_amd as av
     attn_fwd, attn_bwd = (av.attn_fwd_causal, av.attn_bwd_causal) if causal else (av.attn_fwd, av.attn_bwd)
@@ -38,7 +38,7 @@ def run_hip(w, x, poison=True, causal=False):
     o = torch.full_like(q, fill)
     lse = torch.full((w.B, w.H, w.N), fill, dtype=torch.float32, device="cuda")
     dq, dk, dv = (torch.full_like(q, fill) for _ in range(3))
-    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda").fill_(255)
     attn_fwd(q, k, v, o, lse, w.scale)
     attn_bwd(q, k, v, o, lse, dO, dq, dk, dv, w.scale, ws)
     torch.cuda.synchronize()
@@ -57,7 +57,7 @@ def run_hip_packed(w, x, poison=True):
     o = torch.full_like(dO, fill)
     lse = torch.full((w.B, w.H, w.N), fill, dtype=torch.float32, device="cuda")
     dqkv = torch.full_like(qkv, fill)
-    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda").fill_(255)
     av.attn_fwd_qkvpacked(qkv, o, lse, w.scale)
     av.attn_bwd_qkvpacked(qkv, o, lse, dO, dqkv, w.scale, ws)
     torch.cuda.synchronize()
@@ -107,7 +107,7 @@ def run_hip_f16(w, x16):
     o = torch.full_like(q, float("nan"))
     lse = torch.full((w.B, w.H, w.N), float("nan"), dtype=torch.float32, device="cuda")
     dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(3))
-    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda").fill_(255)
     av.attn_fwd_f16(q, k, v, o, lse, w.scale)
     av.attn_bwd_f16(q, k, v, o, lse, dO, dq, dk, dv, w.scale, ws)
     torch.cuda.synchronize()

@@ -361,7 +361,7 @@ def test_largest_addressable_head_slice():
     o = torch.full_like(q, float("nan"))
     lse = torch.full((B, H, N), float("nan"), dtype=torch.float32, device="cuda")
     dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(3))
-    ws = torch.empty(av.attn_bwd_workspace_bytes(B, H, N, d), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(av.attn_bwd_workspace_bytes(B, H, N, d), dtype=torch.uint8, device="cuda").fill_(255)
     av.attn_fwd(q, k, v, o, lse, 0.125)
     av.attn_bwd(q, k, v, o, lse, dO, dq, dk, dv, 0.125, ws)
     torch.cuda.synchronize()
@@ -396,7 +396,7 @@ def test_two_streams_with_their_own_workspaces_do_not_disturb_each_other(shapes)
         o = torch.empty_like(q)
         lse = torch.empty((w.B, w.H, w.N), dtype=torch.float32, device="cuda")
         dq, dk, dv = (torch.empty_like(q) for _ in range(3))
-        wsb = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda")
+        wsb = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda").fill_(255)
         outs.append(dict(q=q, k=k, v=v, dO=dO, o=o, lse=lse, dq=dq, dk=dk, dv=dv, ws=wsb))
     torch.cuda.synchronize()
     for rep in range(3):          # interleave the enqueues
@@ -462,7 +462,7 @@ def test_whole_backward_equals_its_two_phases(B, H, N, d):
     whole = gh.run_hip(w, x)
     q, k, v, dO = (gh.to_gpu_bf16(x[n]) for n in ("q", "k", "v", "dO"))
     dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(3))
-    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda").fill_(255)
     av.attn_bwd_dq(q, k, v, whole["o"], whole["lse"], dO, dq, w.scale, ws)
     av.attn_bwd_dkdv(q, k, v, whole["lse"], dO, dk, dv, w.scale, ws)
     torch.cuda.synchronize()
@@ -480,7 +480,7 @@ def test_the_two_phases_stay_callable_on_short_sequences(B, H, N, d):
     whole = gh.run_hip(w, x)
     q, k, v, dO = (gh.to_gpu_bf16(x[n]) for n in ("q", "k", "v", "dO"))
     dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(3))
-    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda").fill_(255)
     av.attn_bwd_dq(q, k, v, whole["o"], whole["lse"], dO, dq, w.scale, ws)
     av.attn_bwd_dkdv(q, k, v, whole["lse"], dO, dk, dv, w.scale, ws)
     torch.cuda.synchronize()
@@ -501,7 +501,7 @@ def test_calls_can_be_captured_in_a_graph_and_replayed():
     o = torch.empty_like(q)
     lse = torch.empty((w.B, w.H, w.N), dtype=torch.float32, device="cuda")
     dq, dk, dv = (torch.empty_like(q) for _ in range(3))
-    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda").fill_(255)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):                              # captures on a side stream

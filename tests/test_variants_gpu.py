@@ -25,7 +25,7 @@ def run_ex(w, x, f16, causal, packed):
     dO = _upload(x["dO"], f16)
     o = torch.full_like(dO, float("nan"))
     lse = torch.full((w.B, w.H, w.N), float("nan"), dtype=torch.float32, device="cuda")
-    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda").fill_(255)
     if packed:
         qkv = _upload(np.stack([x["q"], x["k"], x["v"]], axis=2), f16)
         dqkv = torch.full_like(qkv, float("nan"))
@@ -277,7 +277,10 @@ def test_small_launches_cut_into_four_groups(B, H, N, f16, causal, packed):
     (1, 43, 385, 64, False, False), (1, 43, 385, 64, True, True), (1, 43, 385, 80, False, True), (2, 26, 321, 64, False, False),
     (1, 64, 384, 64, True, False), (1, 65, 385, 64, False, False), (2, 40, 448, 64, True, False), (1, 65, 512, 64, False, True),
     (1, 52, 600, 64, False, False), (1, 53, 610, 64, False, True), (1, 56, 640, 64, True, True), (1, 57, 577, 64, False, True),
-    (1, 75, 577, 64, False, False), (2, 43, 620, 64, True, False), (3, 27, 639, 80, False, False)])
+    (1, 75, 577, 64, False, False), (2, 43, 620, 64, True, False), (3, 27, 639, 80, False, False),
+    # backward in 96 rows that end half way through the last 64, at 5 tiles and 8
+    (2, 30, 270, 64, False, False), (2, 30, 270, 64, True, True), (2, 30, 270, 80, True, False), (2, 30, 270, 80, False, True),
+    (1, 48, 480, 64, False, False), (1, 48, 480, 64, False, True)])
 def test_cuts_around_one_and_two_workgroups_per_compute_unit(B, H, N, d, f16, causal):
     import torch
     w = si.small_workload(B, H, N, d, seed=9750 + N + d)
@@ -306,6 +309,29 @@ def test_pipelined_dk_dv_of_small_launches(B, H, N, f16, packed):
     check(w, x, run_ex(w, x, f16, False, packed), f16, False)
 
 
+# The per-query scalars that dQ leaves in the workspace for dK and dV, LSE * log2(e) and -delta, reach to the end of the last 64 queries with
+# +inf and 0, whatever block of rows ends there: 64, 96 (also half way through the last 64) and 128 rows, two groups, four and one, and pairs.
+@pytest.mark.parametrize("B,H,N,d", [(1, 3, 300, 64), (1, 2, 1025, 64), (2, 30, 270, 64), (2, 30, 270, 80), (1, 48, 480, 64), (1, 16, 1030, 64),
+                                     (1, 16, 1025, 80), (1, 32, 785, 64), (1, 86, 321, 64), (1, 51, 1025, 64), (1, 51, 1060, 64), (2, 3, 100, 64)])
+def test_the_scalars_left_for_dk_and_dv_reach_to_the_end_of_the_last_tile(B, H, N, d):
+    import math
+    import torch
+    import paper_2309_16669_amd as av
+    gen = torch.Generator(device="cuda").manual_seed(N + d)
+    q, k, v, dO = (torch.randn(B, N, H, d, device="cuda", generator=gen).bfloat16() for _ in range(4))
+    o, dq, lse = torch.empty_like(q), torch.empty_like(q), torch.empty(B, H, N, device="cuda")
+    ws = torch.empty(av.attn_bwd_workspace_bytes(B, H, N, d), dtype=torch.uint8, device="cuda").fill_(255)
+    av.attn_fwd(q, k, v, o, lse, 0.125)
+    av.attn_bwd_dq(q, k, v, o, lse, dO, dq, 0.125, ws)
+    npad = (N + 63) // 64 * 64
+    got = ws[:B * H * 2 * npad * 4].view(torch.float32).view(B, H, 2, npad)
+    assert bool((got[:, :, 0, N:] == math.inf).all()) and bool((got[:, :, 1, N:] == 0).all())
+    delta = (o.double() * dO.double()).sum(-1).transpose(1, 2)
+    # one rounding of the product; delta: d additions in fp32 of products of about 0.1
+    assert float((got[:, :, 0, :N].double() - lse.double() * math.log2(math.e)).abs().max()) <= 2.0 ** -22 * float(lse.abs().max()) * 1.5
+    assert float((got[:, :, 1, :N].double() + delta).abs().max()) <= d * 2.0 ** -24 * float((o.double() * dO.double()).abs().sum(-1).max())
+
+
 # Units of 32 queries that lie wholly past the end, in tiles past the end (an odd number of tiles in two groups) and in half tiles, are
 # left out: a key with an infinite component that no query sees (weights of exactly 0, as for a finite one far below the others) gets dK and
 # dV of 0 and changes nothing of the other keys'.  64, 96 and 128 rows, pipelined; then the other kernels.
@@ -318,14 +344,14 @@ def test_units_past_the_end_leave_keys_with_infinite_components_alone(H, N, f16)
     gen = torch.Generator(device="cuda").manual_seed(N + H)
     q, k, v, dO = (torch.randn(1, N, H, 64, device="cuda", generator=gen).to(dt) for _ in range(4))
     q[..., 0] = 1.0
-    ws = torch.empty(av.attn_bwd_workspace_bytes(1, H, N, 64), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(av.attn_bwd_workspace_bytes(1, H, N, 64), dtype=torch.uint8, device="cuda").fill_(255)
     outs = []
     for low in (-30000.0, float("-inf")):
         k[:, [40, N - 3], :, 0] = low
         o, dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(4))
         lse = torch.full((1, H, N), float("nan"), device="cuda")
         av.attn_fwd_ex(q, k, v, o, lse, 0.125, False)
-        av.attn_bwd_ex(q, k, v, o, lse, dO, dq, dk, dv, 0.125, ws.fill_(255), False)
+        av.attn_bwd_ex(q, k, v, o, lse, dO, dq, dk, dv, 0.125, ws, False)
         torch.cuda.synchronize()
         outs.append((o, lse, dq[..., 1:], dk, dv))      # (dQ of channel 0 is a product of that component with 0)
     for name, a, b in zip(("o", "lse", "dq", "dk", "dv"), *outs):
@@ -379,18 +405,21 @@ def test_dq_in_pairs_of_blocks_at_its_shortest(B, H, N, f16, packed):
 def test_short_last_workgroups_do_not_open_another_round(heads, more, N, paired):
     import torch
     gen = torch.Generator(device="cuda").manual_seed(N + heads)
-    x = [torch.randn(more, N, 1, 64, device="cuda", generator=gen).bfloat16() for _ in range(4)]
-    got = [_dq_of(*(t[:h] for t in x)) for h in (heads, more)]
+    q, k, v, dO = (torch.randn(more, N, 1, 64, device="cuda", generator=gen).bfloat16() for _ in range(4))
+    # one forward for both launches: its own cut of the rows is not what is looked at
+    import paper_2309_16669_amd as av
+    o, lse = torch.empty_like(q), torch.empty(more, 1, N, device="cuda")
+    av.attn_fwd_ex(q, k, v, o, lse, 0.125, False)
+    got = [_dq_of(*(t[:h] for t in (q, k, v, o, lse, dO))) for h in (heads, more)]
     assert torch.equal(got[0].view(torch.int16), got[1][:heads].view(torch.int16)) != paired
 
 
-def _dq_of(q, k, v, dO):
+def _dq_of(q, k, v, o, lse, dO):
     import torch
     import paper_2309_16669_amd as av
     B, N, H, d = q.shape
-    o, dq, lse = torch.empty_like(q), torch.full_like(q, float("nan")), torch.empty(B, H, N, device="cuda")
-    ws = torch.empty(av.attn_bwd_workspace_bytes(B, H, N, d), dtype=torch.uint8, device="cuda")
-    av.attn_fwd_ex(q, k, v, o, lse, 0.125, False)
+    dq = torch.full_like(q, float("nan"))
+    ws = torch.empty(av.attn_bwd_workspace_bytes(B, H, N, d), dtype=torch.uint8, device="cuda").fill_(255)
     av.attn_bwd_dq(q, k, v, o, lse, dO, dq, 0.125, ws)
     torch.cuda.synchronize()
     return dq

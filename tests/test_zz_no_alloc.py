@@ -25,7 +25,7 @@ def _both_ways(w):
     lse = torch.empty((w.B, w.H, w.N), dtype=torch.float32, device="cuda")
     av.attn_fwd(q, k, v, o, lse, w.scale)
     ref = [torch.full_like(q, float("nan")) for _ in range(3)]
-    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(av.attn_bwd_workspace_bytes(w.B, w.H, w.N, w.d), dtype=torch.uint8, device="cuda").fill_(255)
     av.attn_bwd(q, k, v, o, lse, dO, *ref, w.scale, ws)
     got = [torch.full_like(q, float("nan")) for _ in range(3)]
     p = lambda t: ctypes.c_void_p(t.data_ptr())
