@@ -33,6 +33,8 @@
 // address a register and the instruction's offset) and descriptors once per head: 3072 x 196 180 -> 166 (3.7 TB/s), x 160
 // 130 -> 121, x 130 114 -> 104, x 224 196 -> 184, x 256 225 -> 218, 8000 x 200 causal 416 -> 394, 16384 x 77 causal 267 -> 261,
 // x 64 221 -> 216, x 40 153 -> 146; 8 x 200 14.0 -> 12.6, 384 x 200 29.0 -> 27.7, 768 x 128 causal 26.0 -> 25.0, the smallest equal.
+// Where every workgroup has one head and nearly every compute unit a workgroup, a launch is one burst of requests, which this layout makes
+// in half lines: 200 to 256 heads 0.92 to 1.005 of the time without mask, but 0.94 to 1.023 with one (256 x 180 14.45 -> 14.74).
 // Against two kernels of avion_bwd.h of one group each it was 0.60 to 0.99 of their time at 1 to 768 heads x 129..256 before
 // that; two kernels of two groups each (64-row blocks, two groups) were faster by 0 to 4 % at 196..224
 // tokens and 8 to 14 % at 240..256 below 96 heads.
@@ -77,6 +79,11 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
     // Masked instances of 6 to 8 blocks need up to 44 bytes of scratch with the early request: 8000 heads x 200 435 us instead of
     // 394, 1024 x 256 70.1 instead of 61.4.  The other walking instances do not: behind it, 3072 x 196 174 instead of 166.
     constexpr bool EARLY_TR = Cfg::EARLY_TR && !(CAUSAL && Cfg::WALK && NB >= 6);
+    // Eight blocks without mask: dQ of the block before is written in two halves, one to each half of the vector work.  In one piece its eight
+    // products are compiled to a chain of their own, each behind a wait for its operands (208 heads x 228 18.8 us instead of 18.05, 16 x 240 14.97
+    // instead of 14.18, 3072 x 240 214 instead of 207).  With fewer blocks the compiler spreads them by itself (in halves 180 tokens 1 to 3 %
+    // slower), with a mask each is behind a branch (equal or slower).
+    constexpr bool SPLIT_DQ = Cfg::WALK && NB == 8 && !CAUSAL;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, lane = tid % 64, l32 = lane % 32, g = lane / 32;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -184,20 +191,21 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
             load_o(next);
         }
 
-        // dQ^T of block jj, this wavefront's 16 channels: K^T dS^T over the keys
+        // dQ^T of block jj, this wavefront's 16 channels: K^T dS^T over the keys, or over 32-key steps s0 .. s1 - 1 of them
         f32x4 dqa[QT];
-        auto form_dq = [&](int jj) {
+        auto form_dq_part = [&](int jj, int s0, int s1) {
             const char* dsj = ds + (jj & 1) * Cfg::DS_BYTES;
             const int nk = CAUSAL ? min(NB, jj + 1) : NB;
 #pragma unroll
             for (int t = 0; t < QT; ++t) {
-                dqa[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (s0 == 0) dqa[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int s = 0; s < NB; ++s)
+                for (int s = s0; s < s1; ++s)
                     if (!CAUSAL || s < nk)
                         dqa[t] = E::mfma16(ktf[s], tr16_frag(dsj, Cfg::DS_STRIDE, lane, QT == 1 ? q16 : 16 * t, s), dqa[t]);
             }
         };
+        auto form_dq = [&](int jj) { form_dq_part(jj, 0, NB); };
         auto store_dq = [&](int jj) {
 #pragma unroll
             for (int t = 0; t < QT; ++t) {
@@ -230,13 +238,14 @@ avion_bwd_head_kernel(const raw16* __restrict__ q, const raw16* __restrict__ k, 
                 s = E::mfma(aq, kf[ks], ks == 0 && !MASK ? f32x16_zero() : s);
                 dp = E::mfma(ag, vf[ks], dp);
             }
-            if (decltype(with_dq)::value && Cfg::WALK) form_dq(j - 1);
+            if (decltype(with_dq)::value && Cfg::WALK && !SPLIT_DQ) form_dq(j - 1);
             char* mine = dsj + (k0 + l32) * Cfg::DS_STRIDE + 8 * g;
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 f32x4 l4[2];
 #pragma unroll
                 for (int a4 = 0; a4 < 2; ++a4) l4[a4] = *reinterpret_cast<const f32x4*>(rowv + 8 * (2 * half + a4));
+                if (decltype(with_dq)::value && SPLIT_DQ) form_dq_part(j - 1, half * (NB / 2), half ? NB : NB / 2);
                 frag8 tg[CT], tq[CT];
                 auto load_tr = [&] {
 #pragma unroll
