@@ -38,18 +38,18 @@ MEASURED_HBM_BYTES_PER_LAUNCH = {
     # (2.0 x FETCH_SIZE + 1.0 x WRITE_SIZE) KiB, the factors being what the same counters read for a plain copy of
     # known size.  Measured offline on separate q/k/v tensors with N(0,1) operands; any other run prints null.
     # "avion_dq_kernel" stands for the dQ phase: on vitb_batch and vitb_long it runs as avion_dq_pair_kernel.
-    ("vitb_batch", "bf16", "avion_fwd_kernel"): (3.1100e+08, "profiles/vitb_batch_bf16.txt"),
-    ("vitb_batch", "bf16", "avion_dq_kernel"): (4.8630e+08, "profiles/vitb_batch_bf16.txt"),
-    ("vitb_batch", "bf16", "avion_dkdv_kernel"): (4.7000e+08, "profiles/vitb_batch_bf16.txt"),
-    ("vitb_batch", "f16", "avion_fwd_kernel"): (3.1100e+08, "profiles/vitb_batch_f16.txt"),
-    ("vitb_batch", "f16", "avion_dq_kernel"): (4.8950e+08, "profiles/vitb_batch_f16.txt"),
-    ("vitb_batch", "f16", "avion_dkdv_kernel"): (4.7000e+08, "profiles/vitb_batch_f16.txt"),
-    ("vith_d80", "bf16", "avion_fwd_kernel"): (1.3830e+08, "profiles/vith_d80.txt"),
-    ("vith_d80", "bf16", "avion_dq_kernel"): (2.1190e+08, "profiles/vith_d80.txt"),
-    ("vith_d80", "bf16", "avion_dkdv_kernel"): (2.2060e+08, "profiles/vith_d80.txt"),
-    ("vitb_long", "bf16", "avion_fwd_kernel"): (1.5810e+08, "profiles/vitb_long.txt"),
-    ("vitb_long", "bf16", "avion_dq_kernel"): (2.5400e+08, "profiles/vitb_long.txt"),
-    ("vitb_long", "bf16", "avion_dkdv_kernel"): (2.4400e+08, "profiles/vitb_long.txt"),
+    ("vitb_batch", "bf16", "avion_fwd_kernel"): (3.1110e+08, "profiles/vitb_batch_bf16.txt"),
+    ("vitb_batch", "bf16", "avion_dq_kernel"): (4.8720e+08, "profiles/vitb_batch_bf16.txt"),
+    ("vitb_batch", "bf16", "avion_dkdv_kernel"): (4.6980e+08, "profiles/vitb_batch_bf16.txt"),
+    ("vitb_batch", "f16", "avion_fwd_kernel"): (3.1110e+08, "profiles/vitb_batch_f16.txt"),
+    ("vitb_batch", "f16", "avion_dq_kernel"): (4.8680e+08, "profiles/vitb_batch_f16.txt"),
+    ("vitb_batch", "f16", "avion_dkdv_kernel"): (4.6990e+08, "profiles/vitb_batch_f16.txt"),
+    ("vith_d80", "bf16", "avion_fwd_kernel"): (1.3820e+08, "profiles/vith_d80.txt"),
+    ("vith_d80", "bf16", "avion_dq_kernel"): (2.1250e+08, "profiles/vith_d80.txt"),
+    ("vith_d80", "bf16", "avion_dkdv_kernel"): (2.1920e+08, "profiles/vith_d80.txt"),
+    ("vitb_long", "bf16", "avion_fwd_kernel"): (1.5780e+08, "profiles/vitb_long.txt"),
+    ("vitb_long", "bf16", "avion_dq_kernel"): (2.5370e+08, "profiles/vitb_long.txt"),
+    ("vitb_long", "bf16", "avion_dkdv_kernel"): (2.4410e+08, "profiles/vitb_long.txt"),
 }
 PREWARM_SECONDS = 0.3
 

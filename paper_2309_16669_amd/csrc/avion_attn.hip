@@ -354,8 +354,8 @@ Cut fwd_cut(const Fill& f, int d, bool causal)
     if (t >= 6 && f.w128 <= kComputeUnits) return {4, t >= 16 ? 4 : 2};
     // Up to two workgroups of 96 rows per compute unit: two groups each, three wavefronts per SIMD instead of one or two.  24 x 1568 32.4 ->
     // 29.4 us, 16 x 2400 46.5 -> 40.9, 12 x 3136 59.5 -> 52.1, 40 x 785 18.9 -> 18.1; 0.93 of the time in the mean of 189 shapes, 1.03 at most; at 300 to
-    // 350 tokens up to 1.08.  (Beyond it and up to two of 128 rows, 128 rows in two groups would be 0.97 in the mean; one group stays there:
-    // its bits are those of larger launches, which a test of dQ's cuts takes them to be.)
+    // 350 tokens up to 1.08.  (Beyond it and up to two of 128 rows, 128 rows in two groups measured 0.97 in the mean; that line is not drawn
+    // yet, and one group stays there.)
     if (!causal && t >= 7 && f.w96 <= 2 * kComputeUnits) return {3, 2};
     // causal blocks are of unequal length, which shorter ones even out: 0.80 of the time up to 560 workgroups of 64 rows (30 shapes,
     // none slower), 1.05 and more from 600 on; two groups of 128 rows up to 512 0.93 (153 shapes, 1.04 at most)
@@ -469,11 +469,13 @@ constexpr bool kBwdCut = KG <= 2 || (D == 64 && NW == 2);
 // dQ in two blocks of queries per wavefront (avion_pair.h), for launches beyond one workgroup of 128 rows per compute unit.  Its
 // workgroups take 256 rows, and a compute unit does one in the time of 1.75 of avion_dq_kernel's 128-row ones, whether it has
 // one at a time or two; both launches end with the unit that has most.  So it is taken where its share of workgroups per unit, rounded
-// up, is at most 7/12 of the other kernel's.  Measured over 1100 shapes, time over avion_dq_kernel's by the two shares: 1 of 2 0.92 (341 shapes),
-// 2 of 4 0.86 (121), 3 of 6 0.91, 4 of 7 0.96, 5 of 9 0.95, 7 of 12 0.96; on the other side 2 of 2 1.43, 2 of 3 1.10, 3 of 4 1.17, 3 of 5 1.03, 5 of 8
-// 1.00, 6 of 10 0.98, 7 of 11 1.03.  A head's short last workgroup counts as one.  Us: 32 x 3136 152.8 -> 121.5, 64 x 1568 81.4 -> 67.8, 24 x
-// 1568 40.5 -> 36.3, 80 x 1200 66.2 -> 56.1, 384 x 1568 400 -> 363.  Below 500 tokens (700 from five shares on) its longer prologue
-// takes what it gives: at 400 0.97 to 1.04 of the time, at 500 to 700 and six shares 1.00.
+// up, is at most 7/12 of the other kernel's.  Time over avion_dq_kernel's by the two shares (131 shapes, repeated launches in a graph): 1 of 2
+// 0.89 (0.96 at most), 2 of 4 0.85 (0.93), 3 of 6 0.88 (0.98), 4 of 7 0.94, 5 of 9 0.93, 6 of 11 0.92, 7 of 12 0.96 (0.98), more 0.87 to 0.96; on
+// the other side (single launches) 2 of 2 1.43, 2 of 3 1.10, 3 of 4 1.17, 3 of 5 1.03, 5 of 8 1.00, 6 of 10 0.98, 7 of 11 1.03.  A head's short last
+// workgroup counts as one.  Us: 32 x 3136 152.8 -> 121.5, 64 x 1568 81.4 -> 67.8, 24 x 1568 40.5 -> 36.3, 80 x 1200 66.2 -> 56.1, 384 x 1568
+// 400 -> 363, 192 x 784 65.0 -> 60.0 (67.6 -> 67.1 between the other kernels of an encoder layer, whose caches are cold and rows packed).
+// Below 500 tokens (700 from five shares on) its longer prologue takes what it gives: at 400 0.97 to 1.04 of the time, at 500 to 700 and six
+// shares 1.00.
 bool by_pair(long long heads, int N, int d, Variant var)
 {
     const long long wgs = heads * ((N + 127) / 128), pair_wgs = heads * (((N + 31) / 32 + kPairBlocks - 1) / kPairBlocks);
@@ -516,9 +518,10 @@ int dq_impl(const void* q, const void* k, const void* v, const void* o, const fl
     });
 }
 
-// dK and dV by the pipelined kernel (avion_flow.h): always two groups.  Its time over avion_dkdv_kernel's, 400 shapes: 64 rows 0.97 (5 tiles) to
-// 0.88 (14) against two groups and 0.89 to 0.93 against four; 96 rows 1.11 at 5 tiles, 0.98 (1.02 at most) at 6 to 8, 0.97 at 9, 0.91 at 30 and
-// more; 128 rows 1.03 at 6 to 8 tiles, 0.99 at 12 to 14, 0.98 at 15, 0.95 at 30 (its longer start).
+// dK and dV by the pipelined kernel (avion_flow.h): always two groups.  Its time over avion_dkdv_kernel's in the same cut (94 shapes, launches
+// in a graph): 64 rows 0.96 at 5 tiles, 0.91 at 9, 0.89 at 14 (two groups there), 0.89 to 0.92 from 15 to 45 (four); 96 rows 1.03 at 5 and 6, 1.00 at
+// 7, 0.98 to 1.01 at 8, 0.97 at 9, 0.95 at 12, 0.92 at 45; 128 rows 0.99 at 6 to 8, 0.97 at 12 to 16, 0.95 at 45.  The lines at 8 and 15 tiles were
+// drawn when it still walked units past the end (128 rows then 1.03 at 6 to 8 tiles, 0.99 at 12 to 14).
 bool by_flow(Cut c, const Fill& f, int d, Variant var)
 {
     return d == 64 && !var.causal && c.kg > 1 && f.tiles >= (c.nw == 2 ? 0 : c.nw == 3 ? 8 : 15);

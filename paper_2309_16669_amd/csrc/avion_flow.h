@@ -4,15 +4,16 @@
 // What bounds that kernel there is the latency of one wavefront's unit: two wavefronts per SIMD cannot fill each other's
 // waits for LDS and for the last product of a chain.  Here the wavefront's own products stand beside its vector work: while the
 // scores of 32 queries become weights, dV and dK of the 32 before them and S and dP of the 32 after them are formed, and every
-// operand is requested eight products ahead into the registers that the product eight before it has left.  248 registers, two
+// operand is requested eight products ahead into the registers that the product eight before it has left.  242 registers, two
 // wavefronts per SIMD.  In a loop without tile fetches a unit of the chain takes 832 cycles at two wavefronts per SIMD (1052 at
 // one), of this form 676 (859).
 // Tiles as in avion_pair.h, four buffers: a barrier in the middle of a tile, when nothing of the tile before is needed any more (the
 // columns of its last unit were taken in the first half tile), certifies that the next one has landed and lets the one three ahead
 // be fetched.
-// Measured, us, avion_dkdv_kernel -> this: 16 heads x 785 13.9 -> 12.4, 8 x 1568 19.9 (four groups) -> 17.9, 6 x 3000 43.9 -> 39.8, 12 x 1568
-// 26.3 -> 24.7; on the other side of the lines 32 x 785 17.7 -> 18.2, 48 x 400 11.9 -> 12.3.  Waiting for three tiles instead of one before
-// the first unit cost 0.2 to 0.8 us more, the loads of a tile one by one instead of in fours and fives up to 2.
+// Measured, us, avion_dkdv_kernel -> this: 16 heads x 785 13.6 -> 12.0, 8 x 1568 19.8 (four groups) -> 17.4, 6 x 3000 43.4 -> 38.3, 12 x 1568
+// 26.0 -> 23.4; on the other side of the lines 36 x 789 17.4 -> 16.8, 61 x 289 9.9 -> 10.1.  Waiting for three tiles instead of one before
+// the first unit cost 0.2 to 0.8 us more, the loads of a tile one by one instead of in fours and fives up to 2, walking units past the end (an odd
+// tile's worth of zeros, or half of one) 0.1 to 0.9.
 // On a full chip, one group, it is no faster than three wavefronts per SIMD of that kernel (avion_pair.h).
 #pragma once
 #include "avion_pair.h"

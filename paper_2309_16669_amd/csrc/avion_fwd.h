@@ -39,8 +39,9 @@
 //
 // What bounds it on a full chip: vector issue and, behind it, LDS.  Padded rows of 144 bytes -> quad_at's layout (no bank conflicts,
 // an eighth less deposited, a tile's loads in one statement), us, same bits: 384 heads x 1568 285.7 -> 280.9, causal 172.1 -> 168.7, 96 x
-// 3000 253.8 -> 249.3, 3072 x 196 78.1 -> 76.0, 16384 x 77 183.4 -> 175.6 (causal 176.4), x 40 causal 101.5 -> 95.8, 8 x 77 causal 5.63 -> 5.26,
-// 8 x 1568 15.3 -> 14.8, 16 x 400 8.10 -> 7.63; 0.93 to 1.007 of the time over 31 shapes.  (dK/dV in it, at three wavefronts per SIMD,
+// 3000 253.8 -> 249.3, 3072 x 196 78.1 -> 76.0, 16384 x 77 183.4 -> 175.6 (causal 176.4), x 40 causal 101.5 -> 95.8; 0.93 to 1.007 of the time over 31
+// shapes.  Launches in a graph: 8 x 77 causal 4.92 -> 4.63, 8 x 600 8.91 -> 8.26, 16 x 400 7.96 -> 7.39.  Of the LDS cycles on 384 x 1568, 2.9 %
+// instead of 34 % are conflicts, and LDS is busy 25 % of the launch instead of 37.  (dK/dV in it, at three wavefronts per SIMD,
 // 452.7 -> 465.2: the two addresses more take registers that keep operands in flight.)
 //
 // Template parameters: head dim D, wavefronts per group NW, groups KG, element format E (Bf16 or F16),
@@ -61,7 +62,8 @@ struct FwdCfg {
     static constexpr int LDS_BYTES = KG * Ring::LDS_BYTES > SAFE_BYTES ? KG * Ring::LDS_BYTES : SAFE_BYTES;
     // wavefronts per SIMD the register budget is sized for: what LDS lets a compute unit hold, at most 4;
     // with several groups one workgroup per compute unit, with two groups up to two: six wavefronts each may put four on one SIMD
-    // (40 heads x 785 18.4 -> 22.4 us at 130 registers instead of 128)
+    // (40 heads x 785 18.4 -> 22.4 us at 130 registers instead of 128; blocks of 64 rows, which never need it, take 128 to 130 either way
+    // and the same time: 8 x 77 causal 4.66, 4.68 without)
     static constexpr int WG_PER_CU = 160 * 1024 / LDS_BYTES;
     static constexpr int WAVES_PER_SIMD = KG == 2 && D == 64 ? 4 : KG > 1 ? (NW * KG + 3) / 4 : WG_PER_CU * NW / 4 > 4 ? 4 : WG_PER_CU * NW / 4;
 };
